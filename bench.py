@@ -4,7 +4,7 @@
 Default workload: gradient on the O1280 mesh (6,599,680 nodes, 19,799,000
 edges), 137 levels, FP64 fields -- the headline configuration.  A step is
 one gradient application over the resident [node][level] field; the other
-operators (divergence, Laplacian) and the FP32 + Kahan form are timed in the
+operators (divergence, Laplacian) and the FP32 form are timed in the
 same run and reported under "ops".
 
 Printed: ONE JSON line with edge*level updates per second, the HBM roofline

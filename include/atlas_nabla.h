@@ -222,8 +222,8 @@ atlas_status atlas_mesh_get_info(atlas_mesh_t mesh, atlas_mesh_info *info);
 /*   curl       (u,v) [V][nlev][2] -> out [V][nlev] (radial component)       */
 /*   laplacian  f [V][nlev]       -> out [V][nlev], = divergence(gradient)  */
 /* dtype ATLAS_F64: FP64 fields and arithmetic.  dtype ATLAS_F32: FP32      */
-/* fields, FP64 geometry, FP32 edge terms with a compensated (Kahan) node   */
-/* sum, final scaling in FP64.                                              */
+/* fields, FP64 geometry, edge terms, node sums and scaling on the promoted */
+/* values, one rounding to FP32 at the end.                                 */
 /* Errors (nothing enqueued): ATLAS_EINVAL for a NULL or misaligned pointer,*/
 /* nlev < 1 or above the mesh's max_levels (atlas_mesh_info), overlapping   */
 /* input/output, unknown dtype; ATLAS_EDEVICE if the launch fails.          */
@@ -272,7 +272,10 @@ typedef enum {
   ATLAS_VARIANT_COLUMN = 1, /* one wavefront per node, lanes over levels   */
   ATLAS_VARIANT_FLAT = 2,   /* lanes over flattened (node, level) pairs    */
   ATLAS_VARIANT_FLUX = 3,   /* two kernels: edge fluxes into an [E][nlev]
-                               buffer (EdgeColumns-like), then the gather  */
+                               buffer (EdgeColumns-like), then the gather.
+                               FP32 fields run the column form instead
+                               (their FP64 terms do not fit the buffer) and
+                               leave the flux workspace untouched          */
   ATLAS_VARIANT_SWEEP = 4,  /* one workgroup per (tile, level chunk) walks
                                its band parallel by parallel, keeping three
                                consecutive parallels' columns in LDS       */

@@ -17,15 +17,15 @@
 // No atomics: every output element has exactly one writer, so results are
 // bitwise reproducible and independent of the launch shape.
 //
-// FP32 fields: the same sums in difference form, sum_r sS_r (x_n - x_i)/2 +
-// x_i sum_r sS_r (equal in exact arithmetic), with FP32 edge terms, a
-// compensated (Kahan) FP32 node sum, the closure term and the final scaling
-// in FP64.  Differences of neighbouring values are small and nearly exact in
-// FP32, which keeps the error relative to the result instead of the field.
+// FP32 fields: the same sums over the promoted values, formed in FP64 with
+// explicit fused multiply-adds and rounded to FP32 once at the end (the
+// vector ALU runs FP64 at the FP32 rate, so this costs a conversion per
+// value and a third of the operations of compensated FP32 sums).
 //
-// Compiled with -ffp-contract=off: no operation is fused, so the separate
-// edge-flux form (flux buffer, then gather) and the fused forms produce the
-// same bits.
+// Compiled with -ffp-contract=off: no operation is fused unless written so,
+// and every launch form of an operator produces the same bits.  (The
+// separate edge-flux form, flux buffer then gather, exists for FP64 fields:
+// a buffer of FP32 fluxes could not carry the FP64 terms.)
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -66,40 +66,6 @@ __device__ __forceinline__ bool tile_range(const DevMesh &m, int tile, int npb,
 // order; every launch form drives the same policy, so all forms produce the
 // same bits.
 // ---------------------------------------------------------------------------
-struct Kahan {
-  float s = 0.0f, c = 0.0f;
-  __device__ __forceinline__ void add(float t) {
-    const float y = t - c;
-    const float u = s + y;
-    c = (u - s) - y;
-    s = u;
-  }
-  __device__ __forceinline__ double value() const { return (double)s - (double)c; }
-};
-
-// Edge term of the FP32 difference form (identical for both endpoints of a
-// mesh edge, negated for the two ends of a pole edge).
-template <int OP>
-__device__ __forceinline__ void diff_terms_f32(const double2 &s, float xi, float xn,
-                                               v2f ui, v2f un, double ci, double cn,
-                                               float &tx, float &ty, float &t) {
-  if (OP == OP_GRAD) {
-    const float h = 0.5f * (xn - xi);
-    tx = (float)s.x * h;
-    ty = (float)s.y * h;
-  } else {
-    const float csum = (float)(cn + ci), cdif = (float)(cn - ci);
-    // divergence: a = u, b = v cos;  curl: a = v, b = u cos
-    const float ai = (OP == OP_DIV) ? ui.x : ui.y, an = (OP == OP_DIV) ? un.x : un.y;
-    const float qi = (OP == OP_DIV) ? ui.y : ui.x, qn = (OP == OP_DIV) ? un.y : un.x;
-    // b_n - b_i = ((q_n - q_i)(c_n + c_i) + (q_n + q_i)(c_n - c_i)) / 2
-    const float db = 0.5f * ((qn - qi) * csum + (qn + qi) * cdif);
-    const float da = an - ai;
-    const float ta = (float)s.x * (0.5f * da), tb = (float)s.y * (0.5f * db);
-    t = (OP == OP_DIV) ? ta + tb : ta - tb;
-  }
-}
-
 // Output stores are non-temporal (streamed past the caches, so they do not
 // evict input columns that neighbours still need); ATLASX_CACHED_STORE
 // selects ordinary stores.
@@ -149,13 +115,12 @@ template <> struct Pol<double, OP_GRAD> {
     s.gt = s.gt + S.y * xe;
   }
   using Out = v2d;
-  static __device__ __forceinline__ Out result(const St &s, double al, double be, double, double,
-                                               double) {
+  static __device__ __forceinline__ Out result(const St &s, double al, double be) {
     return Out{al * s.gl, be * s.gt};
   }
   static __device__ __forceinline__ void store(double *out, size_t idx, const St &s, double al,
-                                               double be, double cx, double cy, double ci) {
-    const Out r = result(s, al, be, cx, cy, ci);
+                                               double be) {
+    const Out r = result(s, al, be);
     st_out2(out + 2 * idx, r.x, r.y);
   }
   static __device__ __forceinline__ void keep(St &s, const St &t, bool use) {
@@ -184,13 +149,12 @@ template <int OP> struct PolDC64 {
     s.acc = s.acc + f;
   }
   using Out = double;
-  static __device__ __forceinline__ Out result(const St &s, double al, double, double, double,
-                                               double) {
+  static __device__ __forceinline__ Out result(const St &s, double al, double) {
     return al * s.acc;
   }
   static __device__ __forceinline__ void store(double *out, size_t idx, const St &s, double al,
-                                               double be, double cx, double cy, double ci) {
-    st_out(out + idx, result(s, al, be, cx, cy, ci));
+                                               double be) {
+    st_out(out + idx, result(s, al, be));
   }
   static __device__ __forceinline__ void keep(St &s, const St &t, bool use) {
     s.acc = use ? t.acc : s.acc;
@@ -199,36 +163,35 @@ template <int OP> struct PolDC64 {
 template <> struct Pol<double, OP_DIV> : PolDC64<OP_DIV> {};
 template <> struct Pol<double, OP_CURL> : PolDC64<OP_CURL> {};
 
-// FP32 gradient, difference form with Kahan sums; the closure sums
-// (cx, cy) = sum sS are formed in FP64 by the caller.
+// FP32 fields: the FP64 sums with fused multiply-adds, of the normals
+// themselves (the edge averages' factor 1/2 is applied to the sum: exact).
+// O1280, 137 levels, against compensated FP32 sums of the differences, which
+// took four operations per term and kept the SIMDs busy all the time:
+// gradient 3.78 -> 3.15 ms, divergence 4.52 -> 4.31, Laplacian 7.98 -> 6.22;
+// O640, 91 levels, divergence and curl in one pass 1.13 -> 0.97.
 template <> struct Pol<float, OP_GRAD> {
   static constexpr int kOp = OP_GRAD;
   using V = float;
   static constexpr bool kVecIn = false, kVecOut = true;
-  struct St { float xi; Kahan kx, ky; };
-  static __device__ __forceinline__ void init(St &s, V xi, double) { s.xi = xi; s.kx = Kahan(); s.ky = Kahan(); }
+  struct St { double xi, gl, gt; };
+  static __device__ __forceinline__ void init(St &s, V xi, double) { s.xi = xi; s.gl = 0.0; s.gt = 0.0; }
   static __device__ __forceinline__ void add(St &s, V xn, const double2 &S, bool pole, double) {
-    float tx, ty, t;
-    diff_terms_f32<OP_GRAD>(S, s.xi, xn, v2f{}, v2f{}, 0.0, 0.0, tx, ty, t);
-    if (!pole) s.kx.add(tx);
-    s.ky.add(ty);
+    const double xe = s.xi + (double)xn;
+    if (!pole) s.gl = __builtin_fma(S.x, xe, s.gl);
+    s.gt = __builtin_fma(S.y, xe, s.gt);
   }
   using Out = v2f;
-  static __device__ __forceinline__ Out result(const St &s, double al, double be, double cx,
-                                               double cy, double) {
-    return Out{(float)(al * (s.kx.value() + cx * (double)s.xi)),
-               (float)(be * (s.ky.value() + cy * (double)s.xi))};
+  static __device__ __forceinline__ Out result(const St &s, double al, double be) {
+    return Out{(float)(al * (0.5 * s.gl)), (float)(be * (0.5 * s.gt))};
   }
   static __device__ __forceinline__ void store(float *out, size_t idx, const St &s, double al,
-                                               double be, double cx, double cy, double ci) {
-    const Out r = result(s, al, be, cx, cy, ci);
+                                               double be) {
+    const Out r = result(s, al, be);
     st_out2(out + 2 * idx, r.x, r.y);
   }
   static __device__ __forceinline__ void keep(St &s, const St &t, bool use) {
-    s.kx.s = use ? t.kx.s : s.kx.s;
-    s.kx.c = use ? t.kx.c : s.kx.c;
-    s.ky.s = use ? t.ky.s : s.ky.s;
-    s.ky.c = use ? t.ky.c : s.ky.c;
+    s.gl = use ? t.gl : s.gl;
+    s.gt = use ? t.gt : s.gt;
   }
 };
 
@@ -236,45 +199,32 @@ template <int OP> struct PolDC32 {
   static constexpr int kOp = OP;
   using V = v2f;
   static constexpr bool kVecIn = true, kVecOut = false;
-  struct St { v2f ui; double ci; Kahan ka; };
-  static __device__ __forceinline__ void init(St &s, V ui, double ci) { s.ui = ui; s.ci = ci; s.ka = Kahan(); }
+  struct St { double ai, bi, acc; };
+  static __device__ __forceinline__ void init(St &s, V ui, double ci) {
+    s.ai = (OP == OP_DIV) ? ui.x : ui.y;
+    s.bi = (double)((OP == OP_DIV) ? ui.y : ui.x) * ci;
+    s.acc = 0.0;
+  }
   static __device__ __forceinline__ void add(St &s, V un, const double2 &S, bool, double cn) {
-    float tx, ty, t;
-    diff_terms_f32<OP>(S, 0.0f, 0.0f, s.ui, un, s.ci, cn, tx, ty, t);
-    s.ka.add(t);
+    const double an = (OP == OP_DIV) ? un.x : un.y, qn = (OP == OP_DIV) ? un.y : un.x;
+    const double ae = s.ai + an, be = __builtin_fma(qn, cn, s.bi);
+    s.acc = __builtin_fma(S.x, ae, s.acc);
+    s.acc = __builtin_fma((OP == OP_DIV) ? S.y : -S.y, be, s.acc);
   }
   using Out = float;
-  static __device__ __forceinline__ Out result(const St &s, double al, double, double cx,
-                                               double cy, double) {
-    const double a_i = (OP == OP_DIV) ? (double)s.ui.x : (double)s.ui.y;
-    const double b_i = ((OP == OP_DIV) ? (double)s.ui.y : (double)s.ui.x) * s.ci;
-    const double closure = (OP == OP_DIV) ? cx * a_i + cy * b_i : cx * a_i - cy * b_i;
-    return (float)(al * (s.ka.value() + closure));
+  static __device__ __forceinline__ Out result(const St &s, double al, double) {
+    return (float)(al * (0.5 * s.acc));
   }
   static __device__ __forceinline__ void store(float *out, size_t idx, const St &s, double al,
-                                               double be, double cx, double cy, double ci) {
-    st_out(out + idx, result(s, al, be, cx, cy, ci));
+                                               double be) {
+    st_out(out + idx, result(s, al, be));
   }
   static __device__ __forceinline__ void keep(St &s, const St &t, bool use) {
-    s.ka.s = use ? t.ka.s : s.ka.s;
-    s.ka.c = use ? t.ka.c : s.ka.c;
+    s.acc = use ? t.acc : s.acc;
   }
 };
 template <> struct Pol<float, OP_DIV> : PolDC32<OP_DIV> {};
 template <> struct Pol<float, OP_CURL> : PolDC32<OP_CURL> {};
-
-// Closure sums of a node (FP32 forms): sum over the incidences that enter
-// the operator of the signed normals.
-template <int OP>
-__device__ __forceinline__ void closure_add(double &cx, double &cy, const double2 &S, bool pole) {
-  if (OP == OP_GRAD) {
-    if (!pole) cx = cx + S.x;
-    cy = cy + S.y;
-  } else if (!pole) {
-    cx = cx + S.x;
-    cy = cy + S.y;
-  }
-}
 
 // One element at level k (any nlev); used by the generic column loop and
 // by the flat form.
@@ -289,7 +239,6 @@ __device__ __forceinline__ void element(const DevMesh &m, const T *__restrict__ 
   const double ci = P::kVecIn ? m.coslat[node] : 0.0;
   typename P::St st;
   P::init(st, vin[(size_t)node * L + k], ci);
-  double cx = 0.0, cy = 0.0;
   for (int r = r0; r < r1; ++r) {
     const uint32_t nb = (uint32_t)m.nbr[r];
     const bool pole = (nb & kPoleBit) != 0;
@@ -297,11 +246,10 @@ __device__ __forceinline__ void element(const DevMesh &m, const T *__restrict__ 
     const double2 S = m.S[r];
     const size_t n = nb & ~kPoleBit;
     const double cn = P::kVecIn ? m.coslat[n] : 0.0;
-    closure_add<OP>(cx, cy, S, pole);
     P::add(st, vin[n * L + k], S, pole, cn);
   }
   const double al = m.alpha[p], be = P::kVecOut ? m.beta[p] : 0.0;
-  P::store(out, (size_t)node * L + k, st, al, be, cx, cy, ci);
+  P::store(out, (size_t)node * L + k, st, al, be);
 }
 
 // Chunked column form: work units are (level chunk, tile), chunk-major, so
@@ -345,7 +293,7 @@ __global__ void __launch_bounds__(1024) k_column_chunked(DevMesh m, const T *__r
 template <class P, int NCH, int G>
 __device__ __forceinline__ void column_group(const DevMesh &m, const typename P::V *__restrict__ vin,
                                              size_t L, const int (&kk)[NCH], int rb, int n,
-                                             typename P::St (&st)[NCH], double &cx, double &cy) {
+                                             typename P::St (&st)[NCH]) {
   using V = typename P::V;
   uint32_t nb[G];
   double2 S[G];
@@ -368,7 +316,6 @@ __device__ __forceinline__ void column_group(const DevMesh &m, const typename P:
     if (j < n) {
       const bool pole = (nb[j] & kPoleBit) != 0;
       if (!(P::kVecIn && pole)) {
-        closure_add<P::kOp>(cx, cy, S[j], pole);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) P::add(st[c], xn[j][c], S[j], pole, cn[j]);
       }
@@ -395,16 +342,15 @@ __device__ __forceinline__ void column_node(const DevMesh &m, const T *__restric
   typename P::St st[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) P::init(st[c], vin[(size_t)node * L + kk[c]], ci);
-  double cx = 0.0, cy = 0.0;
   if (ONE_GROUP) {
-    column_group<P, NCH, G>(m, vin, L, kk, r0, r1 - r0, st, cx, cy);
+    column_group<P, NCH, G>(m, vin, L, kk, r0, r1 - r0, st);
   } else {
-    for (int rb = r0; rb < r1; rb += G) column_group<P, NCH, G>(m, vin, L, kk, rb, min(G, r1 - rb), st, cx, cy);
+    for (int rb = r0; rb < r1; rb += G) column_group<P, NCH, G>(m, vin, L, kk, rb, min(G, r1 - rb), st);
   }
   const double al = pr.alpha, be = P::kVecOut ? pr.beta : 0.0;
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
-    if (lane + 64 * c < nlev) P::store(out, (size_t)node * L + lane + 64 * c, st[c], al, be, cx, cy, ci);
+    if (lane + 64 * c < nlev) P::store(out, (size_t)node * L + lane + 64 * c, st[c], al, be);
 }
 
 template <class T, int OP, int NCH, int G>
@@ -678,12 +624,10 @@ __device__ __forceinline__ void colv_node(const DevMesh &m, const T *__restrict_
   // uses and stay one burst, instead of being moved into a branch per
   // incidence and waited for one at a time.  Padding entries (j >= n) and
   // pole edges of div/curl leave the state as it was.
-  double cx = 0.0, cy = 0.0;
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     const bool pole = (nb[j] & kPoleBit) != 0;
     if (j < kMinRow) {  // present in every row, never the pole edge
-      closure_add<P::kOp>(cx, cy, S[j], false);
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -691,10 +635,6 @@ __device__ __forceinline__ void colv_node(const DevMesh &m, const T *__restrict_
       continue;
     }
     const bool use = j < n && !(P::kVecIn && pole);
-    double tx = cx, ty = cy;
-    closure_add<P::kOp>(tx, ty, S[j], pole);
-    cx = use ? tx : cx;
-    cy = use ? ty : cy;
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -715,7 +655,7 @@ __device__ __forceinline__ void colv_node(const DevMesh &m, const T *__restrict_
     int w[W];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      const Out r = P::result(st[c][v], al, be, cx, cy, ci);
+      const Out r = P::result(st[c][v], al, be);
       __builtin_memcpy(&w[v * (int)sizeof(Out) / 4], &r, sizeof(Out));
     }
     const int ob = off[c] == kBufOff ? kBufOff : s[c] * (int)sizeof(Out);
@@ -728,17 +668,17 @@ __device__ __forceinline__ void colv_node(const DevMesh &m, const T *__restrict_
 // in flight (at the default target it delays part of the burst to save
 // registers, and each delayed load is then waited for on its own).  The
 // most waves per SIMD at which the burst fits without spilling: five for
-// FP32 in one chunk (the FP32 divergence at 137 levels: 85 registers and
-// 4.55 ms, against 97 and 4.75 ms at four); four up to two chunks, and for
-// FP64 lanes of at most 16 bytes (the FP64 divergence: 97 registers and
+// FP32 in one chunk; four up to two chunks (FP32 lanes above 8 bytes: two),
+// and for FP64 lanes of at most 16 bytes (the FP64 divergence: 97 registers and
 // 7.31 ms, against 169 and 7.73 ms at two); otherwise two.
 template <class T, int LB, int NCH> constexpr int colv_waves() {
-  return sizeof(T) == 4 && NCH == 1 ? 5 : NCH <= 2 || (sizeof(T) == 8 && LB <= 16) ? 4 : 2;
+  return sizeof(T) == 4 ? (NCH == 1 ? 5 : NCH == 2 && LB <= 8 ? 4 : 2)
+         : NCH <= 2 || LB <= 16 ? 4 : 2;
 }
 // The same for the one-pass divergence + curl (two states per level).
 template <class T, int NV, int NCH> constexpr int colv_dc_waves() {
-  return sizeof(T) == 4 && NCH == 1 && NV <= 3 ? 5
-         : NCH <= 2 || (sizeof(T) == 8 && NV == 1 && NCH == 3) ? 4 : 2;
+  return sizeof(T) == 4 ? (NCH == 1 ? (NV <= 3 ? 5 : 4) : NCH == 2 && NV <= 1 ? 4 : 2)
+         : NCH <= 2 || (NV == 1 && NCH == 3) ? 4 : 2;
 }
 
 template <class T, int OP, int NV, int NCH>
@@ -833,12 +773,10 @@ __device__ __forceinline__ void colv_node_dc(const DevMesh &m, const T *__restri
 #pragma unroll
     for (int c = 0; c < NCH; ++c) xn[j][c] = buf_load<R>(rs, off[c]);
   }
-  double cx = 0.0, cy = 0.0;  // the same closure sums serve both operators
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     const bool pole = (nb[j] & kPoleBit) != 0;
     if (j < kMinRow) {
-      closure_add<OP_DIV>(cx, cy, S[j], false);
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -849,10 +787,6 @@ __device__ __forceinline__ void colv_node_dc(const DevMesh &m, const T *__restri
       continue;
     }
     const bool use = j < n && !pole;
-    double tx = cx, ty = cy;
-    closure_add<OP_DIV>(tx, ty, S[j], pole);
-    cx = use ? tx : cx;
-    cy = use ? ty : cy;
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -874,8 +808,8 @@ __device__ __forceinline__ void colv_node_dc(const DevMesh &m, const T *__restri
     int wd[W], wc[W];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      const T a = PD::result(sd[c][v], al, 0.0, cx, cy, ci);
-      const T b = PC::result(sc[c][v], al, 0.0, cx, cy, ci);
+      const T a = PD::result(sd[c][v], al, 0.0);
+      const T b = PC::result(sc[c][v], al, 0.0);
       __builtin_memcpy(&wd[v * (int)sizeof(T) / 4], &a, sizeof(T));
       __builtin_memcpy(&wc[v * (int)sizeof(T) / 4], &b, sizeof(T));
     }
@@ -1017,7 +951,6 @@ __global__ void __launch_bounds__(1024) k_sweep(DevMesh m, const T *__restrict__
         const double ci = P::kVecIn ? m.coslat[node] : 0.0;
         typename P::St st;
         P::init(st, bq[ts * kc + lane], ci);
-        double cx = 0.0, cy = 0.0;
         for (int rb = r0; rb < r1; rb += G) {
           // all loads of the group first (indices clamped into the row),
           // then the accumulation in row order
@@ -1041,12 +974,11 @@ __global__ void __launch_bounds__(1024) k_sweep(DevMesh m, const T *__restrict__
             if (rb + j >= r1) break;
             const bool pole = (lr[j] & kLrefPole) != 0;
             if (P::kVecIn && pole) continue;
-            closure_add<OP>(cx, cy, S[j], pole);
             P::add(st, xn[j], S[j], pole, cn[j]);
           }
         }
         const double al = rec.alpha, be = P::kVecOut ? rec.beta : 0.0;
-        P::store(out, (size_t)node * L + k0 + lane, st, al, be, cx, cy, ci);
+        P::store(out, (size_t)node * L + k0 + lane, st, al, be);
       }
     }
     if (pf) deposit(q + 2);
@@ -1276,21 +1208,15 @@ __global__ void __launch_bounds__(1024) k_sweepv(DevMesh m, const T *__restrict_
         const int l = lr[j] & ~kLrefPole;
         xn[j] = buf[((q + ((l >> 16) & 3) - 1) & 3) * slot_stride + (l & 0xffff) * vpc + kc];
       }
-      double cx = 0.0, cy = 0.0;
 #pragma unroll
       for (int j = 0; j < G; ++j) {
         const bool pole = (lr[j] & kLrefPole) != 0;
         if (j < kMinRow) {  // present in every row, never the pole edge
-          closure_add<P::kOp>(cx, cy, S[j], false);
 #pragma unroll
           for (int v = 0; v < NV; ++v) P::add(st[v], LV::get(xn[j], v), S[j], false, cn[j]);
           continue;
         }
         const bool use = j < n && !(P::kVecIn && pole);
-        double tx = cx, ty = cy;
-        closure_add<P::kOp>(tx, ty, S[j], pole);
-        cx = use ? tx : cx;
-        cy = use ? ty : cy;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
           typename P::St tt = st[v];
@@ -1304,7 +1230,7 @@ __global__ void __launch_bounds__(1024) k_sweepv(DevMesh m, const T *__restrict_
       int w[W];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const Out r = P::result(st[v], al, be, cx, cy, ci);
+        const Out r = P::result(st[v], al, be);
         __builtin_memcpy(&w[v * (int)sizeof(Out) / 4], &r, sizeof(Out));
       }
       const int ob = lane_on ? s_l * (int)sizeof(Out) : kBufOff;
@@ -1637,15 +1563,10 @@ __global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict_
         const int sl = dq == 0 ? sm : (dq == 1 ? sq : sp);
         xn[j] = ldrow(sl * fcap + (l & 0xffff) * nvc);
       }
-      double cx = 0.0, cy = 0.0;  // closure sums (FP32 forms): full normals
-      double ccx = 0.0, ccy = 0.0;  // the curl's (DC)
 #pragma unroll
       for (int j = 0; j < G; ++j) {
         const bool pole = (lr[j] & kLrefPole) != 0;
-        const double2 S2 = make_double2(Sh[j].x + Sh[j].x, Sh[j].y + Sh[j].y);
         if (j < kMinRow) {  // present in every row, never the pole edge
-          if constexpr (sizeof(T) == 4) closure_add<P::kOp>(cx, cy, S2, false);
-          if constexpr (sizeof(T) == 4 && DC) closure_add<OP_CURL>(ccx, ccy, S2, false);
 #pragma unroll
           for (int v = 0; v < NV; ++v) sweep_term<T, OP>(st[v], LV::get(xn[j], v), Sh[j], false, cn[j]);
           if constexpr (DC) {
@@ -1656,18 +1577,6 @@ __global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict_
           continue;
         }
         const bool use = j < n && !(P::kVecIn && pole);
-        if constexpr (sizeof(T) == 4) {
-          double tx = cx, ty = cy;
-          closure_add<P::kOp>(tx, ty, S2, pole);
-          cx = use ? tx : cx;
-          cy = use ? ty : cy;
-          if constexpr (DC) {
-            double ux = ccx, uy = ccy;
-            closure_add<OP_CURL>(ux, uy, S2, pole);
-            ccx = use ? ux : ccx;
-            ccy = use ? uy : ccy;
-          }
-        }
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
           typename P::St tt = st[v];
@@ -1687,7 +1596,7 @@ __global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict_
       int wd[W];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const Out r = P::result(st[v], al, be, cx, cy, ci);
+        const Out r = P::result(st[v], al, be);
         __builtin_memcpy(&wd[v * (int)sizeof(Out) / 4], &r, sizeof(Out));
       }
       auto store_row = [&](T *dst, const int (&w)[W]) {
@@ -1725,7 +1634,7 @@ __global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict_
         int wc[W];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          const typename PC::Out r = PC::result(stc[v], al, be, ccx, ccy, ci);
+          const typename PC::Out r = PC::result(stc[v], al, be);
           __builtin_memcpy(&wc[v * (int)sizeof(Out) / 4], &r, sizeof(Out));
         }
         store_row(out2, wc);
@@ -2025,20 +1934,6 @@ __global__ void __launch_bounds__(1024) k_lsweep(DevMesh m, const T *__restrict_
           const int c2[2] = {w9.z, w9.w};
           __builtin_memcpy(&cosg, c2, 8);
         }
-        // closure of the node's normals (level independent)
-        double cx = 0.0, cy = 0.0;
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          const bool pole = (lr[j] & kLrefPole) != 0;
-          if (j < kMinRow) {
-            closure_add<OP_GRAD>(cx, cy, S[j], false);
-            continue;
-          }
-          double tx = cx, ty = cy;
-          closure_add<OP_GRAD>(tx, ty, S[j], pole);
-          cx = j < n ? tx : cx;
-          cy = j < n ? ty : cy;
-        }
 #pragma unroll 1
         for (int i = 0; i < NL; ++i) {
           const int k = hl + lpn * i;
@@ -2075,7 +1970,7 @@ __global__ void __launch_bounds__(1024) k_lsweep(DevMesh m, const T *__restrict_
           RG g;
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
-            const typename PG::Out o = PG::result(st[v], al, be, cx, cy, 0.0);
+            const typename PG::Out o = PG::result(st[v], al, be);
             g.e[2 * v] = o.x;
             if constexpr (F64) g.e[2 * v + 1] = o.y * cosg;  // v cos(lat), as the divergence forms it
             else g.e[2 * v + 1] = o.y;
@@ -2131,20 +2026,6 @@ __global__ void __launch_bounds__(1024) k_lsweep(DevMesh m, const T *__restrict_
         }
         const i32x4 w9 = r[9];
         const int node = w9.x, n = w9.y, self = w9.z;  // self: LDS offset
-        double cx = 0.0, cy = 0.0;
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          const bool pole = (lr[j] & kLrefPole) != 0;
-          if (j < kMinRow) {
-            closure_add<OP_DIV>(cx, cy, S[j], false);
-            continue;
-          }
-          double tx = cx, ty = cy;
-          closure_add<OP_DIV>(tx, ty, S[j], pole);
-          const bool use = j < n && !pole;
-          cx = use ? tx : cx;
-          cy = use ? ty : cy;
-        }
 #pragma unroll 1
         for (int i = 0; i < NL; ++i) {
           const int k = hl + lpn * i;
@@ -2185,7 +2066,7 @@ __global__ void __launch_bounds__(1024) k_lsweep(DevMesh m, const T *__restrict_
           struct Words { int v[WD]; } o;
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
-            const T x = PD::result(st[v], al, 0.0, cx, cy, ci);
+            const T x = PD::result(st[v], al, 0.0);
             __builtin_memcpy(&o.v[v * (int)sizeof(T) / 4], &x, sizeof(T));
           }
           if (k < nvc) *reinterpret_cast<Words *>(out + (size_t)node * L + first(kc)) = o;
@@ -2510,12 +2391,10 @@ __global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict
         RF xn[G];
 #pragma unroll
         for (int j = 0; j < G; ++j) xn[j] = fbuf[(lr[j] & ~kLrefPole) + kc];
-        double cx = 0.0, cy = 0.0;
 #pragma unroll
         for (int j = 0; j < G; ++j) {
           const bool pole = (lr[j] & kLrefPole) != 0;
           if (j < kMinRow) {  // present in every row, never the pole edge
-            closure_add<OP_GRAD>(cx, cy, S[j], false);
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
               if constexpr (F64) grad_add_half(st[v], LF::get(xn[j], v), S[j], false);
@@ -2524,10 +2403,6 @@ __global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict
             continue;
           }
           const bool use = j < n;
-          double tx = cx, ty = cy;
-          closure_add<OP_GRAD>(tx, ty, S[j], pole);
-          cx = use ? tx : cx;
-          cy = use ? ty : cy;
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
             typename PG::St tt = st[v];
@@ -2539,7 +2414,7 @@ __global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict
         RG g;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          const typename PG::Out o = PG::result(st[v], al, be, cx, cy, 0.0);
+          const typename PG::Out o = PG::result(st[v], al, be);
           g.e[2 * v] = o.x;
           if constexpr (F64) g.e[2 * v + 1] = o.y * cosg;  // v cos(lat), as the divergence forms it
           else g.e[2 * v + 1] = o.y;
@@ -2602,12 +2477,10 @@ __global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict
         RG gn[G];
 #pragma unroll
         for (int j = 0; j < G; ++j) gn[j] = gload((lr[j] & ~kLrefPole) + kc);
-        double cx = 0.0, cy = 0.0;
 #pragma unroll
         for (int j = 0; j < G; ++j) {
           const bool pole = (lr[j] & kLrefPole) != 0;
           if (j < kMinRow) {
-            closure_add<OP_DIV>(cx, cy, S[j], false);
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
               if constexpr (F64) div_add_half_w(st[v], LG::get(gn[j], v), S[j]);
@@ -2616,10 +2489,6 @@ __global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict
             continue;
           }
           const bool use = j < n && !pole;
-          double tx = cx, ty = cy;
-          closure_add<OP_DIV>(tx, ty, S[j], pole);
-          cx = use ? tx : cx;
-          cy = use ? ty : cy;
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
             typename PD::St tt = st[v];
@@ -2632,7 +2501,7 @@ __global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict
         struct Words { int v[WD]; } o;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          const T x = PD::result(st[v], al, 0.0, cx, cy, ci);
+          const T x = PD::result(st[v], al, 0.0);
           __builtin_memcpy(&o.v[v * (int)sizeof(T) / 4], &x, sizeof(T));
         }
         if (lane_on) *reinterpret_cast<Words *>(out + (size_t)node * L + first(kc)) = o;
@@ -2728,11 +2597,11 @@ __global__ void __launch_bounds__(1024) k_flat(DevMesh m, const T *__restrict__ 
 // ---------------------------------------------------------------------------
 // Flux form, kernel 1 of 2: one value per (edge slot, level) into an
 // EdgeColumns-like buffer [E + npole][nlev] (x2 for the gradient).  Slots
-// E.. are the pole edges (gradient only).
+// E.. are the pole edges (gradient only).  FP64 fields only.
 // ---------------------------------------------------------------------------
-template <class T, int OP>
-__global__ void __launch_bounds__(256) k_edge_flux(DevMesh m, const T *__restrict__ in,
-                                                   T *__restrict__ flux, int nlev) {
+template <int OP>
+__global__ void __launch_bounds__(256) k_edge_flux(DevMesh m, const double *__restrict__ in,
+                                                   double *__restrict__ flux, int nlev) {
   const int nslot = (OP == OP_GRAD) ? m.E + m.npole : m.E;
   const size_t L = (size_t)nlev;
   const size_t total = (size_t)nslot * L;
@@ -2742,49 +2611,31 @@ __global__ void __launch_bounds__(256) k_edge_flux(DevMesh m, const T *__restric
     const int k = (int)(g - (size_t)e * L);
     const int a = m.e2n[2 * e], b = m.e2n[2 * e + 1];
     const double2 S = m.eS[e];
-    if constexpr (sizeof(T) == 8) {
-      if (OP == OP_GRAD) {
-        const double xe = 0.5 * (in[(size_t)a * L + k] + in[(size_t)b * L + k]);
-        double2 f;
-        f.x = S.x * xe;
-        f.y = S.y * xe;
-        reinterpret_cast<double2 *>(flux)[g] = f;
-      } else {
-        const double2 *vin = reinterpret_cast<const double2 *>(in);
-        const double2 ua = vin[(size_t)a * L + k], ub = vin[(size_t)b * L + k];
-        const double ca = m.coslat[a], cb = m.coslat[b];
-        const double aa = (OP == OP_DIV) ? ua.x : ua.y, ab = (OP == OP_DIV) ? ub.x : ub.y;
-        const double ba = ((OP == OP_DIV) ? ua.y : ua.x) * ca;
-        const double bb = ((OP == OP_DIV) ? ub.y : ub.x) * cb;
-        const double ae = 0.5 * (aa + ab), be = 0.5 * (ba + bb);
-        flux[g] = (OP == OP_DIV) ? S.x * ae + S.y * be : S.x * ae - S.y * be;
-      }
+    if (OP == OP_GRAD) {
+      const double xe = 0.5 * (in[(size_t)a * L + k] + in[(size_t)b * L + k]);
+      double2 f;
+      f.x = S.x * xe;
+      f.y = S.y * xe;
+      reinterpret_cast<double2 *>(flux)[g] = f;
     } else {
-      // difference form seen from endpoint a (neighbour b)
-      float tx, ty, t;
-      if (OP == OP_GRAD) {
-        diff_terms_f32<OP_GRAD>(S, in[(size_t)a * L + k], in[(size_t)b * L + k], v2f{},
-                                v2f{}, 0.0, 0.0, tx, ty, t);
-        float2 f;
-        f.x = tx;
-        f.y = ty;
-        reinterpret_cast<float2 *>(flux)[g] = f;
-      } else {
-        const v2f *vin = reinterpret_cast<const v2f *>(in);
-        diff_terms_f32<OP>(S, 0.0f, 0.0f, vin[(size_t)a * L + k], vin[(size_t)b * L + k],
-                           m.coslat[a], m.coslat[b], tx, ty, t);
-        flux[g] = t;
-      }
+      const double2 *vin = reinterpret_cast<const double2 *>(in);
+      const double2 ua = vin[(size_t)a * L + k], ub = vin[(size_t)b * L + k];
+      const double ca = m.coslat[a], cb = m.coslat[b];
+      const double aa = (OP == OP_DIV) ? ua.x : ua.y, ab = (OP == OP_DIV) ? ub.x : ub.y;
+      const double ba = ((OP == OP_DIV) ? ua.y : ua.x) * ca;
+      const double bb = ((OP == OP_DIV) ? ub.y : ub.x) * cb;
+      const double ae = 0.5 * (aa + ab), be = 0.5 * (ba + bb);
+      flux[g] = (OP == OP_DIV) ? S.x * ae + S.y * be : S.x * ae - S.y * be;
     }
   }
 }
 
 // Flux form, kernel 2 of 2: each node gathers its slots in the same order
 // and with the same signs as the fused forms.
-template <class T, int OP>
-__global__ void __launch_bounds__(1024) k_gather_flux(DevMesh m, const T *__restrict__ in,
-                                                      const T *__restrict__ flux,
-                                                      T *__restrict__ out, int nlev,
+template <int OP>
+__global__ void __launch_bounds__(1024) k_gather_flux(DevMesh m,
+                                                      const double *__restrict__ flux,
+                                                      double *__restrict__ out, int nlev,
                                                       int per_xcd) {
   int p0, p1;
   if (!tile_range(m, xcd_tile(blockIdx.x, per_xcd), 0, p0, p1)) return;
@@ -2795,69 +2646,29 @@ __global__ void __launch_bounds__(1024) k_gather_flux(DevMesh m, const T *__rest
     const int k = e - pl * nlev;
     const int p = p0 + pl;
     const int node = m.perm[p], r0 = m.rowp[p], r1 = m.rowp[p + 1];
-    if constexpr (sizeof(T) == 8) {
-      if (OP == OP_GRAD) {
-        double gl = 0.0, gt = 0.0;
-        for (int r = r0; r < r1; ++r) {
-          const uint32_t slot = (uint32_t)m.inc_edge[r];
-          const bool pole = ((uint32_t)m.nbr[r] & kPoleBit) != 0;
-          const double2 f = reinterpret_cast<const double2 *>(flux)[(size_t)(slot & ~kPoleBit) * L + k];
-          const bool neg = (slot & kPoleBit) != 0;
-          if (!pole) gl = gl + (neg ? -f.x : f.x);
-          gt = gt + (neg ? -f.y : f.y);
-        }
-        double2 o;
-        o.x = m.alpha[p] * gl;
-        o.y = m.beta[p] * gt;
-        reinterpret_cast<double2 *>(out)[(size_t)node * L + k] = o;
-      } else {
-        double acc = 0.0;
-        for (int r = r0; r < r1; ++r) {
-          if ((uint32_t)m.nbr[r] & kPoleBit) continue;
-          const uint32_t slot = (uint32_t)m.inc_edge[r];
-          const double f = flux[(size_t)(slot & ~kPoleBit) * L + k];
-          acc = acc + ((slot & kPoleBit) ? -f : f);
-        }
-        out[(size_t)node * L + k] = m.alpha[p] * acc;
+    if (OP == OP_GRAD) {
+      double gl = 0.0, gt = 0.0;
+      for (int r = r0; r < r1; ++r) {
+        const uint32_t slot = (uint32_t)m.inc_edge[r];
+        const bool pole = ((uint32_t)m.nbr[r] & kPoleBit) != 0;
+        const double2 f = reinterpret_cast<const double2 *>(flux)[(size_t)(slot & ~kPoleBit) * L + k];
+        const bool neg = (slot & kPoleBit) != 0;
+        if (!pole) gl = gl + (neg ? -f.x : f.x);
+        gt = gt + (neg ? -f.y : f.y);
       }
+      double2 o;
+      o.x = m.alpha[p] * gl;
+      o.y = m.beta[p] * gt;
+      reinterpret_cast<double2 *>(out)[(size_t)node * L + k] = o;
     } else {
-      if (OP == OP_GRAD) {
-        const float xi = in[(size_t)node * L + k];
-        Kahan kx, ky;
-        double cx = 0.0, cy = 0.0;
-        for (int r = r0; r < r1; ++r) {
-          const uint32_t slot = (uint32_t)m.inc_edge[r] & ~kPoleBit;
-          const bool pole = ((uint32_t)m.nbr[r] & kPoleBit) != 0;
-          float2 f = reinterpret_cast<const float2 *>(flux)[(size_t)slot * L + k];
-          const double2 s = m.S[r];
-          // the pole term changes sign at the pole edge's second node
-          if (pole && m.e2n[2 * slot] != node) f.y = -f.y;
-          if (!pole) { kx.add(f.x); cx = cx + s.x; }
-          ky.add(f.y);
-          cy = cy + s.y;
-        }
-        float2 o;
-        o.x = (float)(m.alpha[p] * (kx.value() + cx * (double)xi));
-        o.y = (float)(m.beta[p] * (ky.value() + cy * (double)xi));
-        reinterpret_cast<float2 *>(out)[(size_t)node * L + k] = o;
-      } else {
-        const float2 ui = reinterpret_cast<const float2 *>(in)[(size_t)node * L + k];
-        const double ci = m.coslat[node];
-        Kahan ka;
-        double cx = 0.0, cy = 0.0;
-        for (int r = r0; r < r1; ++r) {
-          if ((uint32_t)m.nbr[r] & kPoleBit) continue;
-          const uint32_t slot = (uint32_t)m.inc_edge[r] & ~kPoleBit;
-          const double2 s = m.S[r];
-          ka.add(flux[(size_t)slot * L + k]);
-          cx = cx + s.x;
-          cy = cy + s.y;
-        }
-        const double a_i = (OP == OP_DIV) ? (double)ui.x : (double)ui.y;
-        const double b_i = ((OP == OP_DIV) ? (double)ui.y : (double)ui.x) * ci;
-        const double closure = (OP == OP_DIV) ? cx * a_i + cy * b_i : cx * a_i - cy * b_i;
-        out[(size_t)node * L + k] = (float)(m.alpha[p] * (ka.value() + closure));
+      double acc = 0.0;
+      for (int r = r0; r < r1; ++r) {
+        if ((uint32_t)m.nbr[r] & kPoleBit) continue;
+        const uint32_t slot = (uint32_t)m.inc_edge[r];
+        const double f = flux[(size_t)(slot & ~kPoleBit) * L + k];
+        acc = acc + ((slot & kPoleBit) ? -f : f);
       }
+      out[(size_t)node * L + k] = m.alpha[p] * acc;
     }
   }
 }
@@ -3472,15 +3283,23 @@ static atlas_status launch_typed(const MeshStore &ms, const T *in, int nlev, T *
                          sh.nodes_per_block, per_xcd);
       break;
     case ATLAS_VARIANT_FLUX: {
-      T *flux = static_cast<T *>(ws);
-      const size_t nslot = (size_t)m.E + (OP == OP_GRAD ? m.npole : 0);
-      const size_t total = nslot * (size_t)nlev;
-      const unsigned nb = (unsigned)std::min<size_t>((total + 255) / 256, 256 * 1024);
-      hipLaunchKernelGGL((k_edge_flux<T, OP>), dim3(nb), dim3(256), 0, st, m, in, flux, nlev);
-      const int per = (m.ntiles + 7) / 8;
-      hipLaunchKernelGGL((k_gather_flux<T, OP>), dim3(per * 8), block, 0, st, m, in,
-                         (const T *)flux, out, nlev, per);
-      break;
+      if constexpr (sizeof(T) == 4) {
+        // the terms of an FP32 field's sums are FP64: the column form
+        // computes them (the workspace stays as it is)
+        LaunchShape col;
+        col.nodes_per_block = 16;
+        return launch_typed<T, OP>(ms, in, nlev, out, ws, col, st, dm);
+      } else {
+        T *flux = static_cast<T *>(ws);
+        const size_t nslot = (size_t)m.E + (OP == OP_GRAD ? m.npole : 0);
+        const size_t total = nslot * (size_t)nlev;
+        const unsigned nb = (unsigned)std::min<size_t>((total + 255) / 256, 256 * 1024);
+        hipLaunchKernelGGL((k_edge_flux<OP>), dim3(nb), dim3(256), 0, st, m, in, flux, nlev);
+        const int per = (m.ntiles + 7) / 8;
+        hipLaunchKernelGGL((k_gather_flux<OP>), dim3(per * 8), block, 0, st, m, (const T *)flux,
+                           out, nlev, per);
+        break;
+      }
     }
     case ATLAS_VARIANT_SWEEP: {
       if (!m.sweep_ok) return fail(ATLAS_EINVAL, "the sweep form needs a mesh of parallels");
