@@ -55,6 +55,7 @@ constexpr uint32_t kPoleBit = 0x80000000u;
 constexpr int kIncPad = 8;               // incidence arrays carry one extra group
 constexpr int32_t kLrefPole = 1 << 30;  // sweep reference of a pole edge
 constexpr int kGRefs = 8;               // references per gradient node (two-ring plan)
+constexpr int kSweepMinTiles = 1024;  // tiles with which a mesh counts as a large one
 constexpr int kDefaultBand = 32;   // parallels per band of the processing order
 constexpr int kDefaultWidth = 32;  // nodes per sector of a band's widest parallel
 
@@ -62,6 +63,25 @@ constexpr int kDefaultWidth = 32;  // nodes per sector of a band's widest parall
 struct __align__(32) PosRec {
   int32_t node, r0, r1, selfslot;
   double alpha, beta;
+};
+
+// The tiles of the wave-specialised sweep: the mesh's tiles, each cut into
+// `parts` longitude parts and its band into `bands`, with the runs each piece
+// touches and every position's references into the ring of runs.
+constexpr int kSweepwSlots = 5;  // runs in the ring
+constexpr int kSgeoFull = 1 << 19;  // in a references word: six incidences, none a pole edge
+constexpr int kSgeoPole = 1 << 20;  // << j: incidence j is a pole edge
+struct SweepView {
+  int32_t ntiles = 0;                // pieces
+  int32_t parts = 1, bands = 1;
+  int32_t rings = 0;                 // most own parallels of a piece
+  int32_t segmax = 0;                // longest run (nodes)
+  int32_t pmax = 0;                  // most own positions of a tile on one parallel
+  const int32_t *tile_seg = nullptr; // [ntiles+1] run range of a tile
+  const int4 *seg = nullptr;         // {ring offset, ring size, first index, length}
+  const int2 *seg_pos = nullptr;     // own positions of the run [lo, hi)
+  const int4 *refs = nullptr;        // [V] {own row | n << 16 | flags, rows 0, 1, rows 2, 3,
+                                     //      rows 4, 5} (rows of the ring: slot * segmax + t)
 };
 
 struct DevMesh {
@@ -110,7 +130,8 @@ struct DevMesh {
   int32_t l2_pmax = 0;               // most own positions of a tile on one parallel
   const int4 *l2_ggeo = nullptr;     // packed gradient-node records (device-built)
   const int4 *l2_lgeo = nullptr;     // packed own-position records (device-built)
-  const int4 *sgeo = nullptr;        // packed per-position sweep geometry (device-built)
+  const int4 *sgeo = nullptr;        // packed sweep records, scalar inputs (device-built)
+  const int4 *sgeo_v = nullptr;      // the same, vector inputs
 };
 
 // ------------------------------------------------------------- kernels
@@ -186,6 +207,7 @@ bool zipper_conforming(const atlas_mesh_desc *d, const std::vector<int64_t> &off
 
 struct MeshStore {
   DevMesh d;
+  std::vector<SweepView> cuts;  // of the sweep's tiles, by parts, then bands (empty: no sweep)
   int device = 0;
   RemapSource rs;
   const double *node_lon = nullptr;  // device [V], by node id

@@ -9,8 +9,11 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <numeric>
 #include <string>
+#include <thread>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -190,6 +193,36 @@ static void processing_order(const atlas_mesh_desc *d, int band, int width,
   }
 }
 
+// Work over `n` items on the host's threads: how many to use (a few
+// thousand items each at least), and fn(w) for w = 0 .. count - 1 on them.
+static int host_threads(int64_t n) {
+  const int64_t hw = std::max(1u, std::thread::hardware_concurrency());
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(hw, 16), n / 64));
+}
+template <class F>
+static void on_threads(int count, const F &fn) {
+  std::vector<std::exception_ptr> err(count);
+  auto run = [&](int w) {
+    try {
+      fn(w);
+    } catch (...) {  // rethrown below, on the calling thread
+      err[w] = std::current_exception();
+    }
+  };
+  std::vector<std::thread> th;
+  th.reserve(count);
+  int started = 1;
+  try {
+    for (; started < count; ++started) th.emplace_back(run, started);
+  } catch (...) {  // no more threads to be had: the rest runs here
+  }
+  run(0);
+  for (int w = started; w < count; ++w) run(w);
+  for (auto &t : th) t.join();
+  for (auto &e : err)
+    if (e) std::rethrow_exception(e);
+}
+
 // Parallel-sweep plan.  For every tile: the parallels it owns plus one
 // above and one below, each reduced to the shortest cyclic run of nodes that
 // holds the tile's own nodes and all their neighbours; the slot of every
@@ -287,6 +320,155 @@ static bool sweep_plan(const std::vector<int64_t> &off, const std::vector<int32_
   return true;
 }
 
+// The shortest cyclic run of a parallel of nx nodes that holds the indices
+// `a` (sorted here).
+static bool cyclic_run(std::vector<int32_t> &a, int32_t nx, int32_t &lo, int32_t &len) {
+  std::sort(a.begin(), a.end());
+  a.erase(std::unique(a.begin(), a.end()), a.end());
+  if (a.empty()) {
+    lo = 0;
+    len = 0;
+  } else if ((int32_t)a.size() == nx) {
+    lo = 0;
+    len = nx;
+  } else {
+    int32_t best = -1, at = 0;  // the run is the complement of the widest gap
+    for (size_t k = 0; k < a.size(); ++k) {
+      const int32_t g = (k + 1 < a.size()) ? a[k + 1] - a[k] : a[0] + nx - a[k];
+      if (g > best) {
+        best = g;
+        at = (int32_t)k;
+      }
+    }
+    lo = a[(at + 1) % a.size()];
+    len = nx - best + 1;
+  }
+  return len < 65536;
+}
+
+// The sweep's tiles cut into `parts` longitude parts (part k owns the k-th
+// share of the tile's positions on every parallel) and their bands into
+// `bands`.  Like sweep_plan per piece, with the references as rows of the
+// ring the wave-specialised sweep keeps its runs in.  False where a reference
+// would not fit its 16 bits or a row has more than six incidences.
+struct CutPlan {
+  std::vector<int32_t> tile_seg;
+  std::vector<int4> seg, refs;
+  std::vector<int2> seg_pos;
+  int32_t segmax = 0, pmax = 0, rings = 0;
+};
+
+static bool cut_plan(const std::vector<int64_t> &off, const std::vector<int32_t> &ring_of,
+                     const std::vector<int32_t> &perm, const std::vector<int32_t> &tile_ptr,
+                     const std::vector<int32_t> &rowp, const std::vector<int32_t> &nbr, int parts,
+                     int bands, CutPlan &cp) {
+  const int64_t T = (int64_t)tile_ptr.size() - 1;
+  const int32_t nr = (int32_t)off.size() - 1;
+  auto nb = [&](int32_t r) { return (int32_t)((uint32_t)nbr[r] & ~kPoleBit); };
+  // every thread takes a range of tiles and lists their runs
+  struct Part {
+    std::vector<int32_t> nseg;  // runs of each tile part
+    std::vector<int4> seg;
+    std::vector<int2> seg_pos;
+    int32_t segmax = 0, pmax = 0, rings = 0;
+    bool ok = true;
+  };
+  const int pieces = parts * bands;
+  const int nthr = host_threads(T);
+  std::vector<Part> done(nthr);
+  auto runs = [&](int w) {
+    Part &o = done[w];
+    std::vector<int2> own, pos;
+    std::vector<std::vector<int32_t>> need;
+    for (int64_t t = T * w / nthr; t < T * (w + 1) / nthr && o.ok; ++t) {
+      // the tile's positions on each of its parallels
+      const int32_t j0 = ring_of[perm[tile_ptr[t]]];
+      own.clear();
+      for (int32_t p = tile_ptr[t]; p < tile_ptr[t + 1]; ++p) {
+        const int32_t q = ring_of[perm[p]] - j0;
+        while ((int32_t)own.size() <= q) own.push_back(make_int2(p, p));
+        own[q].y = p + 1;
+      }
+      for (int u = 0; u < pieces; ++u) {
+        const int k = u % parts, b = u / parts;
+        const int64_t nq = (int64_t)own.size();
+        const int32_t qa = (int32_t)(nq * b / bands), qb = (int32_t)(nq * (b + 1) / bands);
+        o.rings = std::max(o.rings, qb - qa);
+        const int32_t rlo = std::max(0, j0 + qa - 1), rhi = std::min(nr - 1, j0 + qb);
+        need.assign(rhi - rlo + 1, {});
+        pos.assign(rhi - rlo + 1, make_int2(0, 0));
+        for (int32_t q = qa; q < qb; ++q) {
+          const int32_t n = own[q].y - own[q].x;
+          const int2 pr = make_int2(own[q].x + (int32_t)((int64_t)n * k / parts),
+                                    own[q].x + (int32_t)((int64_t)n * (k + 1) / parts));
+          pos[j0 + q - rlo] = pr;
+          o.pmax = std::max(o.pmax, pr.y - pr.x);
+          for (int32_t p = pr.x; p < pr.y; ++p) {
+            need[j0 + q - rlo].push_back((int32_t)(perm[p] - off[j0 + q]));
+            if (rowp[p + 1] - rowp[p] > 6) o.ok = false;
+            for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r)
+              need[ring_of[nb(r)] - rlo].push_back((int32_t)(nb(r) - off[ring_of[nb(r)]]));
+          }
+        }
+        o.nseg.push_back(rhi - rlo + 1);
+        for (int32_t q = 0; q <= rhi - rlo; ++q) {
+          const int32_t nx = (int32_t)(off[rlo + q + 1] - off[rlo + q]);
+          int32_t lo = 0, len = 0;
+          if (!cyclic_run(need[q], nx, lo, len)) o.ok = false;
+          o.segmax = std::max(o.segmax, len);
+          o.seg.push_back(make_int4((int32_t)off[rlo + q], nx, lo, len));
+          o.seg_pos.push_back(pos[q]);
+        }
+      }
+    }
+  };
+  on_threads(nthr, runs);
+  cp.tile_seg.assign(1, 0);
+  std::vector<size_t> base(nthr, 0);
+  for (int w = 0; w < nthr; ++w) {
+    const Part &o = done[w];
+    if (!o.ok) return false;
+    base[w] = cp.seg.size();
+    for (int32_t n : o.nseg) cp.tile_seg.push_back(cp.tile_seg.back() + n);
+    cp.seg.insert(cp.seg.end(), o.seg.begin(), o.seg.end());
+    cp.seg_pos.insert(cp.seg_pos.end(), o.seg_pos.begin(), o.seg_pos.end());
+    cp.segmax = std::max(cp.segmax, o.segmax);
+    cp.pmax = std::max(cp.pmax, o.pmax);
+    cp.rings = std::max(cp.rings, o.rings);
+  }
+  if ((int64_t)kSweepwSlots * cp.segmax >= 65536) return false;
+  cp.refs.resize(perm.size());
+  on_threads(nthr, [&](int w) {
+    for (int64_t u = T * w / nthr * pieces; u < T * (w + 1) / nthr * pieces; ++u) {
+      const int32_t s0 = cp.tile_seg[u], s1 = cp.tile_seg[u + 1];
+      for (int32_t s = s0; s < s1; ++s) {
+        // ring row of node i, on the parallel of run s + dq
+        auto row = [&](int32_t i, int32_t dq) {
+          const int4 g = cp.seg[s + dq];
+          int32_t t = i - g.x - g.z;
+          if (t < 0) t += g.y;
+          return (s + dq - s0) % kSweepwSlots * cp.segmax + t;
+        };
+        for (int32_t p = cp.seg_pos[s].x; p < cp.seg_pos[s].y; ++p) {
+          const int32_t n = rowp[p + 1] - rowp[p], j = ring_of[perm[p]];
+          const int32_t self = row(perm[p], 0);
+          int32_t r[6], flags = n << 16;
+          for (int32_t k = 0; k < 6; ++k) {
+            r[k] = self;
+            if (k >= n) continue;
+            r[k] = row(nb(rowp[p] + k), ring_of[nb(rowp[p] + k)] - j);
+            if ((uint32_t)nbr[rowp[p] + k] & kPoleBit) flags |= kSgeoPole << k;
+          }
+          if (n == 6 && !(flags & (63 * kSgeoPole))) flags |= kSgeoFull;
+          cp.refs[p] = make_int4(self | flags, r[0] | r[1] << 16, r[2] | r[3] << 16,
+                                 r[4] | r[5] << 16);
+        }
+      }
+    }
+  });
+  return true;
+}
+
 // Two-ring plan of the fused Laplacian.  For every tile: its own
 // parallels [ja, jb]; the gradient is needed at the tile's nodes and their
 // neighbours (parallels ja-1 .. jb+1), and those gradients need the field at
@@ -311,30 +493,6 @@ struct LaplPlan {
   std::vector<int32_t> lself;     // per position: slot in its g-run
   int32_t fmax = 0, gmax = 0, pmax = 0;
 };
-
-static bool cyclic_run(std::vector<int32_t> &a, int32_t nx, int32_t &lo, int32_t &len) {
-  std::sort(a.begin(), a.end());
-  a.erase(std::unique(a.begin(), a.end()), a.end());
-  if (a.empty()) {
-    lo = 0;
-    len = 0;
-  } else if ((int32_t)a.size() == nx) {
-    lo = 0;
-    len = nx;
-  } else {
-    int32_t best = -1, at = 0;  // the run is the complement of the widest gap
-    for (size_t k = 0; k < a.size(); ++k) {
-      const int32_t g = (k + 1 < a.size()) ? a[k + 1] - a[k] : a[0] + nx - a[k];
-      if (g > best) {
-        best = g;
-        at = (int32_t)k;
-      }
-    }
-    lo = a[(at + 1) % a.size()];
-    len = nx - best + 1;
-  }
-  return len < 65536;
-}
 
 static bool lapl_plan(const std::vector<int64_t> &off, const std::vector<int32_t> &perm,
                       const std::vector<int32_t> &tile_ptr, const std::vector<int32_t> &rowp,
@@ -535,6 +693,22 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   LaplPlan lp;
   const bool l2_ok = sweep_ok && lapl_plan(rings_of(d), perm, tile_ptr, rowp, nbr, lp);
   if (!l2_ok) lp = LaplPlan();
+  // the sweep's cuts: longitude parts for columns too long for whole tiles;
+  // bands as well where the mesh has too few tiles to fill the chip
+  std::vector<std::pair<int, int>> shapes = {{1, 1}, {2, 1}, {3, 1}};
+  if ((int64_t)tile_ptr.size() - 1 < kSweepMinTiles)
+    shapes = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {1, 6}, {2, 1}, {2, 2}, {3, 1}, {3, 2}};
+  std::vector<CutPlan> cuts(sweep_ok ? shapes.size() : 0);
+  if (sweep_ok) {
+    const std::vector<int64_t> off = rings_of(d);
+    std::vector<int32_t> ring_of(V);
+    for (size_t j = 0; j + 1 < off.size(); ++j)
+      for (int64_t i = off[j]; i < off[j + 1]; ++i) ring_of[i] = (int32_t)j;
+    for (size_t k = 0; k < cuts.size(); ++k)
+      if (!cut_plan(off, ring_of, perm, tile_ptr, rowp, nbr, shapes[k].first, shapes[k].second,
+                    cuts[k]))
+        cuts.clear();
+  }
   // cos(lat) of every incidence's neighbour, so a node's row is read with
   // contiguous loads
   std::vector<double> ncos(nbr.size());
@@ -605,6 +779,23 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
     delete m;
     return st;
   }
+  m->cuts.resize(cuts.size());
+  for (size_t k = 0; k < cuts.size(); ++k) {
+    SweepView &v = m->cuts[k];
+    if ((st = upload_array(*m, cuts[k].tile_seg, &v.tile_seg)) != ATLAS_OK ||
+        (st = upload_array(*m, cuts[k].seg, &v.seg)) != ATLAS_OK ||
+        (st = upload_array(*m, cuts[k].seg_pos, &v.seg_pos)) != ATLAS_OK ||
+        (st = upload_array(*m, cuts[k].refs, &v.refs)) != ATLAS_OK) {
+      delete m;
+      return st;
+    }
+    v.segmax = cuts[k].segmax;
+    v.pmax = cuts[k].pmax;
+    v.rings = cuts[k].rings;
+    v.parts = shapes[k].first;
+    v.bands = shapes[k].second;
+    v.ntiles = (int32_t)cuts[k].tile_seg.size() - 1;
+  }
   std::vector<PosRec> pos(V);
   for (int64_t p = 0; p < V; ++p) {
     pos[p].node = perm[p];
@@ -626,7 +817,7 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
     delete m;
     return st;
   }
-  if (sweep_ok && (st = pack_sweep_geometry(*m)) != ATLAS_OK) {
+  if (!cuts.empty() && (st = pack_sweep_geometry(*m)) != ATLAS_OK) {
     delete m;
     return st;
   }

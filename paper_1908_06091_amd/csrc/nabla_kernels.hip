@@ -28,6 +28,9 @@
 // a buffer of FP32 fluxes could not carry the FP64 terms.)
 #include <hip/hip_runtime.h>
 
+#include <climits>
+#include <type_traits>
+
 #include "internal.h"
 
 namespace atlasx {
@@ -118,6 +121,16 @@ template <> struct Pol<double, OP_GRAD> {
   static __device__ __forceinline__ Out result(const St &s, double al, double be) {
     return Out{al * s.gl, be * s.gt};
   }
+  // the same from halved normals Sh = S/2 (exact; same bits, one
+  // multiplication less)
+  static __device__ __forceinline__ void add_half(St &s, V xn, const double2 &Sh, bool pole, double) {
+    const double xe = s.xi + xn;
+    if (!pole) s.gl = s.gl + Sh.x * xe;
+    s.gt = s.gt + Sh.y * xe;
+  }
+  static __device__ __forceinline__ Out result_half(const St &s, double al, double be) {
+    return result(s, al, be);
+  }
   static __device__ __forceinline__ void store(double *out, size_t idx, const St &s, double al,
                                                double be) {
     const Out r = result(s, al, be);
@@ -127,6 +140,7 @@ template <> struct Pol<double, OP_GRAD> {
     s.gl = use ? t.gl : s.gl;
     s.gt = use ? t.gt : s.gt;
   }
+  static __device__ __forceinline__ void settle(St &s) { asm volatile("" : "+v"(s.gl), "+v"(s.gt)); }
 };
 
 // FP64 divergence / curl: sum of sS_lon a_e +- sS_lat b_e with edge
@@ -152,6 +166,16 @@ template <int OP> struct PolDC64 {
   static __device__ __forceinline__ Out result(const St &s, double al, double) {
     return al * s.acc;
   }
+  static __device__ __forceinline__ void add_half(St &s, V un, const double2 &Sh, bool, double cn) {
+    const double an = (OP == OP_DIV) ? un.x : un.y;
+    const double bn = ((OP == OP_DIV) ? un.y : un.x) * cn;
+    const double ae = s.ai + an, be = s.bi + bn;
+    const double f = (OP == OP_DIV) ? Sh.x * ae + Sh.y * be : Sh.x * ae - Sh.y * be;
+    s.acc = s.acc + f;
+  }
+  static __device__ __forceinline__ Out result_half(const St &s, double al, double be) {
+    return result(s, al, be);
+  }
   static __device__ __forceinline__ void store(double *out, size_t idx, const St &s, double al,
                                                double be) {
     st_out(out + idx, result(s, al, be));
@@ -159,6 +183,7 @@ template <int OP> struct PolDC64 {
   static __device__ __forceinline__ void keep(St &s, const St &t, bool use) {
     s.acc = use ? t.acc : s.acc;
   }
+  static __device__ __forceinline__ void settle(St &s) { asm volatile("" : "+v"(s.acc)); }
 };
 template <> struct Pol<double, OP_DIV> : PolDC64<OP_DIV> {};
 template <> struct Pol<double, OP_CURL> : PolDC64<OP_CURL> {};
@@ -184,6 +209,13 @@ template <> struct Pol<float, OP_GRAD> {
   static __device__ __forceinline__ Out result(const St &s, double al, double be) {
     return Out{(float)(al * (0.5 * s.gl)), (float)(be * (0.5 * s.gt))};
   }
+  static __device__ __forceinline__ void add_half(St &s, V xn, const double2 &Sh, bool pole,
+                                                  double cn) {
+    add(s, xn, Sh, pole, cn);
+  }
+  static __device__ __forceinline__ Out result_half(const St &s, double al, double be) {
+    return Out{(float)(al * s.gl), (float)(be * s.gt)};
+  }
   static __device__ __forceinline__ void store(float *out, size_t idx, const St &s, double al,
                                                double be) {
     const Out r = result(s, al, be);
@@ -193,6 +225,7 @@ template <> struct Pol<float, OP_GRAD> {
     s.gl = use ? t.gl : s.gl;
     s.gt = use ? t.gt : s.gt;
   }
+  static __device__ __forceinline__ void settle(St &s) { asm volatile("" : "+v"(s.gl), "+v"(s.gt)); }
 };
 
 template <int OP> struct PolDC32 {
@@ -215,6 +248,13 @@ template <int OP> struct PolDC32 {
   static __device__ __forceinline__ Out result(const St &s, double al, double) {
     return (float)(al * (0.5 * s.acc));
   }
+  static __device__ __forceinline__ void add_half(St &s, V un, const double2 &Sh, bool pole,
+                                                  double cn) {
+    add(s, un, Sh, pole, cn);
+  }
+  static __device__ __forceinline__ Out result_half(const St &s, double al, double) {
+    return (float)(al * s.acc);
+  }
   static __device__ __forceinline__ void store(float *out, size_t idx, const St &s, double al,
                                                double be) {
     st_out(out + idx, result(s, al, be));
@@ -222,6 +262,7 @@ template <int OP> struct PolDC32 {
   static __device__ __forceinline__ void keep(St &s, const St &t, bool use) {
     s.acc = use ? t.acc : s.acc;
   }
+  static __device__ __forceinline__ void settle(St &s) { asm volatile("" : "+v"(s.acc)); }
 };
 template <> struct Pol<float, OP_DIV> : PolDC32<OP_DIV> {};
 template <> struct Pol<float, OP_CURL> : PolDC32<OP_CURL> {};
@@ -1005,8 +1046,6 @@ __global__ void __launch_bounds__(1024) k_sweep(DevMesh m, const T *__restrict__
 constexpr int kSweepEpt = 4;   // staged lane vectors per thread and run
 constexpr int kGeoWords = 11;  // 16-byte words of staged rows per position:
                                // S[6] (6), lref[8] (2), ncos[6] (3)
-constexpr int kSweepMinTiles = 1024;  // tiles below which the default stays
-                                      // with the column form
 
 template <class T, int OP, int NV, int EPT>
 __global__ void __launch_bounds__(1024) k_sweepv(DevMesh m, const T *__restrict__ in,
@@ -1256,37 +1295,51 @@ __global__ void __launch_bounds__(1024) k_sweepv(DevMesh m, const T *__restrict_
 // consumers never wait on memory (their stores drain while the next
 // parallels are computed) and the producers wait only for their own loads.
 // The producers form two groups that take alternate runs: at step q the
-// group of run q+3 loads its columns and packed geometry into ring slot
-// (q+3) mod 5, and at the end of step q the other group waits for run q+2,
-// which it issued one step earlier -- so every load has two steps to land.
-// The consumers compute the own positions of run q from slots q-1, q, q+1.
-// The roles run separate loops that meet at one workgroup barrier per step.
-// Lane vectors are 16 bytes (FP64: 2 levels of a scalar, 1 of a vector;
-// FP32: 4 of a scalar, 2 of a vector).  Items of a slot are numbered (node
-// of the run) x (lane vector of the chunk), so each load instruction fills
-// 64 consecutive 16-byte LDS words.  The packed normals are halved (exact):
-// the FP64 edge term sS (x_i + x_n)/2 is formed as (sS/2)(x_i + x_n) with the
-// same bits and one multiplication less.
+// group of run q+3 loads its columns and packed records into its ring
+// slots, and at the end of step q the other group waits for run q+2, which
+// it issued one step earlier -- so every load has two steps to land.  The
+// consumers compute the own positions of run q from runs q-1, q, q+1.  The
+// roles run separate loops that meet at one workgroup barrier per step.
+//
+// A run's columns lie in its ring slot row by row, vpc 16-byte vectors each.
+// A position's neighbours are named by their row in the whole ring (run r of
+// a tile always takes slot r mod 5, so the rows are known when the mesh is
+// built): one multiply-add turns a reference into an LDS address.
+//
+// Lanes.  An element is the least a lane computes: 8 bytes of a scalar
+// column (one FP64 level, two FP32 ones), 16 of a vector column (the one-pass
+// FP32 divergence and curl: 8, for its registers).  A position
+// takes LPN lanes, lane h of them the elements h, h + LPN, ... (NE of them),
+// so one decoding of a record serves NE elements, and every store
+// instruction writes one contiguous run of the row.  Results go through
+// plain stores: rows start at any multiple of the element size, and the L2
+// merges the lines that two rows or two instructions share (streaming
+// stores of such rows write them twice: 4.0 against 5.1 TB/s, whole rows).
 // ---------------------------------------------------------------------------
-constexpr int kSgeoWords = 14;  // packed sweep geometry per position (16-byte
-                                // words): {node, n, selfslot, 0}, (alpha,
-                                // beta), S[6] / 2, lref[8], ncos[6],
-                                // (cos lat, 0)
-// Positions per wavefront: as many as 64 lanes hold chunks of (at most 8)
-// 8 lane vectors: eight, 12: five, 16: four, 21: three, 32: two; wider
-// chunks one.
-constexpr int kSweepwNpn8 = 8;
+// Per position: one 16-byte word of references ({own row | n << 16 | flags,
+// rows 0 and 1, rows 2 and 3, rows 4 and 5}, one set for each cut of the
+// tiles) and a packed record of 16-byte words, {node, 0, alpha}, {beta
+// (scalar inputs) or cos(lat), 0}, S[6] / 2, and for vector inputs the
+// neighbours' cos(lat).
+constexpr int kSgeoWordsS = 8, kSgeoWordsV = 11;
+// Elements per lane: at most what 128 registers hold (one workgroup of up to
+// 1024 threads per compute unit).
+template <class T, int OP, bool DC>
+constexpr int sweepw_max_ne() {
+  return sizeof(T) == 8 ? (DC ? 3 : 5) : OP == OP_GRAD ? 5 : 4;
+}
+// Levels of an element.
+template <class T, bool DC>
+constexpr int sweepw_elem_levels() {
+  return sizeof(T) == 8 || DC ? 1 : 2;
+}
 constexpr int kSweepwGroups = 2;     // producer groups (runs taken in turn)
-constexpr int kSweepwLead = kSweepwGroups + 1;  // run q + lead issued at step q
-constexpr int kSweepwSlots = kSweepwLead + 2;   // field ring: runs q-1 .. q+lead
-constexpr int kSweepwGeoSlots = kSweepwLead + 1;  // geometry ring: runs q ..
-                                                  // q+lead (the consumers read
-                                                  // only run q's records)
-// Waves per producer group: two for every operator (with the item indices
-// advanced incrementally, a second producer wave made the FP64 divergence
-// sweep faster too: 7.84 -> 7.62 ms at O1280, 137 levels; 2.08 -> 1.97 ms
-// at 37 levels).
-template <int OP> constexpr int sweepw_group_waves() { return 2; }
+constexpr int kSweepwGroupWaves = 2; // waves of a group
+constexpr int kSweepwLead = kSweepwSlots - 2;     // run q + lead issued at step q; field
+                                                  // ring: runs q-1 .. q+lead
+constexpr int kSweepwGeoSlots = kSweepwLead + 1;  // record ring: runs q .. q+lead
+// lanes past a short last chunk read up to this far past their row
+constexpr int kSweepwLdsTail = 32 * 16;
 
 __device__ __forceinline__ void lds_dma16(const i32x4 &rsrc, void *lds_wave_base, int voff) {
   __amdgpu_buffer_rsrc_t r;
@@ -1295,65 +1348,40 @@ __device__ __forceinline__ void lds_dma16(const i32x4 &rsrc, void *lds_wave_base
       r, (__attribute__((address_space(3))) void *)lds_wave_base, 16, voff, 0, 0, 0);
 }
 
-// The FP64 edge terms with halved normals (bits of Pol<double, *>::add).
-__device__ __forceinline__ void sweep_add_half(Pol<double, OP_GRAD>::St &s, double xn,
-                                               const double2 &Sh, bool pole, double) {
-  const double xe = s.xi + xn;
-  if (!pole) s.gl = s.gl + Sh.x * xe;
-  s.gt = s.gt + Sh.y * xe;
-}
-template <int OP>
-__device__ __forceinline__ void sweep_add_half(typename PolDC64<OP>::St &s, v2d un,
-                                               const double2 &Sh, bool, double cn) {
-  const double an = (OP == OP_DIV) ? un.x : un.y;
-  const double bn = ((OP == OP_DIV) ? un.y : un.x) * cn;
-  const double ae = s.ai + an, be = s.bi + bn;
-  const double f = (OP == OP_DIV) ? Sh.x * ae + Sh.y * be : Sh.x * ae - Sh.y * be;
-  s.acc = s.acc + f;
-}
-
-template <class T, int OP>
-__device__ __forceinline__ void sweep_term(typename Pol<T, OP>::St &s,
-                                           typename Pol<T, OP>::V xn, const double2 &Sh,
-                                           bool pole, double cn) {
-  if constexpr (sizeof(T) == 8) {
-    if constexpr (OP == OP_GRAD) sweep_add_half(s, xn, Sh, pole, cn);
-    else sweep_add_half<OP>(s, xn, Sh, pole, cn);
-  } else {
-    Pol<T, OP>::add(s, xn, make_double2(Sh.x + Sh.x, Sh.y + Sh.y), pole, cn);
-  }
-}
-
 // DC (OP = OP_DIV only): the curl of the same field as well, into out2,
 // from the same loads; each output bitwise that of its own operator.
-template <class T, int OP, int NV, int NPN, bool DC = false>
-__global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict__ in,
-                                                 T *__restrict__ out, T *__restrict__ out2,
-                                                 int nlev, int vpc, int ntiles, int per_xcd,
-                                                 int fcap, int gcap) {
+template <class T, int OP, int LPN, int NE, bool DC>
+__global__ void __launch_bounds__(1024) k_sweepw(SweepView m, const int4 *__restrict__ geo,
+                                                 const T *__restrict__ in, T *__restrict__ out,
+                                                 T *__restrict__ out2, int nlev, int vpc,
+                                                 int per_xcd) {
   static_assert(!DC || OP == OP_DIV, "the one-pass curl rides on the divergence");
   using P = Pol<T, OP>;
   using PC = Pol<T, OP_CURL>;
   using V = typename P::V;
-  using LV = LaneVec<V, NV>;
-  using R = typename LV::raw;
   using Out = typename P::Out;
-  static_assert(sizeof(R) == 16, "wave-specialised sweep: 16-byte lane vectors");
-  constexpr int GW = P::kVecIn ? kSgeoWords : 10;  // geometry words read per position
-  constexpr int kSweepwGroupWaves = sweepw_group_waves<OP>();
+  constexpr int NV = 16 / (int)sizeof(V);          // levels per vector
+  constexpr int EL = sweepw_elem_levels<T, DC>();
+  constexpr int EB = EL * (int)sizeof(V);          // bytes of an element
+  constexpr int EPV = 16 / EB;                     // elements per vector
+  constexpr int GW = P::kVecIn ? kSgeoWordsV : kSgeoWordsS;
   constexpr int NPW = kSweepwGroups * kSweepwGroupWaves;
+  constexpr int NPN = 64 / LPN;                    // positions per wavefront
+  struct __align__(EB) Elem { V v[EL]; };
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  R *fbuf = reinterpret_cast<R *>(smem_raw);                           // [field slots][fcap]
-  i32x4 *gbuf = reinterpret_cast<i32x4 *>(fbuf + kSweepwSlots * fcap);  // [geometry slots][gcap]
+  const int segmax = m.segmax, gcap = m.pmax * GW;
+  i32x4 *fbuf = reinterpret_cast<i32x4 *>(smem_raw);  // [field slots][segmax][nvc]
+  i32x4 *rbuf = fbuf + kSweepwSlots * segmax * vpc;    // [record slots][pmax] references
+  i32x4 *gbuf = rbuf + kSweepwGeoSlots * m.pmax;       // [record slots][gcap] records
   const int u = xcd_tile(blockIdx.x, per_xcd);
   const int nvec = (nlev + NV - 1) / NV;
   const int nchunk = (nvec + vpc - 1) / vpc;
   const int tile = u / nchunk;
   const int c = u - tile * nchunk;
-  if (tile >= ntiles) return;
+  if (tile >= m.ntiles) return;
   const int v0 = c * vpc;
   if (v0 >= nvec) return;
-  const int nvc = min(vpc, nvec - v0);  // lane vectors in this chunk
+  const int nvc = min(vpc, nvec - v0);  // vectors in this chunk
   const int s0 = cst(m.tile_seg)[tile];
   const int nseg = cst(m.tile_seg)[tile + 1] - s0;
   const size_t L = (size_t)nlev;
@@ -1379,30 +1407,29 @@ __global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict_
     // ---- producers: group grp loads the runs r with r mod groups = grp ----
     const int grp = wave / kSweepwGroupWaves, gwave = wave - grp * kSweepwGroupWaves;
     const V *vin = reinterpret_cast<const V *>(in);
-    // columns and geometry of run q into the ring slots of q, the waves of
+    // columns and records of run q into the ring slots of q, the waves of
     // the calling group (or, with nwv = NPW, all producers) sharing the
-    // load instructions
+    // load instructions; lanes past the run's last item are off (the words
+    // behind it belong to the next slot)
     auto load = [&](int q, int w, int nwv) {
-      const int sl = q % kSweepwSlots;
       {
         const int rb = cst(segi)[4 * (s0 + q)], nx = cst(segi)[4 * (s0 + q) + 1];
         const int lo = cst(segi)[4 * (s0 + q) + 2], len = cst(segi)[4 * (s0 + q) + 3];
         const i32x4 rs = make_rsrc(vin + (size_t)rb * L, (uint32_t)nx * col_bytes);
         const int nitems = len * nvc;
-        R *slot = fbuf + sl * fcap;
-        // item i = (node t of the run) x (lane vector k); t and k advance
-        // by whole strides of the calling waves' load instructions
+        i32x4 *slot = fbuf + (q % kSweepwSlots) * segmax * nvc;
+        // item i = (node t of the run) x (vector k); t and k advance by
+        // whole strides of the calling waves' load instructions
         const int i0 = w * 64 + lane, di = nwv * 64;
         int t = i0 / nvc, k = i0 - t * nvc;
         const int dt = di / nvc, dk = di - dt * nvc;
         for (int b = w; b * 64 < nitems; b += nwv) {
-          int off = kBufOff;
           if (b * 64 + lane < nitems) {
             int ii = lo + t;
             if (ii >= nx) ii -= nx;
-            off = ii * (int)col_bytes + min(NV * (v0 + k), nlev - NV) * (int)sizeof(V);
+            lds_dma16(rs, slot + b * 64,
+                      ii * (int)col_bytes + min(NV * (v0 + k), nlev - NV) * (int)sizeof(V));
           }
-          lds_dma16(rs, slot + b * 64, off);
           t += dt;
           k += dk;
           if (k >= nvc) {
@@ -1413,19 +1440,13 @@ __global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict_
       }
       {
         const int plo = run_lo(q), n = run_hi(q) - plo;
-        const i32x4 rs = make_rsrc(m.sgeo + (size_t)plo * kSgeoWords,
-                                   (uint32_t)n * kSgeoWords * 16u);
-        const int nitems = n * GW;
-        i32x4 *slot = gbuf + (q % kSweepwGeoSlots) * gcap;
-        for (int b = w; b * 64 < nitems; b += nwv) {
-          const int i = b * 64 + lane;
-          int off = kBufOff;
-          if (i < nitems) {
-            const int t = i / GW, wd = i - t * GW;
-            off = (t * kSgeoWords + wd) * 16;
-          }
-          lds_dma16(rs, slot + b * 64, off);
-        }
+        auto copy = [&](const int4 *src, i32x4 *dst, int words) {
+          const i32x4 rs = make_rsrc(src, (uint32_t)words * 16u);
+          for (int b = w; b * 64 < words; b += nwv)
+            if (b * 64 + lane < words) lds_dma16(rs, dst + b * 64, (b * 64 + lane) * 16);
+        };
+        copy(m.refs + plo, rbuf + (q % kSweepwGeoSlots) * m.pmax, n);
+        copy(geo + (size_t)plo * GW, gbuf + (q % kSweepwGeoSlots) * gcap, n * GW);
       }
     };
     // prologue: runs qa-1 .. qa+1 by every producer (waited), runs qa+2 ..
@@ -1457,195 +1478,152 @@ __global__ void __launch_bounds__(1024) k_sweepw(DevMesh m, const T *__restrict_
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   const int cw = wave - NPW, ncw = nw - NPW;
-  // NPN positions per wavefront, 64 / NPN lanes each (chunks of at most
-  // 64 / NPN lane vectors); where NPN does not divide 64 the lanes left over
-  // repeat the last position's first lanes and store nothing
-  constexpr int LPN = 64 / NPN;
-  const int sub_raw = NPN > 1 ? lane / LPN : 0;
-  const int sub = min(sub_raw, NPN - 1);
-  const int hl = lane - sub_raw * LPN;
-  const int kc = min(hl, nvc - 1);  // lanes past the chunk read a valid entry
-  const bool lane_on = sub_raw < NPN && hl < nvc;
-  // Lanes whose results exceed 16 bytes (the gradient: two components at
-  // NV levels) would make every store instruction strided, each lane
-  // writing part of its own piece of the row.  Such a lane takes NG groups
-  // of GS adjacent levels (16 bytes of output each), one from each of the
-  // chunk's NG equal parts: group g holds level slots g GS nvc + GS kc + e,
-  // so the g-th store of the lanes covers one contiguous run of the row.
-  // Every level goes through the same arithmetic: the bits are unchanged.
-  constexpr bool kSplit = NV * sizeof(Out) > 16;
-  constexpr int GS = kSplit ? (int)(16 / sizeof(Out)) : NV;  // levels per group
-  constexpr int NG = NV / GS;
-  static_assert(!kSplit || (ElemOf<V>::C == 1 && NV % GS == 0), "split lanes: scalar inputs");
-  int s_g[NG];  // first output level of each group
+  const int sub = lane / LPN, hl = lane - sub * LPN;
+  const int nel = nvc * EPV;  // elements in this chunk
+  const uint32_t rowb = (uint32_t)nvc * 16u;
+  const unsigned char *lane_base = smem_raw + hl * EB;
+  // byte offset in the output row of the lane's element g: its vector is
+  // clamped inside the column, so the last one may repeat levels
+  int off_g[NE];
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    const int p = kSplit ? g * GS * nvc + GS * kc : NV * kc;  // slot in the chunk
-    s_g[g] = min(NV * (v0 + p / NV), nlev - NV) + p % NV;
+  for (int g = 0; g < NE; ++g) {
+    const int e = hl + g * LPN;
+    off_g[g] = (min(NV * (v0 + e / EPV), nlev - NV) + EL * (e % EPV)) * (int)sizeof(Out);
   }
-  // the lane's NV levels of the chunk row starting at lane vector `base`
-  auto ldrow = [&](int base) {
-    if constexpr (kSplit) {
-      struct Grp { typename ElemOf<V>::E e[GS]; };
-      const Grp *fv = reinterpret_cast<const Grp *>(fbuf + base);
-      R r;
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const Grp x = fv[g * nvc + kc];
-        __builtin_memcpy(&r.e[g * GS], x.e, sizeof(Grp));
-      }
-      return r;
-    } else {
-      return fbuf[base + kc];
+  const size_t row_out = L * sizeof(Out);
+
+  // the sums and results of one position; FULL: six incidences, none a pole
+  // edge (nearly every position), so nothing is selected
+  auto position = [&](const i32x4 *rec, const i32x4 &ref, auto full_c) {
+    constexpr bool FULL = decltype(full_c)::value;
+    // (keeps the compiler from hoisting the two instances' common reads, all
+    // six neighbours', above the branch between them)
+    if constexpr (!FULL) asm volatile("" ::: "memory");
+    const i32x4 w0 = rec[0], w1 = rec[1];
+    double al, sc;  // alpha; beta or cos(lat)
+    {
+      const int a2[2] = {w0.z, w0.w}, b2[2] = {w1.x, w1.y};
+      __builtin_memcpy(&al, a2, 8);
+      __builtin_memcpy(&sc, b2, 8);
     }
-  };
-  int sq = qa % kSweepwSlots;           // slot of run q
-  for (int q = qa; q <= qb; ++q) {
-    const int plo = run_lo(q), phi = run_hi(q);
-    const int sm = sq == 0 ? kSweepwSlots - 1 : sq - 1;  // slot of run q-1
-    const int sp = sq == kSweepwSlots - 1 ? 0 : sq + 1;  // slot of run q+1
-    const i32x4 *gq = gbuf + (q % kSweepwGeoSlots) * gcap;
-    for (int p = plo + NPN * cw + sub; p < phi; p += NPN * ncw) {
-      const i32x4 *g = gq + (p - plo) * GW;
-      const i32x4 w0 = g[0], w1 = g[1];
-      const int node = w0.x, n = w0.y, selfslot = w0.z;
-      double al, be;
+    const int flags = ref.x;
+    const uint32_t rw[6] = {(uint32_t)ref.y & 0xffffu, (uint32_t)ref.y >> 16,
+                            (uint32_t)ref.z & 0xffffu, (uint32_t)ref.z >> 16,
+                            (uint32_t)ref.w & 0xffffu, (uint32_t)ref.w >> 16};
+    typename P::St st[NE][EL];
+    typename PC::St stc[DC ? NE : 1][EL];
+    const unsigned char *self = lane_base + __umul24((uint32_t)flags & 0xffffu, rowb);
+#pragma unroll
+    for (int g = 0; g < NE; ++g) {
+      const Elem x = *reinterpret_cast<const Elem *>(self + g * LPN * EB);
+#pragma unroll
+      for (int e = 0; e < EL; ++e) {
+        P::init(st[g][e], x.v[e], sc);
+        if constexpr (DC) PC::init(stc[g][e], x.v[e], sc);
+      }
+    }
+    // Neighbour j + 1 is read while neighbour j is added.  With many
+    // elements the reads must not move further up (all six neighbours at
+    // once would spill).
+    Elem x[2][NE];
+    auto read = [&](int j) {
+      const unsigned char *col = lane_base + __umul24(rw[j], rowb);
+#pragma unroll
+      for (int g = 0; g < NE; ++g)
+        x[j & 1][g] = *reinterpret_cast<const Elem *>(col + g * LPN * EB);
+    };
+    read(0);
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      if (j < 5) read(j + 1);
+      double2 Sh;
       {
-        const int a2[2] = {w1.x, w1.y}, b2[2] = {w1.z, w1.w};
-        __builtin_memcpy(&al, a2, 8);
-        __builtin_memcpy(&be, b2, 8);
+        const i32x4 v = rec[2 + j];
+        __builtin_memcpy(&Sh, &v, 16);
       }
-      if (!P::kVecOut) be = 0.0;
-      constexpr int G = 6;
-      double2 Sh[G];
-      int lr[8];
-      double cn[G];
-      double ci = 0.0;
+      double cn = 0.0;
+      if constexpr (P::kVecIn) __builtin_memcpy(&cn, reinterpret_cast<const double *>(rec + 8) + j, 8);
+      const bool pole = !FULL && j >= kMinRow && (flags & (kSgeoPole << j)) != 0;
+      const bool use = FULL || j < kMinRow || (j < ((flags >> 16) & 7) && !(P::kVecIn && pole));
 #pragma unroll
-      for (int j = 0; j < G; ++j) {
-        const i32x4 v = g[2 + j];
-        __builtin_memcpy(&Sh[j], &v, 16);
-      }
-      {
-        const i32x4 a = g[8], b = g[9];
-        lr[0] = a.x; lr[1] = a.y; lr[2] = a.z; lr[3] = a.w;
-        lr[4] = b.x; lr[5] = b.y; lr[6] = b.z; lr[7] = b.w;
-      }
-      if constexpr (P::kVecIn) {
+      for (int g = 0; g < NE; ++g) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const i32x4 v = g[10 + k];
-          __builtin_memcpy(&cn[2 * k], &v, 16);
-        }
-        const i32x4 v = g[13];
-        const int cc[2] = {v.x, v.y};
-        __builtin_memcpy(&ci, cc, 8);
-      } else {
-#pragma unroll
-        for (int j = 0; j < G; ++j) cn[j] = 0.0;
-      }
-      typename P::St st[NV];
-      typename PC::St stc[DC ? NV : 1];
-      {
-        const R xi = ldrow(sq * fcap + selfslot * nvc);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) P::init(st[v], LV::get(xi, v), ci);
-        if constexpr (DC) {
-#pragma unroll
-          for (int v = 0; v < NV; ++v) PC::init(stc[v], LV::get(xi, v), ci);
-        }
-      }
-      R xn[G];
-#pragma unroll
-      for (int j = 0; j < G; ++j) {
-        const int l = lr[j] & ~kLrefPole;
-        const int dq = (l >> 16) & 3;  // 0: run q-1, 1: run q, 2: run q+1
-        const int sl = dq == 0 ? sm : (dq == 1 ? sq : sp);
-        xn[j] = ldrow(sl * fcap + (l & 0xffff) * nvc);
-      }
-#pragma unroll
-      for (int j = 0; j < G; ++j) {
-        const bool pole = (lr[j] & kLrefPole) != 0;
-        if (j < kMinRow) {  // present in every row, never the pole edge
-#pragma unroll
-          for (int v = 0; v < NV; ++v) sweep_term<T, OP>(st[v], LV::get(xn[j], v), Sh[j], false, cn[j]);
-          if constexpr (DC) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-              sweep_term<T, OP_CURL>(stc[v], LV::get(xn[j], v), Sh[j], false, cn[j]);
-          }
-          continue;
-        }
-        const bool use = j < n && !(P::kVecIn && pole);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          typename P::St tt = st[v];
-          sweep_term<T, OP>(tt, LV::get(xn[j], v), Sh[j], pole, cn[j]);
-          P::keep(st[v], tt, use);
-        }
-        if constexpr (DC) {
-#pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            typename PC::St tt = stc[v];
-            sweep_term<T, OP_CURL>(tt, LV::get(xn[j], v), Sh[j], pole, cn[j]);
-            PC::keep(stc[v], tt, use);
-          }
-        }
-      }
-      constexpr int W = NV * (int)sizeof(Out) / 4;
-      int wd[W];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const Out r = P::result(st[v], al, be);
-        __builtin_memcpy(&wd[v * (int)sizeof(Out) / 4], &r, sizeof(Out));
-      }
-      auto store_row = [&](T *dst, const int (&w)[W]) {
-        if constexpr (kSplit) {
-          // one contiguous run per group (16 bytes per lane)
-          const size_t ew = sizeof(Out) / sizeof(T);
-          const i32x4 ro = make_rsrc(dst + (size_t)node * L * ew, (uint32_t)(L * sizeof(Out)));
-#pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            const i32x4 v4 = {w[4 * g], w[4 * g + 1], w[4 * g + 2], w[4 * g + 3]};
-            if constexpr (NPN == 1) {
-              buf_store16(v4, ro, lane_on ? s_g[g] * (int)sizeof(Out) : kBufOff, 0, kStoreAux);
-            } else if (lane_on) {
-              *reinterpret_cast<i32x4 *>(dst + ((size_t)node * L + s_g[g]) * ew) = v4;
+        for (int e = 0; e < EL; ++e) {
+          const V xn = x[j & 1][g].v[e];
+          if (FULL || j < kMinRow) {
+            P::add_half(st[g][e], xn, Sh, false, cn);
+            if constexpr (DC) PC::add_half(stc[g][e], xn, Sh, false, cn);
+          } else {
+            typename P::St tt = st[g][e];
+            P::add_half(tt, xn, Sh, pole, cn);
+            P::keep(st[g][e], tt, use);
+            if constexpr (DC) {
+              typename PC::St tc = stc[g][e];
+              PC::add_half(tc, xn, Sh, pole, cn);
+              PC::keep(stc[g][e], tc, use);
             }
           }
-        } else if constexpr (NPN == 1) {
-          // one position per wavefront: a buffer store over its row (the
-          // resource is wavefront-uniform)
-          const i32x4 ro = make_rsrc(dst + (size_t)node * L * (sizeof(Out) / sizeof(T)),
-                                     (uint32_t)(L * sizeof(Out)));
-          const int ob = lane_on ? s_g[0] * (int)sizeof(Out) : kBufOff;
-          buf_store_words<W>(w, ro, ob);
-        } else if (lane_on) {
-          // several positions per wavefront: a store through each lane's
-          // own address
-          struct Words { int v[W]; } o;
-          __builtin_memcpy(o.v, w, sizeof(o));
-          *reinterpret_cast<Words *>(dst + ((size_t)node * L + s_g[0]) * (sizeof(Out) / sizeof(T))) = o;
         }
-      };
-      store_row(out, wd);
-      if constexpr (DC) {
-        static_assert(sizeof(typename PC::Out) == sizeof(Out), "curl output type");
-        int wc[W];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const typename PC::Out r = PC::result(stc[v], al, be);
-          __builtin_memcpy(&wc[v * (int)sizeof(Out) / 4], &r, sizeof(Out));
-        }
-        store_row(out2, wc);
       }
+      if constexpr (NE * EL * (DC ? 2 : 1) >= 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    // (the sums are formed here, not in the branch around each store)
+#pragma unroll
+    for (int g = 0; g < NE; ++g)
+#pragma unroll
+      for (int e = 0; e < EL; ++e) {
+        P::settle(st[g][e]);
+        if constexpr (DC) PC::settle(stc[g][e]);
+      }
+    struct OutElem { Out v[EL]; };
+    const size_t base = (size_t)(uint32_t)w0.x * row_out;
+#pragma unroll
+    for (int g = 0; g < NE; ++g) {
+      if (hl + g * LPN < nel) {
+        OutElem o;
+#pragma unroll
+        for (int e = 0; e < EL; ++e) o.v[e] = P::result_half(st[g][e], al, sc);
+        __builtin_memcpy(reinterpret_cast<unsigned char *>(out) + base + off_g[g], &o, sizeof(o));
+        if constexpr (DC) {
+#pragma unroll
+          for (int e = 0; e < EL; ++e) o.v[e] = PC::result_half(stc[g][e], al, sc);
+          __builtin_memcpy(reinterpret_cast<unsigned char *>(out2) + base + off_g[g], &o, sizeof(o));
+        }
+      }
+    }
+  };
+  for (int q = qa; q <= qb; ++q) {
+    const int plo = run_lo(q), n = run_hi(q) - plo;
+    const i32x4 *rq = rbuf + (q % kSweepwGeoSlots) * m.pmax;
+    const i32x4 *gq = gbuf + (q % kSweepwGeoSlots) * gcap;
+    for (int t = NPN * cw + sub; t < n; t += NPN * ncw) {
+      const i32x4 ref = rq[t];
+      if (__builtin_amdgcn_ballot_w64((ref.x & kSgeoFull) == 0) == 0)
+        position(gq + t * GW, ref, std::true_type{});
+      else
+        position(gq + t * GW, ref, std::false_type{});
     }
     // this step's LDS reads are done before the producers refill a slot
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    sq = sp;
   }
+}
+
+// The instance for LPN lanes per position (8, 16 or 32) and NE elements per
+// lane (1 .. sweepw_max_ne).
+template <class T, int OP, bool DC, int LPN, int NE = 1>
+void (*sweepw_kernel_ne(int ne))(SweepView, const int4 *, const T *, T *, T *, int, int, int) {
+  if constexpr (NE < sweepw_max_ne<T, OP, DC>()) {
+    if (ne > NE) return sweepw_kernel_ne<T, OP, DC, LPN, NE + 1>(ne);
+  }
+  return &k_sweepw<T, OP, LPN, NE, DC>;
+}
+template <class T, int OP, bool DC>
+auto sweepw_kernel(int lpn, int ne) {
+  return lpn == 8    ? sweepw_kernel_ne<T, OP, DC, 8>(ne)
+         : lpn == 16 ? sweepw_kernel_ne<T, OP, DC, 16>(ne)
+                     : sweepw_kernel_ne<T, OP, DC, 32>(ne);
 }
 
 // ---------------------------------------------------------------------------
@@ -2551,32 +2529,30 @@ __global__ void k_pack_lgeo(DevMesh m, i32x4 *__restrict__ dst) {
   __builtin_memcpy(&o[10], m.ncos + pr.r0, 48);
 }
 
-// Packs the wave-specialised sweep's per-position geometry (after the
-// scales are derived): kSgeoWords 16-byte words per position, in position
-// order, normals halved.  Entries past a row are neutral: zero normals, the
-// position's own LDS slot as reference, cos(lat) 1.
-__global__ void k_pack_sgeo(DevMesh m, i32x4 *__restrict__ dst) {
+// Packs the wave-specialised sweep's per-position records (after the scales
+// are derived): `vec` 0 for scalar inputs, 1 for vector inputs.  Entries past
+// a row are neutral: zero normals, cos(lat) 1.
+__global__ void k_pack_sgeo(DevMesh m, int vec, i32x4 *__restrict__ dst) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= m.V) return;
   const PosRec pr = m.pos[p];
   const int n = pr.r1 - pr.r0;
-  i32x4 *o = dst + (size_t)p * kSgeoWords;
-  o[0] = i32x4{pr.node, n, pr.selfslot, 0};
-  const double ab[2] = {pr.alpha, pr.beta};
-  __builtin_memcpy(&o[1], ab, 16);
+  const double sc[2] = {pr.alpha, vec ? m.coslat[pr.node] : pr.beta};
+  int w[4];
+  __builtin_memcpy(w, sc, 16);
+  i32x4 *o = dst + (size_t)p * (vec ? kSgeoWordsV : kSgeoWordsS);
+  o[0] = i32x4{pr.node, 0, w[0], w[1]};
+  o[1] = i32x4{w[2], w[3], 0, 0};
   for (int j = 0; j < 6; ++j) {  // halved normals (exact)
     const double2 v = j < n ? make_double2(0.5 * m.S[pr.r0 + j].x, 0.5 * m.S[pr.r0 + j].y)
                             : make_double2(0.0, 0.0);
     __builtin_memcpy(&o[2 + j], &v, 16);
   }
-  int lr[8];
-  for (int j = 0; j < 8; ++j) lr[j] = j < n ? m.lref[pr.r0 + j] : ((1 << 16) | pr.selfslot);
-  __builtin_memcpy(&o[8], lr, 32);
-  double cn[6];
-  for (int j = 0; j < 6; ++j) cn[j] = j < n ? m.ncos[pr.r0 + j] : 1.0;
-  __builtin_memcpy(&o[10], cn, 48);
-  const double c2[2] = {m.coslat[pr.node], 0.0};
-  __builtin_memcpy(&o[13], c2, 16);
+  if (vec) {
+    double cn[6];
+    for (int j = 0; j < 6; ++j) cn[j] = j < n ? m.ncos[pr.r0 + j] : 1.0;
+    __builtin_memcpy(&o[8], cn, 48);
+  }
 }
 
 template <class T, int OP>
@@ -2897,16 +2873,17 @@ atlas_status pack_lapl_geometry(MeshStore &m, int64_t ngrec) {
 }
 
 atlas_status pack_sweep_geometry(MeshStore &m) {
-  void *g = nullptr;
-  const size_t gb = std::max<size_t>(16, (size_t)m.d.V * kSgeoWords * 16);
-  if (hipMalloc(&g, gb) != hipSuccess) return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
-  m.allocations.push_back(g);
-  m.bytes += gb;
-  if (m.d.V > 0)
-    hipLaunchKernelGGL(k_pack_sgeo, dim3((m.d.V + 255) / 256), dim3(256), 0, 0, m.d,
+  for (int vec = 0; vec < 2; ++vec) {
+    void *g = nullptr;
+    const size_t gb = (size_t)m.d.V * (vec ? kSgeoWordsV : kSgeoWordsS) * 16;
+    if (hipMalloc(&g, gb) != hipSuccess) return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
+    m.allocations.push_back(g);
+    m.bytes += gb;
+    hipLaunchKernelGGL(k_pack_sgeo, dim3((m.d.V + 255) / 256), dim3(256), 0, 0, m.d, vec,
                        static_cast<i32x4 *>(g));
-  ATLASX_HIP(hipGetLastError());
-  m.d.sgeo = static_cast<const int4 *>(g);
+    ATLASX_HIP(hipGetLastError());
+    (vec ? m.d.sgeo_v : m.d.sgeo) = static_cast<const int4 *>(g);
+  }
   return ATLAS_OK;
 }
 
@@ -2931,106 +2908,138 @@ size_t flux_ws_bytes(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt) 
 }
 
 // Built-in shape (the autotuner can replace it per mesh and class), from
-// measurements at O1280, 137 levels.  Long columns: the column form over
-// blocks of 16 consecutive positions (a run of one parallel, so the
-// neighbour columns of consecutive blocks overlap in L2) with the automatic
-// lane-vector width, except: the FP64 gradient runs the wave-specialised
-// sweep (1024 threads), the FP32 gradient one level per lane (its
-// compensated sums keep every lane busy that way).  The Laplacian takes each
-// pass's own shape.  Short columns (measured at O320 and O1280, 1 to 47
-// levels, within 1.3x of the best candidate everywhere, 2-4x faster than the
-// flat form over the mesh's tiles): below 24 levels the flat form over
-// blocks of 64 positions (512 threads); from 24 levels the column form over
-// blocks of 16 positions, one level per lane (FP64 divergence and curl: the
-// automatic lane-vector width), and on meshes of many tiles the
-// register-staged sweep for the FP32 gradient (up to 79 levels) and the
-// wave-specialised sweep for the FP64 divergence and curl (below 48).
+// measurements: the wave-specialised sweep wherever its pieces fill the chip
+// (sweepw_default).  Elsewhere, below 24 levels the flat form over blocks of
+// 64 positions (512 threads), from 24 levels the column form over blocks of
+// 16 consecutive positions (a run of one parallel, so the neighbour columns
+// of consecutive blocks overlap in L2), one level per lane up to 47 levels
+// (FP64 divergence and curl: the automatic lane-vector width) and for the
+// FP32 gradient.  The Laplacian takes the fused form or each pass's own
+// shape.
 constexpr size_t kMaxLds = 160 * 1024;
-size_t sweepw_chunks(const DevMesh &m, int gw, int nvec, int want_vpc, int *nchunk, int *vpc_out,
-                     int *fcap_out, int *gcap_out);
 
-// Where the wave-specialised sweep is the built-in shape (meshes of many
-// tiles with packed geometry), measured at O1280 against the other forms.
-// Narrow level chunks take up to eight positions per wavefront, so short
-// columns fill the lanes too.  FP64 gradient from 4 levels (8: 0.57 against
-// 0.87 ms for the flat form, 37: 1.51 against 2.75 for the column form),
-// long columns in the chunk count that fills the most lanes; FP64
-// divergence and curl from 2 levels (4: 0.47 against 0.62 ms, 16: 0.82
-// against 1.71), from 33 in chunks of 16 lane vectors.  In FP32, where one chunk of at most 32 lane vectors holds
-// the column: the gradient from 12 to 128 levels (16: 0.82 against 1.37 ms
-// for the flat form, 64: 1.50 against 2.07 for the register-staged sweep,
-// 91: 2.58 against 3.02 for the column form), from 88 to 160 levels in
-// chunks of 16 lane vectors, and the divergence and curl from 6 to 64
-// levels (8: 0.65 against 0.96 ms, 48: 2.06 against 2.80), from 41 in
-// chunks of 16, on the largest meshes to 96.  Workgroups of 768
-// threads where the LDS fits twice in a compute unit, in FP32 (24 levels of
-// a vector field: 1.59 against 1.92 ms with 1024), for the FP64 divergence
-// in chunks of 16, and for FP64 chunks of at most 8 lane vectors (4 levels
-// of the gradient: 0.50 against 0.57 ms).
-static bool sweepw_default(const DevMesh &m, atlas_op op, atlas_dtype dt, int nlev, LaunchShape *s) {
-  const bool grad = op == ATLAS_OP_GRADIENT;
-  if (!grad && op != ATLAS_OP_DIVERGENCE && op != ATLAS_OP_CURL) return false;
-  // lane vectors of 16 bytes: levels per lane vector
-  const int nv = dt == ATLAS_F64 ? (grad ? 2 : 1) : (grad ? 4 : 2);
-  const int nvec = (nlev + nv - 1) / nv;
-  int nch = 0, vpc = 0;
-  const size_t lds = sweepw_chunks(m, grad ? 10 : kSgeoWords, nvec, 0, &nch, &vpc, nullptr, nullptr);
-  bool take;
-  int want = 0;  // lane vectors per chunk asked for (0: as many as fit)
-  if (dt == ATLAS_F64 && grad && nch > 1) {
-    // columns of several chunks: the count (up to two more than the fewest)
-    // that fills the most lanes with whole chunks (137 levels: four chunks
-    // of 18, three positions per wavefront, 5.19 against 5.45 ms for two
-    // chunks of 35)
-    double best = 0.0;
-    for (int c = nch; c <= nch + 2; ++c) {
-      const int v = (nvec + c - 1) / c;
-      const double fill = (double)(min(8, 64 / v) * v) / 64.0;
-      if (fill > best + 1e-9) {
-        best = fill;
-        want = v;
+// How the wave-specialised sweep runs a column: the cut of the tiles, the
+// level chunks (nchunk even chunks of at most vpc 16-byte vectors), the
+// lanes per position and elements per lane, and the LDS bytes.
+struct SweepwPlan {
+  int cut = 0, vpc = 0, nchunk = 0, lpn = 0, ne = 0, block = 0;
+  size_t lds = 0;
+};
+
+// Chunk ends inside a row are what the sweep loses most by: the row's 128-byte
+// lines there are written in halves by two workgroups (14.5 GB of rows cut in
+// four: 3.2 TB/s, whole rows: 5.1 TB/s).  So the tiles are cut into the fewest
+// parts with which a whole column fits in LDS, or that need the fewest
+// chunks (O1280 FP64 gradient, 137 levels: four chunks on whole tiles 5.18
+// ms, two chunks 4.77, whole columns on half tiles 4.57) -- but FP64 vector
+// columns stay on whole tiles: most of their bytes are read, and narrow
+// parts read more of them twice (O1280 divergence, 137 levels: three chunks
+// on whole tiles 5.19 ms, whole columns on thirds 5.44).  Of a small mesh's
+// cuts of the bands the one whose rounds of workgroups take the fewest
+// steps (a last round that is nearly empty costs a whole one: O160, 37
+// levels, FP32 divergence, 520 pieces on 512 places 33 us, 500 pieces 23).
+// `want`: at most so many vectors per chunk; epv: elements per vector.
+static SweepwPlan sweepw_plan(const MeshStore &ms, bool vec, bool whole, int epv, int max_ne,
+                              int nvec, int want) {
+  const int most = 32 * max_ne / epv;
+  const int cus = device_cu_count();
+  SweepwPlan best;
+  int64_t best_steps = 0;
+  for (size_t k = 0; k < ms.cuts.size(); ++k) {
+    const SweepView &v = ms.cuts[k];
+    if (whole && v.parts > 1) continue;
+    auto bytes = [&](int c) {
+      return (size_t)16 * (kSweepwSlots * max(1, v.segmax) * c +
+                           kSweepwGeoSlots * max(1, v.pmax) *
+                               (1 + (vec ? kSgeoWordsV : kSgeoWordsS))) +
+             kSweepwLdsTail;
+    };
+    SweepwPlan p;
+    p.cut = (int)k;
+    p.vpc = min(want > 0 ? min(want, most) : most, nvec);
+    p.nchunk = (nvec + p.vpc - 1) / p.vpc;
+    p.vpc = (nvec + p.nchunk - 1) / p.nchunk;
+    while (p.vpc > 1 && bytes(p.vpc) > kMaxLds) {
+      ++p.nchunk;
+      p.vpc = (nvec + p.nchunk - 1) / p.nchunk;
+    }
+    p.nchunk = (nvec + p.vpc - 1) / p.vpc;
+    p.lds = bytes(p.vpc);
+    if (k > 0 && (p.nchunk > best.nchunk ||
+                  (p.nchunk == best.nchunk && v.parts > ms.cuts[best.cut].parts)))
+      continue;
+    // lanes per position and elements per lane: the cheapest pair that
+    // holds the chunk, a wavefront's cost being its elements and a fixed part
+    // (the record's decoding, about three elements' worth) over its positions
+    const int nel = p.vpc * epv;
+    int cost = INT_MAX;
+    for (int l : {8, 16, 32}) {
+      const int e = (nel + l - 1) / l;
+      if (e <= max_ne && (e + 3) * l < cost) {
+        cost = (e + 3) * l;
+        p.lpn = l;
+        p.ne = e;
       }
     }
-  } else if (dt == ATLAS_F64 && !grad && nlev > 32) {
-    want = 16;  // vector columns wider than 32 lane vectors: chunks of 16
-                // (four positions per wavefront) at two workgroups per CU;
-                // O1280: 48 levels 2.07 against 2.74 ms for one chunk of
-                // 48, 72 levels 3.33 against 3.88, 110 levels 4.78 against
-                // 5.82 for the column form, 137 levels 6.19 against 6.57
-                // for three chunks of 46
-  } else if (dt == ATLAS_F32 && !grad && nlev > 40 &&
-             (nlev <= 64 || (nlev <= 96 && m.ntiles >= 4096))) {
-    want = 16;  // (O1280, 48 levels: 1.86 against 2.05 ms in one chunk;
-                // 91 levels: 3.15 against 3.30 for the column form, which
-                // stays ahead at O640 from 65 levels)
-  } else if (dt == ATLAS_F32 && grad && nlev >= 88 && nlev <= 160) {
-    want = 16;  // (O1280, 91 levels: 2.51 against 2.70 ms in one chunk;
-                // 137 levels: 3.81 against 3.87 for the column form)
-  }
-  if (want && want * nv <= 64) {  // a level_chunk a caller may pass back
-    int nch2 = 0, vpc2 = 0;
-    const size_t l2 =
-        sweepw_chunks(m, grad ? 10 : kSgeoWords, nvec, want, &nch2, &vpc2, nullptr, nullptr);
-    if (l2 <= kMaxLds) {
-      s->level_chunk = want * nv;
-      const bool two_per_cu = 2 * l2 <= kMaxLds && !(dt == ATLAS_F64 && grad);
-      s->variant = ATLAS_VARIANT_SWEEP;
-      s->block = two_per_cu ? 768 : 1024;
-      s->nodes_per_block = 0;
-      s->blocks_per_cu = 0;
-      s->level_vec = 0;
-      return true;
+    // the producers, and consumers for one position per lane group a step
+    // (where two workgroups share a compute unit, for one position less: few
+    // runs have pmax)
+    const int npn = 64 / p.lpn;
+    const int own = max(1, 2 * p.lds <= kMaxLds ? v.pmax - 1 : v.pmax);
+    const int waves = min(16, kSweepwGroups * kSweepwGroupWaves + (own + npn - 1) / npn);
+    p.block = 64 * waves;
+    // steps until the last round of workgroups is done (four for each
+    // one's start); waves a compute unit holds by the kernels' registers
+    const int held = p.ne <= 2 ? 32 : p.ne == 3 ? 24 : p.ne == 4 ? 20 : 16;
+    const int64_t places =
+        (int64_t)cus * max(1, min((int)(kMaxLds / p.lds), held / max(8, waves)));
+    const int64_t units = (int64_t)v.ntiles * p.nchunk;
+    const int64_t steps = (units + places - 1) / places * (v.rings + 4);
+    if (k == 0 || p.nchunk < best.nchunk || v.parts < ms.cuts[best.cut].parts ||
+        steps < best_steps) {
+      best = p;
+      best_steps = steps;
     }
   }
-  if (dt == ATLAS_F64)
-    take = grad ? nlev >= 4
-                : nlev >= 2 && (nlev < 48 || (nch <= 3 && (vpc >= 36 || (vpc >= 24 && vpc <= 32))));
-  else
-    take = nch == 1 && vpc <= 32 && nlev >= (grad ? 12 : 6);
-  if (!take) return false;
-  const bool two_per_cu = 2 * lds <= kMaxLds && (dt == ATLAS_F32 || vpc <= kSweepwNpn8);
+  return best;
+}
+template <class T, int OP, bool DC>
+static SweepwPlan sweepw_plan(const MeshStore &m, int nlev, int level_chunk) {
+  constexpr int nv16 = 16 / (int)sizeof(typename Pol<T, OP>::V);
+  return sweepw_plan(m, Pol<T, OP>::kVecIn, Pol<T, OP>::kVecIn && sizeof(T) == 8,
+                     nv16 / sweepw_elem_levels<T, DC>(), sweepw_max_ne<T, OP, DC>(),
+                     (nlev + nv16 - 1) / nv16, (level_chunk + nv16 - 1) / nv16);
+}
+
+// Where the wave-specialised sweep is the built-in shape: on large meshes, and
+// wherever its pieces fill the chip.  Columns that leave room for two
+// workgroups per compute unit ask for 64 tiles (in up to six bands each;
+// O160 has 130: 37 levels, FP32 divergence 27.7 against 32 us for the column
+// form; O80 has 28: 16 against 11 us) and 1.5 M values to hide the walk's
+// latency behind (O160, 10 levels, FP64 gradient: 17.6 against 16.2 us; O200:
+// 23.3 against 26.5), longer ones and those above 48 levels (O160, 91 levels,
+// FP32 gradient: 43 against 34 us) for 600 parts and chunks of whole bands
+// (O320 has 920: 137 levels, FP64 gradient 335 against 466 us; O200 has 570:
+// FP64 divergence 195 against 190 us).
+static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int nlev,
+                           LaunchShape *s) {
+  const DevMesh &m = ms.d;
+  const bool grad = op == ATLAS_OP_GRADIENT;
+  if (!grad && op != ATLAS_OP_DIVERGENCE && op != ATLAS_OP_CURL) return false;
+  const int nv = dt == ATLAS_F64 ? (grad ? 2 : 1) : (grad ? 4 : 2);  // levels per vector
+  if (nlev < nv || m.ntiles < 64) return false;
+  const bool large = m.ntiles >= kSweepMinTiles;
+  if (!large && (int64_t)m.V * nlev < 1500000) return false;
+  const SweepwPlan p = dt == ATLAS_F64 ? (grad ? sweepw_plan<double, OP_GRAD, false>(ms, nlev, 0)
+                                               : sweepw_plan<double, OP_DIV, false>(ms, nlev, 0))
+                                       : (grad ? sweepw_plan<float, OP_GRAD, false>(ms, nlev, 0)
+                                               : sweepw_plan<float, OP_DIV, false>(ms, nlev, 0));
+  if (p.lds > kMaxLds) return false;
+  if (!large && (nlev > 48 || 2 * p.lds > kMaxLds) &&
+      m.ntiles * ms.cuts[p.cut].parts * p.nchunk < 600)
+    return false;
   s->variant = ATLAS_VARIANT_SWEEP;
-  s->block = two_per_cu ? 768 : 1024;
+  s->block = max(512, p.block);
   s->nodes_per_block = 0;
   s->level_chunk = 0;
   s->blocks_per_cu = 0;
@@ -3047,7 +3056,7 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   const bool sweep_fits = m.d.sweep_ok && m.d.ntiles >= kSweepMinTiles &&
                           max(1, m.d.segmax) * kGeoWords <= 768;
   // the wave-specialised sweep needs the packed geometry and rows of 4..6
-  const bool sweepw_fits = sweep_fits && m.d.sgeo && m.d.maxdeg <= 6 && m.d.mindeg >= kMinRow;
+  const bool sweepw_fits = m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow;
   if (op == ATLAS_OP_LAPLACIAN) {
     // large meshes: the fused one-pass form, wave-specialised (it moves a
     // third of the two passes' field bytes; measured faster than the two
@@ -3066,7 +3075,7 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     s.per_pass = 1;
     return s;
   }
-  if (sweepw_fits && sweepw_default(m.d, op, dt, nlev, &s)) return s;
+  if (sweepw_fits && sweepw_default(m, op, dt, nlev, &s)) return s;
   if (nlev < 24) return s;
   // the sweep runs one workgroup per tile and level chunk, each walking its
   // band's parallels in turn: only a mesh of many tiles fills the chip
@@ -3108,33 +3117,6 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
 }
 
 
-// Level chunking of the wave-specialised sweep: nvec lane vectors per column
-// in nchunk even chunks of vpc (at most 64, or level_chunk's share), more
-// chunks until the field ring (kSweepwSlots slots) and the geometry ring
-// (kSweepwGeoSlots slots of gw words per position) fit in LDS.  Returns the
-// LDS bytes.
-size_t sweepw_chunks(const DevMesh &m, int gw, int nvec, int want_vpc, int *nchunk, int *vpc_out,
-                     int *fcap_out, int *gcap_out) {
-  int vpc = min(want_vpc > 0 ? want_vpc : 64, nvec);
-  int nch = (nvec + vpc - 1) / vpc;
-  vpc = (nvec + nch - 1) / nch;
-  const int seg = max(1, m.segmax);
-  const int gcap = (seg * gw + 63) / 64 * 64;
-  auto fcap_of = [&](int v) { return (seg * v + 63) / 64 * 64; };
-  auto bytes = [&](int v) {
-    return (size_t)16 * (kSweepwSlots * fcap_of(v) + kSweepwGeoSlots * gcap);
-  };
-  while (vpc > 1 && bytes(vpc) > kMaxLds) {
-    ++nch;
-    vpc = (nvec + nch - 1) / nch;
-  }
-  *nchunk = (nvec + vpc - 1) / vpc;
-  *vpc_out = vpc;
-  if (fcap_out) *fcap_out = fcap_of(vpc);
-  if (gcap_out) *gcap_out = gcap;
-  return bytes(vpc);
-}
-
 int device_cu_count() {
   static int cached[64] = {0};
   int dev = 0;
@@ -3170,32 +3152,19 @@ static bool sweepw_applies(const DevMesh &m, int nlev, const LaunchShape &sh) {
 // The wave-specialised sweep of `sh` (sweepw_applies); DC: the divergence
 // and, into out2, the curl of the same field in one pass.
 template <class T, int OP, bool DC>
-static atlas_status launch_sweepw(const DevMesh &m, const T *in, T *out, T *out2, int nlev,
+static atlas_status launch_sweepw(const MeshStore &ms, const T *in, T *out, T *out2, int nlev,
                                   const LaunchShape &sh, hipStream_t st) {
-  constexpr int nv16 = 16 / (int)sizeof(typename Pol<T, OP>::V);
-  const int nvec = (nlev + nv16 - 1) / nv16;
-  constexpr int gw = Pol<T, OP>::kVecIn ? kSgeoWords : 10;
-  int nchunk = 0, vpc = 0, fcap = 0, gcap = 0;
-  const size_t lds = sweepw_chunks(m, gw, nvec,
-                                   sh.level_chunk > 0 ? (sh.level_chunk + nv16 - 1) / nv16 : 0,
-                                   &nchunk, &vpc, &fcap, &gcap);
-  if (lds > kMaxLds) return fail(ATLAS_EINVAL, "sweep tile too large for LDS");
-  const int units = m.ntiles * nchunk;
-  const int per = (units + 7) / 8;
-  void (*kern)(DevMesh, const T *, T *, T *, int, int, int, int, int, int) = nullptr;
-  // NPN positions per wavefront when NPN chunks fit in its lanes
-  if constexpr (lane_vec_ok<T, OP, nv16>())
-    kern = vpc <= 8    ? k_sweepw<T, OP, nv16, 8, DC>
-           : vpc <= 12 ? k_sweepw<T, OP, nv16, 5, DC>
-           : vpc <= 16 ? k_sweepw<T, OP, nv16, 4, DC>
-           : vpc <= 21 ? k_sweepw<T, OP, nv16, 3, DC>
-           : vpc <= 32 ? k_sweepw<T, OP, nv16, 2, DC>
-                       : k_sweepw<T, OP, nv16, 1, DC>;
-  if (!kern) return fail(ATLAS_EINVAL, "wave-specialised sweep not available");
+  const DevMesh &m = ms.d;
+  const SweepwPlan p = sweepw_plan<T, OP, DC>(ms, nlev, sh.level_chunk);
+  if (p.lds > kMaxLds) return fail(ATLAS_EINVAL, "sweep tile too large for LDS");
+  const SweepView &v = ms.cuts[p.cut];
+  const int64_t units = (int64_t)v.ntiles * p.nchunk;
+  const int per = (int)((units + 7) / 8);
+  auto kern = sweepw_kernel<T, OP, DC>(p.lpn, p.ne);
   ATLASX_HIP(hipFuncSetAttribute((const void *)kern,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(kern, dim3(per * 8), dim3(sh.block), lds, st, m, in, out, out2, nlev, vpc,
-                     m.ntiles, per, fcap, gcap);
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds));
+  hipLaunchKernelGGL(kern, dim3(per * 8), dim3(sh.block), p.lds, st, v,
+                     Pol<T, OP>::kVecIn ? m.sgeo_v : m.sgeo, in, out, out2, nlev, p.vpc, per);
   ATLASX_HIP(hipGetLastError());
   return ATLAS_OK;
 }
@@ -3314,7 +3283,7 @@ static atlas_status launch_typed(const MeshStore &ms, const T *in, int nlev, T *
       // threads, else the one-level-per-lane sweep runs (same results)
       // wave-specialised sweep (blocks_per_cu == 0): 16-byte lane vectors
       if (sweepw_applies<T, OP>(m, nlev, sh)) {
-        atlas_status s = launch_sweepw<T, OP, false>(m, in, out, nullptr, nlev, sh, st);
+        atlas_status s = launch_sweepw<T, OP, false>(ms, in, out, nullptr, nlev, sh, st);
         if (s != ATLAS_OK) return s;
         break;
       }
@@ -3436,28 +3405,16 @@ static atlas_status launch_div_curl_typed(const MeshStore &ms, atlas_dtype dt, c
     // where the divergence runs the wave-specialised sweep, the curl rides
     // on the same loads
     LaunchShape sh = shape_from(nullptr, ms, ATLAS_OP_DIVERGENCE, nlev, dt);
-    if (sh.variant == ATLAS_VARIANT_SWEEP && sh.level_chunk > 0) {
-      // chunks of 16 lane vectors pay for the divergence alone; with the
-      // curl's states beside it the one pass runs slower in them (9.67
-      // against 8.42 ms at O1280, 137 levels), so it takes the widest
-      // chunks where at most three of at least 36 (or 24-32) lane vectors
-      // fill the lanes, else the column form
-      int nch = 0, vpc = 0;
-      constexpr int nv16 = 16 / (int)sizeof(typename Pol<T, OP_DIV>::V);
-      const size_t lds = sweepw_chunks(m, kSgeoWords, (nlev + nv16 - 1) / nv16, 0, &nch, &vpc,
-                                       nullptr, nullptr);
-      const bool wide = sizeof(T) == 8
-                            ? nlev < 48 || (nch <= 3 && (vpc >= 36 || (vpc >= 24 && vpc <= 32)))
-                            : nch == 1 && vpc <= 32;
-      if (wide) {
-        sh.level_chunk = 0;
-        sh.block = sizeof(T) == 4 && 2 * lds <= kMaxLds ? 768 : 1024;
-      } else {
-        sh.variant = ATLAS_VARIANT_COLUMN;
+    if (sh.variant == ATLAS_VARIANT_SWEEP && sweepw_applies<T, OP_DIV>(m, nlev, sh)) {
+      // (FP32 columns of several chunks: on large meshes only; O1280, 137
+      // levels 4.93 against 5.31 ms for the column form, O320 380 against
+      // 345 us)
+      const SweepwPlan p = sweepw_plan<T, OP_DIV, true>(ms, nlev, sh.level_chunk);
+      if (p.lds <= kMaxLds && (p.nchunk == 1 || sizeof(T) == 8 || m.ntiles >= kSweepMinTiles)) {
+        sh.block = max(512, p.block);
+        return launch_sweepw<T, OP_DIV, true>(ms, in, od, oc, nlev, sh, st);
       }
     }
-    if (sh.variant == ATLAS_VARIANT_SWEEP && sweepw_applies<T, OP_DIV>(m, nlev, sh))
-      return launch_sweepw<T, OP_DIV, true>(m, in, od, oc, nlev, sh, st);
   }
   const int nv = nlev >= 48 ? auto_level_vec<T, OP_DIV>(nlev, m.maxdeg, m.mindeg) : 0;
   if (nv == 0) {
