@@ -293,14 +293,10 @@ typedef struct {
   int32_t variant;          /* atlas_variant                                */
   int32_t block_threads;    /* 64, 128, 256, 512 or 1024                    */
   int32_t nodes_per_block;  /* column/flat: processing positions per block;
-                               0 = the mesh's tiles.  Fused form,
-                               wave-specialised: 4 or 5 = slots of its ring
-                               of field runs (4: each run is loaded one step
-                               before use instead of one and a half, and a
-                               longer level chunk fits in LDS); 0 = five, or
-                               four where five would need one more level
-                               chunk; other values run the register-staged
-                               form                                         */
+                               0 = the mesh's tiles.  Fused form: 0, 4 or 5
+                               runs the wave-specialised form (4 and 5
+                               picked a ring size once), other values the
+                               register-staged one                          */
   int32_t level_chunk;      /* column: levels per unit of work (1..64); the
                                units run chunk by chunk over the whole mesh
                                so a parallel's columns are still cached when
@@ -315,13 +311,13 @@ typedef struct {
                                per wavefront per step, so the set of columns
                                in flight stays small enough for the L2;
                                0 = one workgroup per tile.  Sweep form: 0 =
-                               wave-specialised workgroups (two waves load
+                               wave-specialised workgroups (four waves load
                                the next parallels straight into LDS, the
                                others compute and store; 16-byte lane
                                vectors, at least 256 threads, level_vec 0
                                or the 16-byte width); > 0 = every wave
                                stages loads through registers.  Fused
-                               form: 0 = wave-specialised (four wavefronts
+                               form: 0 = wave-specialised (two wavefronts
                                load the next parallels straight into LDS,
                                the others compute and store; at least 320
                                threads, 16-byte lanes); 1..3 = every wave

@@ -84,6 +84,25 @@ struct SweepView {
                                      //      rows 4, 5} (rows of the ring: slot * segmax + t)
 };
 
+// The pieces of the wave-specialised fused Laplacian, cut like the sweep's:
+// per piece a window of parallels, each with the run of nodes whose field is
+// read (f-run), the run whose gradients are formed (g-run) and the piece's
+// own positions; references as rows of the rings of f-runs and g-runs.
+constexpr int kLswFieldSlots = 5, kLswGradSlots = 4;
+struct LaplView {
+  int32_t ntiles = 0;                // pieces
+  int32_t parts = 1, bands = 1;
+  int32_t rings = 0;                 // most own parallels of a piece
+  int32_t fmax = 0, gmax = 0;        // longest f-run / g-run
+  int32_t pmax = 0;                  // most own positions of a piece on one parallel
+  const int32_t *tile_seg = nullptr; // [ntiles+1] window range of a piece
+  const int4 *fseg = nullptr;        // {ring offset, ring size, f first, f length}
+  const int4 *gseg = nullptr;        // {g first, g length, first of its references, 0}
+  const int2 *seg_pos = nullptr;     // own positions on the parallel [lo, hi)
+  const int4 *grefs = nullptr;       // per g-run node: references into the f-runs
+  const int4 *orefs = nullptr;       // [V] own positions: references into the g-runs
+};
+
 struct DevMesh {
   int32_t V = 0;          // nodes
   int32_t E = 0;          // mesh edges
@@ -132,6 +151,7 @@ struct DevMesh {
   const int4 *l2_lgeo = nullptr;     // packed own-position records (device-built)
   const int4 *sgeo = nullptr;        // packed sweep records, scalar inputs (device-built)
   const int4 *sgeo_v = nullptr;      // the same, vector inputs
+  const int4 *sgeo_n = nullptr;      // the scalar ones by node
 };
 
 // ------------------------------------------------------------- kernels
@@ -208,6 +228,7 @@ bool zipper_conforming(const atlas_mesh_desc *d, const std::vector<int64_t> &off
 struct MeshStore {
   DevMesh d;
   std::vector<SweepView> cuts;  // of the sweep's tiles, by parts, then bands (empty: no sweep)
+  std::vector<LaplView> lcuts;  // of the fused Laplacian's
   int device = 0;
   RemapSource rs;
   const double *node_lon = nullptr;  // device [V], by node id

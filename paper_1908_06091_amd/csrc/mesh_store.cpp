@@ -614,6 +614,159 @@ static bool lapl_plan(const std::vector<int64_t> &off, const std::vector<int32_t
   return true;
 }
 
+// The fused Laplacian's pieces (tiles cut as in cut_plan) on the two-ring
+// window of lapl_plan, with references as ring rows.  False as for cut_plan.
+struct LaplCutPlan {
+  std::vector<int32_t> tile_seg;
+  std::vector<int4> fseg, gseg, grefs, orefs;
+  std::vector<int2> seg_pos;
+  int32_t fmax = 1, gmax = 1, pmax = 1, rings = 0;
+};
+
+static bool lapl_cut_plan(const std::vector<int64_t> &off, const std::vector<int32_t> &ring_of,
+                          const std::vector<int32_t> &perm, const std::vector<int32_t> &inv,
+                          const std::vector<int32_t> &tile_ptr, const std::vector<int32_t> &rowp,
+                          const std::vector<int32_t> &nbr, int parts, int bands, LaplCutPlan &lp) {
+  const int64_t T = (int64_t)tile_ptr.size() - 1;
+  const int32_t nr = (int32_t)off.size() - 1;
+  auto nb = [&](int32_t r) { return (int32_t)((uint32_t)nbr[r] & ~kPoleBit); };
+  struct Part {
+    std::vector<int32_t> nseg;
+    std::vector<int4> fseg, gseg;  // (gseg.z: g nodes before this one in the part)
+    std::vector<int2> seg_pos;
+    int32_t fmax = 1, gmax = 1, pmax = 1, rings = 0, ng = 0;
+    bool ok = true;
+  };
+  const int pieces = parts * bands;
+  const int nthr = host_threads(T);
+  std::vector<Part> done(nthr);
+  on_threads(nthr, [&](int w) {
+    Part &o = done[w];
+    std::vector<int2> own;
+    std::vector<std::vector<int32_t>> gneed, fneed;
+    for (int64_t t = T * w / nthr; t < T * (w + 1) / nthr && o.ok; ++t) {
+      const int32_t j0 = ring_of[perm[tile_ptr[t]]];
+      own.clear();
+      for (int32_t p = tile_ptr[t]; p < tile_ptr[t + 1]; ++p) {
+        const int32_t q = ring_of[perm[p]] - j0;
+        while ((int32_t)own.size() <= q) own.push_back(make_int2(p, p));
+        own[q].y = p + 1;
+      }
+      for (int u = 0; u < pieces; ++u) {
+        const int k = u % parts, b = u / parts;
+        const int64_t nq = (int64_t)own.size();
+        const int32_t qa = (int32_t)(nq * b / bands), qb = (int32_t)(nq * (b + 1) / bands);
+        o.rings = std::max(o.rings, qb - qa);
+        const int32_t rlo = std::max(0, j0 + qa - 2), rhi = std::min(nr - 1, j0 + qb + 1);
+        const int32_t W = rhi - rlo + 1;
+        gneed.assign(W, {});
+        fneed.assign(W, {});
+        const size_t s0 = o.seg_pos.size();
+        for (int32_t q = 0; q < W; ++q) o.seg_pos.push_back(make_int2(0, 0));
+        for (int32_t q = qa; q < qb; ++q) {
+          const int32_t n = own[q].y - own[q].x, j = j0 + q;
+          const int2 pr = make_int2(own[q].x + (int32_t)((int64_t)n * k / parts),
+                                    own[q].x + (int32_t)((int64_t)n * (k + 1) / parts));
+          o.seg_pos[s0 + j - rlo] = pr;
+          o.pmax = std::max(o.pmax, pr.y - pr.x);
+          for (int32_t p = pr.x; p < pr.y; ++p) {
+            gneed[j - rlo].push_back((int32_t)(perm[p] - off[j]));
+            for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r)  // (no pole edge in a divergence)
+              if (!((uint32_t)nbr[r] & kPoleBit))
+                gneed[ring_of[nb(r)] - rlo].push_back((int32_t)(nb(r) - off[ring_of[nb(r)]]));
+          }
+        }
+        o.nseg.push_back(W);
+        for (int32_t q = 0; q < W; ++q) {
+          const int32_t j = rlo + q, nx = (int32_t)(off[j + 1] - off[j]);
+          int32_t lo = 0, len = 0;
+          if (!cyclic_run(gneed[q], nx, lo, len)) o.ok = false;
+          o.gmax = std::max(o.gmax, len);
+          o.gseg.push_back(make_int4(lo, len, o.ng, 0));
+          o.ng += len;
+          // every node of the g-run gets a gradient
+          for (int32_t s = 0; s < len; ++s) {
+            const int32_t i = (int32_t)off[j] + (lo + s) % nx, p = inv[i];
+            fneed[q].push_back(i - (int32_t)off[j]);
+            if (rowp[p + 1] - rowp[p] > 6) o.ok = false;
+            for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r) {
+              const int32_t jn = ring_of[nb(r)];
+              if (jn < rlo || jn > rhi) {
+                o.ok = false;
+                break;
+              }
+              fneed[jn - rlo].push_back((int32_t)(nb(r) - off[jn]));
+            }
+          }
+        }
+        for (int32_t q = 0; q < W; ++q) {
+          const int32_t nx = (int32_t)(off[rlo + q + 1] - off[rlo + q]);
+          int32_t lo = 0, len = 0;
+          if (!cyclic_run(fneed[q], nx, lo, len)) o.ok = false;
+          o.fmax = std::max(o.fmax, len);
+          o.fseg.push_back(make_int4((int32_t)off[rlo + q], nx, lo, len));
+        }
+      }
+    }
+  });
+  lp.tile_seg.assign(1, 0);
+  int64_t ng = 0;
+  for (const Part &o : done) {
+    if (!o.ok) return false;
+    for (int32_t n : o.nseg) lp.tile_seg.push_back(lp.tile_seg.back() + n);
+    lp.fseg.insert(lp.fseg.end(), o.fseg.begin(), o.fseg.end());
+    for (int4 g : o.gseg) lp.gseg.push_back(make_int4(g.x, g.y, g.z + (int32_t)ng, 0));
+    lp.seg_pos.insert(lp.seg_pos.end(), o.seg_pos.begin(), o.seg_pos.end());
+    lp.fmax = std::max(lp.fmax, o.fmax);
+    lp.gmax = std::max(lp.gmax, o.gmax);
+    lp.pmax = std::max(lp.pmax, o.pmax);
+    lp.rings = std::max(lp.rings, o.rings);
+    ng += o.ng;
+    if (ng >= INT32_MAX) return false;
+  }
+  if ((int64_t)kLswFieldSlots * lp.fmax >= 65536 || (int64_t)kLswGradSlots * lp.gmax >= 65536)
+    return false;
+  lp.grefs.resize((size_t)ng);
+  lp.orefs.resize(perm.size());
+  on_threads(nthr, [&](int w) {
+    for (int64_t u = T * w / nthr * pieces; u < T * (w + 1) / nthr * pieces; ++u) {
+      const int32_t s0 = lp.tile_seg[u], s1 = lp.tile_seg[u + 1];
+      for (int32_t s = s0; s < s1; ++s) {
+        // the references of position p on the parallel of run s: rows of
+        // the ring of f-runs (grad) or g-runs
+        auto refs = [&](int32_t p, bool grad) {
+          auto row = [&](int32_t i, int32_t dq) {
+            const int4 f = lp.fseg[s + dq];
+            int32_t t = i - f.x - (grad ? f.z : lp.gseg[s + dq].x);
+            if (t < 0) t += f.y;
+            return grad ? (s + dq - s0) % kLswFieldSlots * lp.fmax + t
+                        : (s + dq - s0) % kLswGradSlots * lp.gmax + t;
+          };
+          const int32_t n = rowp[p + 1] - rowp[p], j = ring_of[perm[p]];
+          const int32_t self = row(perm[p], 0);
+          int32_t r[6], flags = n << 16;
+          for (int32_t k = 0; k < 6; ++k) {
+            r[k] = self;
+            if (k >= n) continue;
+            const bool pole = ((uint32_t)nbr[rowp[p] + k] & kPoleBit) != 0;
+            if (pole) flags |= kSgeoPole << k;
+            // (a pole edge does not enter the divergence, and its far end
+            // need not be in the g-run)
+            if (grad || !pole) r[k] = row(nb(rowp[p] + k), ring_of[nb(rowp[p] + k)] - j);
+          }
+          if (n == 6 && !(flags & (63 * kSgeoPole))) flags |= kSgeoFull;
+          return make_int4(self | flags, r[0] | r[1] << 16, r[2] | r[3] << 16, r[4] | r[5] << 16);
+        };
+        const int4 f = lp.fseg[s], g = lp.gseg[s];
+        for (int32_t t = 0; t < g.y; ++t)
+          lp.grefs[g.z + t] = refs(inv[f.x + (g.x + t) % f.y], true);
+        for (int32_t p = lp.seg_pos[s].x; p < lp.seg_pos[s].y; ++p) lp.orefs[p] = refs(p, false);
+      }
+    }
+  });
+  return true;
+}
+
 template <class T>
 static atlas_status upload_array(MeshStore &m, const std::vector<T> &h, const T **dptr) {
   void *p = nullptr;
@@ -709,6 +862,21 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
                     cuts[k]))
         cuts.clear();
   }
+  std::vector<std::pair<int, int>> lshapes = {{1, 1}, {2, 1}};
+  if ((int64_t)tile_ptr.size() - 1 < kSweepMinTiles)
+    lshapes = {{1, 1}, {1, 2}, {1, 4}, {2, 1}, {2, 2}, {2, 4}};
+  std::vector<LaplCutPlan> lcuts(cuts.empty() ? 0 : lshapes.size());
+  if (!lcuts.empty()) {
+    const std::vector<int64_t> off = rings_of(d);
+    std::vector<int32_t> ring_of(V), inv(V);
+    for (size_t j = 0; j + 1 < off.size(); ++j)
+      for (int64_t i = off[j]; i < off[j + 1]; ++i) ring_of[i] = (int32_t)j;
+    for (int64_t p = 0; p < V; ++p) inv[perm[p]] = (int32_t)p;
+    for (size_t k = 0; k < lcuts.size(); ++k)
+      if (!lapl_cut_plan(off, ring_of, perm, inv, tile_ptr, rowp, nbr, lshapes[k].first,
+                         lshapes[k].second, lcuts[k]))
+        lcuts.clear();
+  }
   // cos(lat) of every incidence's neighbour, so a node's row is read with
   // contiguous loads
   std::vector<double> ncos(nbr.size());
@@ -795,6 +963,26 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
     v.parts = shapes[k].first;
     v.bands = shapes[k].second;
     v.ntiles = (int32_t)cuts[k].tile_seg.size() - 1;
+  }
+  m->lcuts.resize(lcuts.size());
+  for (size_t k = 0; k < lcuts.size(); ++k) {
+    LaplView &v = m->lcuts[k];
+    if ((st = upload_array(*m, lcuts[k].tile_seg, &v.tile_seg)) != ATLAS_OK ||
+        (st = upload_array(*m, lcuts[k].fseg, &v.fseg)) != ATLAS_OK ||
+        (st = upload_array(*m, lcuts[k].gseg, &v.gseg)) != ATLAS_OK ||
+        (st = upload_array(*m, lcuts[k].seg_pos, &v.seg_pos)) != ATLAS_OK ||
+        (st = upload_array(*m, lcuts[k].grefs, &v.grefs)) != ATLAS_OK ||
+        (st = upload_array(*m, lcuts[k].orefs, &v.orefs)) != ATLAS_OK) {
+      delete m;
+      return st;
+    }
+    v.fmax = lcuts[k].fmax;
+    v.gmax = lcuts[k].gmax;
+    v.pmax = lcuts[k].pmax;
+    v.rings = lcuts[k].rings;
+    v.parts = lshapes[k].first;
+    v.bands = lshapes[k].second;
+    v.ntiles = (int32_t)lcuts[k].tile_seg.size() - 1;
   }
   std::vector<PosRec> pos(V);
   for (int64_t p = 0; p < V; ++p) {

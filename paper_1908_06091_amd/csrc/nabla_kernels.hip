@@ -1318,9 +1318,9 @@ __global__ void __launch_bounds__(1024) k_sweepv(DevMesh m, const T *__restrict_
 // ---------------------------------------------------------------------------
 // Per position: one 16-byte word of references ({own row | n << 16 | flags,
 // rows 0 and 1, rows 2 and 3, rows 4 and 5}, one set for each cut of the
-// tiles) and a packed record of 16-byte words, {node, 0, alpha}, {beta
-// (scalar inputs) or cos(lat), 0}, S[6] / 2, and for vector inputs the
-// neighbours' cos(lat).
+// tiles) and a packed record of 16-byte words: for scalar inputs {node, 0,
+// alpha}, {beta, cos(lat)}, S[6] / 2; for vector inputs cos(lat) in beta's
+// place and the neighbours' cos(lat) at the end.
 constexpr int kSgeoWordsS = 8, kSgeoWordsV = 11;
 // Elements per lane: at most what 128 registers hold (one workgroup of up to
 // 1024 threads per compute unit).
@@ -1347,6 +1347,107 @@ __device__ __forceinline__ void lds_dma16(const i32x4 &rsrc, void *lds_wave_base
   __builtin_amdgcn_raw_ptr_buffer_load_lds(
       r, (__attribute__((address_space(3))) void *)lds_wave_base, 16, voff, 0, 0, 0);
 }
+
+// A piece's table of runs, entry q in lane q of every wavefront: read once,
+// then a step's entry comes by v_readlane.  (Read by scalar loads when a step
+// needs them, the entries of most steps came from beyond the L2, a round trip
+// on the path of every load and every step.)  Entries from 64 on, of bands
+// taller than the library's, are read when needed.
+__device__ __forceinline__ int4 cst_int4(const int4 *p, size_t i) {
+  const ATLASX_CST int *d = cst(reinterpret_cast<const int *>(p));
+  return make_int4(d[4 * i], d[4 * i + 1], d[4 * i + 2], d[4 * i + 3]);
+}
+__device__ __forceinline__ int2 cst_int2(const int2 *p, size_t i) {
+  const ATLASX_CST int *d = cst(reinterpret_cast<const int *>(p));
+  return make_int2(d[2 * i], d[2 * i + 1]);
+}
+struct RunTable {
+  const int4 *src;
+  int4 v;
+  __device__ __forceinline__ RunTable(const int4 *p, int n, int lane)
+      : src(p), v(p[min(lane, n - 1)]) {}
+  __device__ __forceinline__ int4 operator()(int q) const {
+    if (q >= 64) return cst_int4(src, q);
+    return make_int4(__builtin_amdgcn_readlane(v.x, q), __builtin_amdgcn_readlane(v.y, q),
+                     __builtin_amdgcn_readlane(v.z, q), __builtin_amdgcn_readlane(v.w, q));
+  }
+};
+struct PosTable {
+  const int2 *src;
+  int2 v;
+  __device__ __forceinline__ PosTable(const int2 *p, int n, int lane)
+      : src(p), v(p[min(lane, n - 1)]) {}
+  __device__ __forceinline__ int2 operator()(int q) const {
+    if (q >= 64) return cst_int2(src, q);
+    return make_int2(__builtin_amdgcn_readlane(v.x, q), __builtin_amdgcn_readlane(v.y, q));
+  }
+};
+
+// The loads of a run's columns by one wavefront of a producer group of `nwv`:
+// its i-th load instruction moves 64 items (node t of the run, vector k of
+// the chunk) whose offsets from the run's first column are the same for
+// every run, so they are computed once; a load then costs a few scalar
+// instructions.  (With the offsets recomputed per load, issuing a step's
+// loads took as long as their latency: O1280, 137 levels, FP64 divergence
+// 5.12 -> 4.87 ms, gradient 4.59 -> 4.47, FP32 gradient 2.47 -> 2.36; the
+// fused Laplacian's loads alone 4.87 -> 3.95.)  The sweep's ring slots are at
+// most 32 KB, 16 load instructions for each of two wavefronts; the fused
+// Laplacian's plan keeps to one wavefront's.
+constexpr int kRunLoads = 16;
+static_assert(kSweepwSlots * kRunLoads * 64 * 16 * kSweepwGroupWaves >= 160 * 1024,
+              "the loads of a run fill the largest ring slot");
+struct RunLoader {
+  int rel[kRunLoads];
+  int w, nwv, lane, nvc;
+  uint32_t col_bytes;
+  // (the last vector of a column ends with the column)
+  __device__ __forceinline__ RunLoader(int w, int nwv, int lane, int nvc, int v0,
+                                       uint32_t col_bytes)
+      : w(w), nwv(nwv), lane(lane), nvc(nvc), col_bytes(col_bytes) {
+    const int i0 = w * 64 + lane, di = nwv * 64;
+    int t = i0 / nvc, k = i0 - t * nvc;
+    const int dt = di / nvc, dk = di - dt * nvc;
+#pragma unroll
+    for (int i = 0; i < kRunLoads; ++i) {
+      rel[i] = t * (int)col_bytes + min(16 * (v0 + k), (int)col_bytes - 16);
+      t += dt;
+      k += dk;
+      if (k >= nvc) {
+        k -= nvc;
+        ++t;
+      }
+    }
+  }
+  // run f = {ring offset, ring size, first, length} of the field at `base`
+  __device__ __forceinline__ void load(const unsigned char *base, const int4 &f,
+                                       i32x4 *slot) const {
+    const int nitems = f.w * nvc;
+    const bool wraps = f.z + f.w > f.y;
+    const unsigned char *ring = base + (size_t)f.x * col_bytes;
+    const uint32_t start = (uint32_t)f.z * col_bytes, size = (uint32_t)f.y * col_bytes;
+    const i32x4 rs = make_rsrc(wraps ? ring : ring + start, wraps ? size : (uint32_t)f.w * col_bytes);
+#pragma unroll
+    for (int i = 0; i < kRunLoads; ++i) {
+      const int b = w + i * nwv;
+      if (b * 64 >= nitems) break;
+      int off = rel[i];
+      if (wraps) {  // past the parallel's end: on from its first column
+        const uint32_t o = (uint32_t)off + start;
+        off = (int)min(o, o - size);
+      }
+      // lanes past the run's last item stay off: the words behind it belong
+      // to the next slot
+      if ((b + 1) * 64 <= nitems || b * 64 + lane < nitems) lds_dma16(rs, slot + b * 64, off);
+    }
+  }
+  // `words` contiguous 16-byte words
+  __device__ __forceinline__ void copy(const int4 *src, i32x4 *dst, int words) const {
+    const i32x4 rs = make_rsrc(src, (uint32_t)words * 16u);
+    for (int b = w; b * 64 < words; b += nwv)
+      if ((b + 1) * 64 <= words || b * 64 + lane < words)
+        lds_dma16(rs, dst + b * 64, (b * 64 + lane) * 16);
+  }
+};
 
 // DC (OP = OP_DIV only): the curl of the same field as well, into out2,
 // from the same loads; each output bitwise that of its own operator.
@@ -1389,14 +1490,12 @@ __global__ void __launch_bounds__(1024) k_sweepw(SweepView m, const int4 *__rest
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = blockDim.x >> 6;
   const int lane = threadIdx.x & 63;
-  const int *segi = reinterpret_cast<const int *>(m.seg);
-  const int *segp = reinterpret_cast<const int *>(m.seg_pos);
-  auto run_lo = [&](int q) { return cst(segp)[2 * (s0 + q)]; };
-  auto run_hi = [&](int q) { return cst(segp)[2 * (s0 + q) + 1]; };
+  const PosTable own(m.seg_pos + s0, nseg, lane);
   // first and last parallel with positions of this tile
   int qa = nseg, qb = -1;
   for (int q = 0; q < nseg; ++q) {
-    if (run_hi(q) > run_lo(q)) {
+    const int2 sp = own(q);
+    if (sp.y > sp.x) {
       qa = min(qa, q);
       qb = q;
     }
@@ -1406,61 +1505,30 @@ __global__ void __launch_bounds__(1024) k_sweepw(SweepView m, const int4 *__rest
   if (wave < NPW) {
     // ---- producers: group grp loads the runs r with r mod groups = grp ----
     const int grp = wave / kSweepwGroupWaves, gwave = wave - grp * kSweepwGroupWaves;
-    const V *vin = reinterpret_cast<const V *>(in);
-    // columns and records of run q into the ring slots of q, the waves of
-    // the calling group (or, with nwv = NPW, all producers) sharing the
-    // load instructions; lanes past the run's last item are off (the words
-    // behind it belong to the next slot)
-    auto load = [&](int q, int w, int nwv) {
-      {
-        const int rb = cst(segi)[4 * (s0 + q)], nx = cst(segi)[4 * (s0 + q) + 1];
-        const int lo = cst(segi)[4 * (s0 + q) + 2], len = cst(segi)[4 * (s0 + q) + 3];
-        const i32x4 rs = make_rsrc(vin + (size_t)rb * L, (uint32_t)nx * col_bytes);
-        const int nitems = len * nvc;
-        i32x4 *slot = fbuf + (q % kSweepwSlots) * segmax * nvc;
-        // item i = (node t of the run) x (vector k); t and k advance by
-        // whole strides of the calling waves' load instructions
-        const int i0 = w * 64 + lane, di = nwv * 64;
-        int t = i0 / nvc, k = i0 - t * nvc;
-        const int dt = di / nvc, dk = di - dt * nvc;
-        for (int b = w; b * 64 < nitems; b += nwv) {
-          if (b * 64 + lane < nitems) {
-            int ii = lo + t;
-            if (ii >= nx) ii -= nx;
-            lds_dma16(rs, slot + b * 64,
-                      ii * (int)col_bytes + min(NV * (v0 + k), nlev - NV) * (int)sizeof(V));
-          }
-          t += dt;
-          k += dk;
-          if (k >= nvc) {
-            k -= nvc;
-            ++t;
-          }
-        }
-      }
-      {
-        const int plo = run_lo(q), n = run_hi(q) - plo;
-        auto copy = [&](const int4 *src, i32x4 *dst, int words) {
-          const i32x4 rs = make_rsrc(src, (uint32_t)words * 16u);
-          for (int b = w; b * 64 < words; b += nwv)
-            if (b * 64 + lane < words) lds_dma16(rs, dst + b * 64, (b * 64 + lane) * 16);
-        };
-        copy(m.refs + plo, rbuf + (q % kSweepwGeoSlots) * m.pmax, n);
-        copy(geo + (size_t)plo * GW, gbuf + (q % kSweepwGeoSlots) * gcap, n * GW);
-      }
+    const unsigned char *field = reinterpret_cast<const unsigned char *>(in);
+    const RunTable runs(m.seg + s0, nseg, lane);
+    const RunLoader ld(gwave, kSweepwGroupWaves, lane, nvc, v0, col_bytes);
+    // columns, references and records of run q into the ring slots of q
+    auto load = [&](int q) {
+      ld.load(field, runs(q), fbuf + (q % kSweepwSlots) * segmax * nvc);
+      const int2 sp = own(q);
+      const int slot = q % kSweepwGeoSlots, n = sp.y - sp.x;
+      ld.copy(m.refs + sp.x, rbuf + slot * m.pmax, n);
+      ld.copy(geo + (size_t)sp.x * GW, gbuf + slot * gcap, n * GW);
     };
-    // prologue: runs qa-1 .. qa+1 by every producer (waited), runs qa+2 ..
-    // qa+lead-1 by their groups (run r waited at the end of step r-2)
-    for (int q = max(0, qa - 1); q <= min(nseg - 1, qa + 1); ++q) load(q, wave, NPW);
+    // prologue: runs qa-1 .. qa+1 (waited), then qa+2 .. qa+lead-1, by their
+    // groups (run r is waited for at the end of step r-2)
+    for (int q = max(0, qa - 1); q <= min(nseg - 1, qa + 1); ++q)
+      if (q % kSweepwGroups == grp) load(q);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     for (int r = qa + 2; r < min(nseg, qa + kSweepwLead); ++r)
-      if (r % kSweepwGroups == grp) load(r, gwave, kSweepwGroupWaves);
+      if (r % kSweepwGroups == grp) load(r);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     for (int q = qa; q <= qb; ++q) {
       if (q + kSweepwLead < nseg && (q + kSweepwLead) % kSweepwGroups == grp)
-        load(q + kSweepwLead, gwave, kSweepwGroupWaves);
+        load(q + kSweepwLead);
       // run q+2 (issued lead-2 steps ago by its group, which has issued
       // nothing since) is in LDS before step q+1 reads it
       if ((q + 2) % kSweepwGroups == grp) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1593,7 +1661,8 @@ __global__ void __launch_bounds__(1024) k_sweepw(SweepView m, const int4 *__rest
     }
   };
   for (int q = qa; q <= qb; ++q) {
-    const int plo = run_lo(q), n = run_hi(q) - plo;
+    const int2 sp = own(q);
+    const int n = sp.y - sp.x;
     const i32x4 *rq = rbuf + (q % kSweepwGeoSlots) * m.pmax;
     const i32x4 *gq = gbuf + (q % kSweepwGeoSlots) * gcap;
     for (int t = NPN * cw + sub; t < n; t += NPN * ncw) {
@@ -1680,15 +1749,6 @@ __device__ __forceinline__ void grad_add_half(Pol<float, OP_GRAD>::St &, float, 
 __device__ __forceinline__ void div_init_w(PolDC32<OP_DIV>::St &, const v2f &) {}
 __device__ __forceinline__ void div_add_half_w(PolDC32<OP_DIV>::St &, const v2f &,
                                                const double2 &) {}
-
-__device__ __forceinline__ int4 cst_int4(const int4 *p, size_t i) {
-  const ATLASX_CST int *d = cst(reinterpret_cast<const int *>(p));
-  return make_int4(d[4 * i], d[4 * i + 1], d[4 * i + 2], d[4 * i + 3]);
-}
-__device__ __forceinline__ int2 cst_int2(const int2 *p, size_t i) {
-  const ATLASX_CST int *d = cst(reinterpret_cast<const int *>(p));
-  return make_int2(d[2 * i], d[2 * i + 1]);
-}
 
 template <class T, int NV, int EPT, int NL>
 __global__ void __launch_bounds__(1024) k_lsweep(DevMesh m, const T *__restrict__ in,
@@ -2058,250 +2118,131 @@ __global__ void __launch_bounds__(1024) k_lsweep(DevMesh m, const T *__restrict_
 // ---------------------------------------------------------------------------
 // Fused Laplacian, wave-specialised: the register-staged kernel above waits
 // at every parallel for the loads it issued one parallel earlier, one
-// memory round trip per step.  Here two producer groups of two wavefronts
-// load the field runs and packed geometry straight into LDS (16-byte DMA
-// loads, as in the wave-specialised sweep) two steps ahead, and never
-// store, so each waits for exactly its own loads; the consumer wavefronts
-// only compute and store.
+// memory round trip per step.  Here, as in the wave-specialised sweep, two
+// producer groups of two wavefronts load straight into LDS two steps ahead
+// and never store, and the consumer wavefronts only compute and store.
 //
-// Step q forms the gradients of the g-run of parallel q (field runs q-1,
-// q, q+1) into gradient slot q mod 3, then -- after a workgroup barrier --
-// the Laplacian of the own positions of parallel q-1 from the gradients of
-// parallels q-2, q-1, q.  Load set k = {field run k+1, geometry of step k
-// (g records of parallel k, own records of parallel k-1)} is issued at step
-// k-2 by group k mod 2 and waited for by that group at the end of step
-// k-1: field ring 5 slots, geometry ring 3, gradient ring 3.  With FS = 4
-// field slots the field run of set k is issued after the mid-step barrier
-// of step k-2 instead (the gradients of that step have then finished
-// reading the slot it takes), one step before it is read rather than one
-// and a half: the ring holds one parallel of columns less, so a longer
-// level chunk fits in LDS.  References in the packed records are resolved
-// once the set has landed, into LDS offsets.
+// Step q forms the gradients of the g-run of parallel q (from field runs
+// q-1, q, q+1) into gradient slot q mod 4 and the Laplacian of the own
+// positions of parallel q-2 (from gradient runs q-3 .. q-1, finished in
+// earlier steps), so the two share the wavefronts with one barrier a step.
+// Load set k = {field run k+1, records of the g-run k, its references, the
+// references of the own positions of parallel k-2} is issued at step k-2 by
+// group k mod 2 and waited for by that group at the end of step k-1: field
+// and record rings of five slots, reference rings of three.  A position's
+// record serves its gradient and, two steps later, its divergence.
+// References are rows of the rings (a parallel's slot is known when the mesh
+// is built), so nothing is resolved at run time.  Lanes and elements as in
+// the sweep; FP64 keeps the second gradient component multiplied by
+// cos(lat) (the divergence's b = v cos(lat), formed once per node), FP32
+// keeps the rounded components and the nodes' cos(lat) beside them.
+//
+// O1280, 137 levels, against one barrier per phase, references resolved by
+// the producers and selects on every row: FP64 8.26 -> 7.20 ms, FP32 6.20 ->
+// 4.85; 10 levels, FP64, 1.83 -> 1.03.  With no gradients it takes 5.6 ms,
+// with no divergences 5.6, with neither (loads and barriers) 3.95: the bound
+// is the LDS, which serves 35 reads of a column's elements and ten of a
+// record's words for each wavefront of positions and each phase.
 // ---------------------------------------------------------------------------
-constexpr int kLswFSlots = 5, kLswGSlots = 3, kLswGeoSlots = 3;
-constexpr int kLswProducers = 4;  // two groups of two wavefronts
+constexpr int kLswGroupWaves = 1, kLswProducers = 2 * kLswGroupWaves;
+constexpr int kLswBlock = 768;  // at most (three wavefronts per SIMD: 168 registers)
+constexpr int kLswRecSlots = 5, kLswRefSlots = 3;
+constexpr int kLswMaxNe = 5;
 
-template <class T, int NV, int FS = kLswFSlots>
-__global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict__ in,
-                                                  T *__restrict__ out, int nlev, int vpc,
-                                                  int ntiles, int per_xcd, int lpn, int fcap,
-                                                  int gcap, int ocap) {
+template <class T, int LPN, int NE>
+__global__ void __launch_bounds__(kLswBlock) k_lsweepw(LaplView m, const int4 *__restrict__ geo,
+                                                  const T *__restrict__ in, T *__restrict__ out,
+                                                  int nlev, int vpc, int per_xcd) {
   using PG = Pol<T, OP_GRAD>;
   using PD = Pol<T, OP_DIV>;
-  using LF = LaneVec<T, NV>;
-  using RF = typename LF::raw;
-  using GV = typename PD::V;
-  using LG = LaneVec<GV, NV>;
-  using RG = typename LG::raw;
-  static_assert(sizeof(RF) == 16, "wave-specialised fused Laplacian: 16-byte lane vectors");
-  static_assert(sizeof(RG) == 2 * sizeof(RF), "gradient lane vector = two field lane vectors");
-  static_assert(FS == 4 || FS == 5, "field ring of four or five slots");
-  constexpr int G = 6;
+  using GV = typename PD::V;                  // gradient of one level
   constexpr bool F64 = sizeof(T) == 8;
-  constexpr int LGW = F64 ? kLGeoWords64 : kLGeoWords;
+  constexpr int NV = 16 / (int)sizeof(T);     // levels per vector
+  constexpr int EL = 8 / (int)sizeof(T);      // levels per element
+  constexpr int NPN = 64 / LPN;               // positions per wavefront
+  constexpr int GW = kSgeoWordsS;
+  struct __align__(8) FElem { T v[EL]; };
+  struct __align__(16) GElem { GV v[EL]; };
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int gmax = m.l2_gmax;
-  const int gstride = 2 * gmax * vpc;   // gradient slot (field lane vectors)
-  const int geo_stride = gcap + ocap;   // geometry slot (16-byte words)
-  RF *fbuf = reinterpret_cast<RF *>(smem_raw);                         // [FS][fcap]
-  RF *gbuf = fbuf + FS * fcap;                                         // [3][gmax][2][vpc]
-  i32x4 *geo = reinterpret_cast<i32x4 *>(gbuf + kLswGSlots * gstride);  // [3][gcap + ocap]
+  const int fmax = m.fmax, gmax = m.gmax, pmax = m.pmax;
+  i32x4 *fbuf = reinterpret_cast<i32x4 *>(smem_raw);   // [field slots][fmax][nvc]
+  i32x4 *gbuf = fbuf + kLswFieldSlots * fmax * vpc;     // [gradient slots][gmax][2 nvc]
+  i32x4 *recs = gbuf + kLswGradSlots * gmax * 2 * vpc;  // [record slots][gmax][GW]
+  i32x4 *gref = recs + kLswRecSlots * gmax * GW;        // [reference slots][gmax]
+  i32x4 *oref = gref + kLswRefSlots * gmax;             // [reference slots][pmax]
+  double *cosb = reinterpret_cast<double *>(oref + kLswRefSlots * pmax);  // FP32: [4][gmax]
   const int u = xcd_tile(blockIdx.x, per_xcd);
   const int nvec = (nlev + NV - 1) / NV;
   const int nchunk = (nvec + vpc - 1) / vpc;
   const int tile = u / nchunk;
   const int c = u - tile * nchunk;
-  if (tile >= ntiles) return;
+  if (tile >= m.ntiles) return;
   const int v0 = c * vpc;
   if (v0 >= nvec) return;
   const int nvc = min(vpc, nvec - v0);
-  const int k0 = cst(m.l2_tile_seg)[tile];
-  const int W = cst(m.l2_tile_seg)[tile + 1] - k0;
+  const int k0 = cst(m.tile_seg)[tile];
+  const int W = cst(m.tile_seg)[tile + 1] - k0;
   const size_t L = (size_t)nlev;
   const uint32_t col_bytes = (uint32_t)(L * sizeof(T));
   const int nw = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  auto first = [&](int k) { return min(NV * (v0 + k), nlev - NV); };
+  const RunTable gruns(m.gseg + k0, W, lane);  // {first, length, first reference, 0}
+  const PosTable positions(m.seg_pos + k0, W, lane);
+  auto glen = [&](int q) { return q < W ? gruns(q).y : 0; };
+  auto own = [&](int q) { return q >= 0 && q < W ? positions(q) : make_int2(0, 0); };
+  // first parallel with gradients, last with own positions
+  int qa = W, qb = -1;
+  for (int q = 0; q < W; ++q) {
+    if (glen(q) > 0) qa = min(qa, q);
+    const int2 sp = own(q);
+    if (sp.y > sp.x) qb = q;
+  }
+  if (qb < 0) return;
 
   if (wave < kLswProducers) {
-    // ---- producers: waves 0, 1 form group 0 and waves 2, 3 group 1; the
-    // even wave of a group loads and resolves geometry, the odd one loads
-    // field runs, so every wave waits only for the loads it issued ---------
-    const int grp = wave >> 1;
-    const bool geo_wave = (wave & 1) == 0;
-    // field run q into slot q mod FS: item i = (node t of the run) x (lane
-    // vector kk); t and kk advance by whole load instructions
+    const int grp = wave / kLswGroupWaves, gwave = wave % kLswGroupWaves;
+    const unsigned char *field = reinterpret_cast<const unsigned char *>(in);
+    const RunTable fruns(m.fseg + k0, W, lane);  // {ring offset, ring size, first, length}
+    const RunLoader ld(gwave, kLswGroupWaves, lane, nvc, v0, col_bytes);
     auto load_f = [&](int q) {
-      if (q < 0 || q >= W) return;
-      const int4 f = cst_int4(m.l2_fseg, k0 + q);  // {ring offset, ring size, first, length}
-      const i32x4 rs = make_rsrc(in + (size_t)f.x * L, (uint32_t)f.y * col_bytes);
-      const int nitems = f.w * nvc;
-      RF *slot = fbuf + (q % FS) * fcap;
-      int t = lane / nvc, kk = lane - t * nvc;
-      const int dt = 64 / nvc, dk = 64 - dt * nvc;
-      for (int b = 0; b * 64 < nitems; ++b) {
-        int off = kBufOff;
-        if (b * 64 + lane < nitems) {
-          int ii = f.z + t;
-          if (ii >= f.y) ii -= f.y;  // the run wraps round the parallel
-          off = ii * (int)col_bytes + first(kk) * (int)sizeof(T);
-        }
-        lds_dma16(rs, slot + b * 64, off);
-        t += dt;
-        kk += dk;
-        if (kk >= nvc) {
-          kk -= nvc;
-          ++t;
-        }
-      }
+      if (q >= 0 && q < W) ld.load(field, fruns(q), fbuf + (q % kLswFieldSlots) * fmax * nvc);
     };
-    // geometry of step k: g records of parallel k, own records of k - 1
+    // records and references of set k
     auto load_g = [&](int k) {
-      if (k < 0 || k > W) return;
-      i32x4 *gs = geo + (k % kLswGeoSlots) * geo_stride;
       if (k < W) {
-        const int4 g = cst_int4(m.l2_gseg, k0 + k);  // {g first, g length, first g record, 0}
-        const i32x4 rs = make_rsrc(m.l2_ggeo + (size_t)g.z * kGGeoWords,
-                                   (uint32_t)g.y * kGGeoWords * 16u);
-        const int nitems = g.y * kGGeoWords;
-        for (int b = 0; b * 64 < nitems; ++b) {
-          const int i = b * 64 + lane;
-          lds_dma16(rs, gs + b * 64, i < nitems ? i * 16 : kBufOff);
-        }
+        const int4 f = fruns(k), g = gruns(k);
+        i32x4 *slot = recs + (k % kLswRecSlots) * gmax * GW;
+        const int4 *first = geo + (size_t)(f.x + g.x) * GW;
+        const int head = min(g.y, f.y - g.x);  // the run may wrap round the parallel
+        ld.copy(first, slot, head * GW);
+        if (head < g.y) ld.copy(geo + (size_t)f.x * GW, slot + head * GW, (g.y - head) * GW);
+        ld.copy(m.grefs + g.z, gref + (k % kLswRefSlots) * gmax, g.y);
       }
-      if (k >= 1) {
-        const int2 sp = cst_int2(m.l2_seg_pos, k0 + k - 1);
-        const int np = sp.y - sp.x;
-        const i32x4 rs = make_rsrc(m.l2_lgeo + (size_t)sp.x * kLGeoWords,
-                                   (uint32_t)np * kLGeoWords * 16u);
-        const int nitems = np * LGW;
-        int t = lane / LGW, wd = lane - t * LGW;
-        constexpr int dt = 64 / LGW, dw = 64 - dt * LGW;
-        for (int b = 0; b * 64 < nitems; ++b) {
-          lds_dma16(rs, gs + gcap + b * 64,
-                    b * 64 + lane < nitems ? (t * kLGeoWords + wd) * 16 : kBufOff);
-          t += dt;
-          wd += dw;
-          if (wd >= LGW) {
-            wd -= LGW;
-            ++t;
-          }
-        }
-      }
+      const int2 sp = own(k - 2);
+      ld.copy(m.orefs + sp.x, oref + (k % kLswRefSlots) * pmax, sp.y - sp.x);
     };
-    // The reference words of geometry set k (words 6, 7, 9 of each record:
-    // one g record and one own record per lane) also go to registers with
-    // the set's loads; once the set has landed they become LDS element
-    // offsets for the step that reads them (field-run references of the g
-    // records of parallel k: runs k-1, k, k+1; gradient-run references of
-    // the own records of parallel k-1: runs k-2, k-1, k; pole flags kept)
-    // and overwrite the copied words.
-    i32x4 gr6 = {}, gr7 = {}, gr9 = {}, or6 = {}, or7 = {}, or9 = {};
-    auto load_refs = [&](int k) {
-      if (k < 0 || k > W) return;
-      if (k < W) {
-        const int4 g = cst_int4(m.l2_gseg, k0 + k);
-        const i32x4 rs = make_rsrc(m.l2_ggeo + (size_t)g.z * kGGeoWords,
-                                   (uint32_t)g.y * kGGeoWords * 16u);
-        const int o = lane < g.y ? lane * kGGeoWords * 16 : kBufOff;
-        gr6 = buf_load<i32x4>(rs, o + 6 * 16);
-        gr7 = buf_load<i32x4>(rs, o + 7 * 16);
-        gr9 = buf_load<i32x4>(rs, o + 9 * 16);
-      }
-      if (k >= 1) {
-        const int2 sp = cst_int2(m.l2_seg_pos, k0 + k - 1);
-        const i32x4 rs = make_rsrc(m.l2_lgeo + (size_t)sp.x * kLGeoWords,
-                                   (uint32_t)(sp.y - sp.x) * kLGeoWords * 16u);
-        const int o = lane < sp.y - sp.x ? lane * kLGeoWords * 16 : kBufOff;
-        or6 = buf_load<i32x4>(rs, o + 6 * 16);
-        or7 = buf_load<i32x4>(rs, o + 7 * 16);
-        or9 = buf_load<i32x4>(rs, o + 9 * 16);
-      }
-    };
-    auto resolve = [&](int k) {
-      // the loaded words are used from here on only: no computation on them
-      // may move up to the loads, where it would wait for the whole set
-      asm volatile("" : "+v"(gr6), "+v"(gr7), "+v"(gr9), "+v"(or6), "+v"(or7), "+v"(or9));
-      if (k < 0 || k > W) return;
-      i32x4 *gs = geo + (k % kLswGeoSlots) * geo_stride;
-      if (k < W) {
-        const int b0 = ((k + FS - 1) % FS) * fcap;
-        const int b1 = (k % FS) * fcap, b2 = ((k + 1) % FS) * fcap;
-        auto rf = [&](int v) {
-          const int l = v & ~kLrefPole, dq = (l >> 16) & 3;
-          return (v & kLrefPole) | ((dq == 0 ? b0 : dq == 1 ? b1 : b2) + (l & 0xffff) * nvc);
-        };
-        if (lane < cst_int4(m.l2_gseg, k0 + k).y) {
-          i32x4 *r = gs + lane * kGGeoWords;
-          i32x4 a = gr6, b = gr7, c = gr9;
-          a.x = rf(a.x); a.y = rf(a.y); a.z = rf(a.z); a.w = rf(a.w);
-          b.x = rf(b.x); b.y = rf(b.y); b.z = rf(b.z); b.w = rf(b.w);
-          c.x = b1 + c.x * nvc;
-          r[6] = a; r[7] = b; r[9] = c;
-        }
-      }
-      if (k >= 1) {
-        const int b0 = ((k + 1) % kLswGSlots) * gstride;
-        const int b1 = ((k + 2) % kLswGSlots) * gstride, b2 = (k % kLswGSlots) * gstride;
-        auto rg = [&](int v) {
-          const int l = v & ~kLrefPole, dq = (l >> 16) & 3;
-          return (v & kLrefPole) | ((dq == 0 ? b0 : dq == 1 ? b1 : b2) + (l & 0xffff) * 2 * vpc);
-        };
-        const int2 sp = cst_int2(m.l2_seg_pos, k0 + k - 1);
-        if (lane < sp.y - sp.x) {
-          i32x4 *r = gs + gcap + lane * LGW;
-          i32x4 a = or6, b = or7, c = or9;
-          a.x = rg(a.x); a.y = rg(a.y); a.z = rg(a.z); a.w = rg(a.w);
-          b.x = rg(b.x); b.y = rg(b.y); b.z = rg(b.z); b.w = rg(b.w);
-          c.z = b1 + c.z * 2 * vpc;
-          r[6] = a; r[7] = b; r[9] = c;
-        }
-      }
-    };
-    // prologue: group 0 takes geometry 0 and field runs 0, 1; group 1
-    // geometry 1 and field run 2; each geometry wave resolves its own set
-    if (geo_wave) {
-      load_refs(grp);  // first: no DMA of the set may wait on these registers
-      load_g(grp);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      resolve(grp);
-    } else {
-      if (grp == 0) {
-        load_f(0);
-        load_f(1);
-      } else {
-        load_f(2);
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // prologue: the runs before set qa, and set qa (waited), then set
+    // qa + 1, each by its group
+    for (int q = qa - 1; q <= qa + 1; ++q)
+      if ((q & 1) == grp) load_f(q);
+    if ((qa & 1) == grp) load_g(qa);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (((qa + 1) & 1) == grp) {
+      load_f(qa + 2);
+      load_g(qa + 1);
     }
-    // the resolved words are in LDS before the consumers pass the barrier
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    for (int q = 0; q <= W; ++q) {
-      // set q + 2 (field run q + 3, geometry q + 2) by group q mod 2
+    for (int q = qa; q <= qb + 2; ++q) {
       if ((q & 1) == grp) {
-        if (geo_wave) {
-          load_refs(q + 2);
-          load_g(q + 2);
-        } else if (FS == 5) {
-          load_f(q + 3);
-        }
+        load_f(q + 3);
+        load_g(q + 2);
       }
+      // set q + 1 lands before step q + 1
+      if (((q + 1) & 1) == grp) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();  // between the consumers' two phases
-      asm volatile("" ::: "memory");
-      // four slots: field run q + 3 takes the slot of run q - 1, which the
-      // gradients of step q (runs q - 1 .. q + 1) have finished reading
-      if (FS == 4 && (q & 1) == grp && !geo_wave) load_f(q + 3);
-      // set q + 1 (issued at step q - 1 by this group; sets 0 and 1 came
-      // with the prologue) lands, and is resolved, before step q + 1
-      if (((q + 1) & 1) == grp && q >= 1) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (geo_wave) resolve(q + 1);
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     }
@@ -2314,182 +2255,213 @@ __global__ void __launch_bounds__(1024) k_lsweepw(DevMesh m, const T *__restrict
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   const int cw = wave - kLswProducers, ncw = nw - kLswProducers;
-  const int npw = 64 / lpn;  // nodes per wavefront, lpn lanes each
-  const int sub = lane / lpn;
-  const int hl = lane - sub * lpn;
-  const bool sub_on = sub < npw;
-  const int kc = min(hl, nvc - 1);  // lanes past the chunk read a valid entry
-  const bool lane_on = sub_on && hl < nvc;
-  auto gload = [&](int at) {
-    RG r;
-    __builtin_memcpy(&r, &gbuf[at], sizeof(RF));
-    __builtin_memcpy(reinterpret_cast<char *>(&r) + sizeof(RF), &gbuf[at + vpc], sizeof(RF));
-    return r;
+  const int sub = lane / LPN, hl = lane - sub * LPN;
+  const int nel = nvc * 2;  // elements in this chunk
+  const uint32_t frow = (uint32_t)nvc * 16u, grow = 2 * frow;
+  const unsigned char *fbase = reinterpret_cast<const unsigned char *>(fbuf) + hl * 8;
+  unsigned char *gbase = reinterpret_cast<unsigned char *>(gbuf) + hl * 16;
+  int off_g[NE];  // byte offset in the output row of element g
+#pragma unroll
+  for (int g = 0; g < NE; ++g) {
+    const int e = hl + g * LPN;
+    off_g[g] = (min(NV * (v0 + e / 2), nlev - NV) + EL * (e & 1)) * (int)sizeof(T);
+  }
+  auto rows_of = [](const i32x4 &r, uint32_t (&rw)[6]) {
+    rw[0] = (uint32_t)r.y & 0xffffu; rw[1] = (uint32_t)r.y >> 16;
+    rw[2] = (uint32_t)r.z & 0xffffu; rw[3] = (uint32_t)r.z >> 16;
+    rw[4] = (uint32_t)r.w & 0xffffu; rw[5] = (uint32_t)r.w >> 16;
   };
-  for (int q = 0; q <= W; ++q) {
-    const i32x4 *gq = geo + (q % kLswGeoSlots) * geo_stride;
-    // ---- gradients at the g-run of parallel q
-    if (q < W) {
-      RF *gout = gbuf + (q % kLswGSlots) * gstride;
-      const int glen = sub_on ? cst_int4(m.l2_gseg, k0 + q).y : 0;
-      for (int s = npw * cw + sub; s < glen; s += npw * ncw) {
-        const i32x4 *r = gq + s * kGGeoWords;
-        double2 S[G];  // halved normals (FP64), the normals (FP32)
-        int lr[8];
+  auto pair_of = [](const i32x4 &w, double &lo, double &hi) {
+    const int a[2] = {w.x, w.y}, b[2] = {w.z, w.w};
+    __builtin_memcpy(&lo, a, 8);
+    __builtin_memcpy(&hi, b, 8);
+  };
+  // FULL: six incidences, none a pole edge (see k_sweepw)
+  auto gradient = [&](const i32x4 *rec, const i32x4 &ref, int row, auto full_c) {
+    constexpr bool FULL = decltype(full_c)::value;
+    if constexpr (!FULL) asm volatile("" ::: "memory");
+    double al, be, cosg, pad;
+    pair_of(rec[0], pad, al);
+    pair_of(rec[1], be, cosg);
+    uint32_t rw[6];
+    rows_of(ref, rw);
+    typename PG::St st[NE][EL];
+    const unsigned char *self = fbase + __umul24((uint32_t)ref.x & 0xffffu, frow);
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
-          __builtin_memcpy(&S[j], &r[j], 16);
-          if constexpr (!F64) S[j] = make_double2(S[j].x + S[j].x, S[j].y + S[j].y);
-        }
-        {
-          const i32x4 a = r[6], b = r[7];
-          lr[0] = a.x; lr[1] = a.y; lr[2] = a.z; lr[3] = a.w;
-          lr[4] = b.x; lr[5] = b.y; lr[6] = b.z; lr[7] = b.w;
-        }
-        double al, be;
-        {
-          const i32x4 w8 = r[8];
-          const int a2[2] = {w8.x, w8.y}, b2[2] = {w8.z, w8.w};
-          __builtin_memcpy(&al, a2, 8);
-          __builtin_memcpy(&be, b2, 8);
-        }
-        const i32x4 w9 = r[9];
-        const int fself = w9.x, n = w9.y;
-        double cosg;
-        {
-          const int c2[2] = {w9.z, w9.w};
-          __builtin_memcpy(&cosg, c2, 8);
-        }
-        typename PG::St st[NV];
-        {
-          const RF xi = fbuf[fself + kc];
+    for (int g = 0; g < NE; ++g) {
+      const FElem x = *reinterpret_cast<const FElem *>(self + g * LPN * 8);
 #pragma unroll
-          for (int v = 0; v < NV; ++v) PG::init(st[v], LF::get(xi, v), 0.0);
-        }
-        RF xn[G];
+      for (int e = 0; e < EL; ++e) PG::init(st[g][e], x.v[e], 0.0);
+    }
+    FElem x[2][NE];
+    double2 S2[2];
+    auto read = [&](int j) {
+      pair_of(rec[2 + j], S2[j & 1].x, S2[j & 1].y);
+      const unsigned char *col = fbase + __umul24(rw[j], frow);
 #pragma unroll
-        for (int j = 0; j < G; ++j) xn[j] = fbuf[(lr[j] & ~kLrefPole) + kc];
+      for (int g = 0; g < NE; ++g)
+        x[j & 1][g] = *reinterpret_cast<const FElem *>(col + g * LPN * 8);
+    };
+    read(0);
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
-          const bool pole = (lr[j] & kLrefPole) != 0;
-          if (j < kMinRow) {  // present in every row, never the pole edge
+    for (int j = 0; j < 6; ++j) {
+      if (j < 5) read(j + 1);
+      const double2 Sh = S2[j & 1];
+      const bool pole = !FULL && j >= kMinRow && (ref.x & (kSgeoPole << j)) != 0;
+      const bool use = FULL || j < kMinRow || j < ((ref.x >> 16) & 7);
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-              if constexpr (F64) grad_add_half(st[v], LF::get(xn[j], v), S[j], false);
-              else PG::add(st[v], LF::get(xn[j], v), S[j], false, 0.0);
-            }
-            continue;
-          }
-          const bool use = j < n;
+      for (int g = 0; g < NE; ++g)
 #pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            typename PG::St tt = st[v];
-            if constexpr (F64) grad_add_half(tt, LF::get(xn[j], v), S[j], pole);
-            else PG::add(tt, LF::get(xn[j], v), S[j], pole, 0.0);
-            PG::keep(st[v], tt, use);
+        for (int e = 0; e < EL; ++e) {
+          if (FULL || j < kMinRow) {
+            PG::add_half(st[g][e], x[j & 1][g].v[e], Sh, false, 0.0);
+          } else {
+            typename PG::St tt = st[g][e];
+            PG::add_half(tt, x[j & 1][g].v[e], Sh, pole, 0.0);
+            PG::keep(st[g][e], tt, use);
           }
         }
-        RG g;
+      if constexpr (NE * EL >= 3) __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const typename PG::Out o = PG::result(st[v], al, be);
-          g.e[2 * v] = o.x;
-          if constexpr (F64) g.e[2 * v + 1] = o.y * cosg;  // v cos(lat), as the divergence forms it
-          else g.e[2 * v + 1] = o.y;
+    for (int g = 0; g < NE; ++g)
+#pragma unroll
+      for (int e = 0; e < EL; ++e) PG::settle(st[g][e]);
+    unsigned char *dst = gbase + __umul24((uint32_t)row, grow);
+#pragma unroll
+    for (int g = 0; g < NE; ++g)
+      if (hl + g * LPN < nel) {
+        GElem o;
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+          const typename PG::Out r = PG::result_half(st[g][e], al, be);
+          o.v[e].x = r.x;
+          if constexpr (F64) o.v[e].y = r.y * cosg;  // v cos(lat), as the divergence forms it
+          else o.v[e].y = r.y;
         }
-        if (lane_on) {
-          RF *d = gout + s * 2 * vpc + kc;
-          __builtin_memcpy(d, &g, sizeof(RF));
-          __builtin_memcpy(d + vpc, reinterpret_cast<const char *>(&g) + sizeof(RF), sizeof(RF));
+        *reinterpret_cast<GElem *>(dst + g * LPN * 16) = o;
+      }
+    if constexpr (!F64) {
+      if (hl == 0) cosb[row] = cosg;
+    }
+  };
+  auto divergence = [&](const i32x4 *rec, const i32x4 &ref, auto full_c) {
+    constexpr bool FULL = decltype(full_c)::value;
+    if constexpr (!FULL) asm volatile("" ::: "memory");
+    const i32x4 w0 = rec[0];
+    double al, be, ci, pad;
+    pair_of(w0, pad, al);
+    pair_of(rec[1], be, ci);
+    uint32_t rw[6];
+    rows_of(ref, rw);
+    typename PD::St st[NE][EL];
+    const unsigned char *self = gbase + __umul24((uint32_t)ref.x & 0xffffu, grow);
+#pragma unroll
+    for (int g = 0; g < NE; ++g) {
+      const GElem x = *reinterpret_cast<const GElem *>(self + g * LPN * 16);
+#pragma unroll
+      for (int e = 0; e < EL; ++e) {
+        if constexpr (F64) div_init_w(st[g][e], x.v[e]);
+        else PD::init(st[g][e], x.v[e], ci);
+      }
+    }
+    GElem x[2][NE];
+    double2 S2[2];
+    double cn2[2] = {0.0, 0.0};
+    auto read = [&](int j) {
+      pair_of(rec[2 + j], S2[j & 1].x, S2[j & 1].y);
+      if constexpr (!F64) cn2[j & 1] = cosb[rw[j]];
+      const unsigned char *col = gbase + __umul24(rw[j], grow);
+#pragma unroll
+      for (int g = 0; g < NE; ++g)
+        x[j & 1][g] = *reinterpret_cast<const GElem *>(col + g * LPN * 16);
+    };
+    read(0);
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      if (j < 5) read(j + 1);
+      const double2 Sh = S2[j & 1];
+      const double cn = cn2[j & 1];
+      const bool use = FULL || j < kMinRow ||
+                       (j < ((ref.x >> 16) & 7) && (ref.x & (kSgeoPole << j)) == 0);
+#pragma unroll
+      for (int g = 0; g < NE; ++g)
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+          typename PD::St tt = st[g][e];
+          if constexpr (F64) div_add_half_w(tt, x[j & 1][g].v[e], Sh);
+          else PD::add_half(tt, x[j & 1][g].v[e], Sh, false, cn);
+          if (FULL || j < kMinRow) st[g][e] = tt;
+          else PD::keep(st[g][e], tt, use);
+        }
+      if constexpr (NE * EL >= 3) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int g = 0; g < NE; ++g)
+#pragma unroll
+      for (int e = 0; e < EL; ++e) PD::settle(st[g][e]);
+    unsigned char *dst = reinterpret_cast<unsigned char *>(out) + (size_t)(uint32_t)w0.x * col_bytes;
+#pragma unroll
+    for (int g = 0; g < NE; ++g)
+      if (hl + g * LPN < nel) {
+        FElem o;
+#pragma unroll
+        for (int e = 0; e < EL; ++e) o.v[e] = PD::result_half(st[g][e], al, 0.0);
+        __builtin_memcpy(dst + off_g[g], &o, sizeof(o));
+      }
+  };
+  for (int q = qa; q <= qb + 2; ++q) {
+    const int ng = glen(q);
+    const int2 sp = own(q - 2);
+    const int no = sp.y - sp.x;
+    const int tg = (ng + NPN - 1) / NPN, td = (no + NPN - 1) / NPN;
+    for (int t = cw; t < tg + td; t += ncw) {
+      if (t < tg) {
+        const int s = t * NPN + sub;
+        if (s < ng) {
+          const i32x4 ref = gref[(q % kLswRefSlots) * gmax + s];
+          const i32x4 *rec = recs + ((q % kLswRecSlots) * gmax + s) * GW;
+          const int row = (q % kLswGradSlots) * gmax + s;
+          if (__builtin_amdgcn_ballot_w64((ref.x & kSgeoFull) == 0) == 0)
+            gradient(rec, ref, row, std::true_type{});
+          else
+            gradient(rec, ref, row, std::false_type{});
+        }
+      } else {
+        const int i = (t - tg) * NPN + sub, r = q - 2;
+        if (i < no) {
+          const i32x4 ref = oref[(q % kLswRefSlots) * pmax + i];
+          // the own row's place in its run, in the record ring
+          const int s = (ref.x & 0xffff) + ((r % kLswRecSlots) - (r % kLswGradSlots)) * gmax;
+          const i32x4 *rec = recs + s * GW;
+          if (__builtin_amdgcn_ballot_w64((ref.x & kSgeoFull) == 0) == 0)
+            divergence(rec, ref, std::true_type{});
+          else
+            divergence(rec, ref, std::false_type{});
         }
       }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();  // the gradients of parallel q are in LDS
-    asm volatile("" ::: "memory");
-    // ---- Laplacian at the own positions of parallel q - 1
-    if (q >= 1) {
-      const int q1 = q - 1;
-      const int2 sp = cst_int2(m.l2_seg_pos, k0 + q1);
-      const int nown = sub_on ? sp.y - sp.x : 0;
-      for (int t = npw * cw + sub; t < nown; t += npw * ncw) {
-        const i32x4 *r = gq + gcap + t * LGW;
-        double2 S[G];
-        int lr[8];
-        double cn[G];
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          __builtin_memcpy(&S[j], &r[j], 16);
-          if constexpr (!F64) S[j] = make_double2(S[j].x + S[j].x, S[j].y + S[j].y);
-        }
-        {
-          const i32x4 a = r[6], b = r[7];
-          lr[0] = a.x; lr[1] = a.y; lr[2] = a.z; lr[3] = a.w;
-          lr[4] = b.x; lr[5] = b.y; lr[6] = b.z; lr[7] = b.w;
-        }
-        if constexpr (!F64) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) __builtin_memcpy(&cn[2 * k], &r[10 + k], 16);
-        } else {
-#pragma unroll
-          for (int j = 0; j < G; ++j) cn[j] = 0.0;
-        }
-        double al, ci;
-        {
-          const i32x4 w8 = r[8];
-          const int a2[2] = {w8.x, w8.y}, c2[2] = {w8.z, w8.w};
-          __builtin_memcpy(&al, a2, 8);
-          __builtin_memcpy(&ci, c2, 8);
-        }
-        const i32x4 w9 = r[9];
-        const int node = w9.x, n = w9.y, self = w9.z;
-        typename PD::St st[NV];
-        {
-          const RG gi = gload(self + kc);
-#pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            if constexpr (F64) div_init_w(st[v], LG::get(gi, v));
-            else PD::init(st[v], LG::get(gi, v), ci);
-          }
-        }
-        RG gn[G];
-#pragma unroll
-        for (int j = 0; j < G; ++j) gn[j] = gload((lr[j] & ~kLrefPole) + kc);
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-          const bool pole = (lr[j] & kLrefPole) != 0;
-          if (j < kMinRow) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-              if constexpr (F64) div_add_half_w(st[v], LG::get(gn[j], v), S[j]);
-              else PD::add(st[v], LG::get(gn[j], v), S[j], false, cn[j]);
-            }
-            continue;
-          }
-          const bool use = j < n && !pole;
-#pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            typename PD::St tt = st[v];
-            if constexpr (F64) div_add_half_w(tt, LG::get(gn[j], v), S[j]);
-            else PD::add(tt, LG::get(gn[j], v), S[j], pole, cn[j]);
-            PD::keep(st[v], tt, use);
-          }
-        }
-        constexpr int WD = NV * (int)sizeof(T) / 4;
-        struct Words { int v[WD]; } o;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const T x = PD::result(st[v], al, 0.0);
-          __builtin_memcpy(&o.v[v * (int)sizeof(T) / 4], &x, sizeof(T));
-        }
-        if (lane_on) *reinterpret_cast<Words *>(out + (size_t)node * L + first(kc)) = o;
-      }
-    }
-    // this step's LDS reads are done before the producers refill a slot
+    // this step's LDS accesses are done before the barrier
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   }
+}
+
+// The instance for LPN lanes per position (8, 16 or 32) and NE elements per
+// lane (1 .. kLswMaxNe).
+template <class T, int LPN, int NE = 1>
+void (*lsweepw_kernel_ne(int ne))(LaplView, const int4 *, const T *, T *, int, int, int) {
+  if constexpr (NE < kLswMaxNe) {
+    if (ne > NE) return lsweepw_kernel_ne<T, LPN, NE + 1>(ne);
+  }
+  return &k_lsweepw<T, LPN, NE>;
+}
+template <class T>
+auto lsweepw_kernel(int lpn, int ne) {
+  return lpn == 8    ? lsweepw_kernel_ne<T, 8>(ne)
+         : lpn == 16 ? lsweepw_kernel_ne<T, 16>(ne)
+                     : lsweepw_kernel_ne<T, 32>(ne);
 }
 
 // Packs the fused Laplacian's per-record geometry (after the scales are
@@ -2529,20 +2501,20 @@ __global__ void k_pack_lgeo(DevMesh m, i32x4 *__restrict__ dst) {
   __builtin_memcpy(&o[10], m.ncos + pr.r0, 48);
 }
 
-// Packs the wave-specialised sweep's per-position records (after the scales
-// are derived): `vec` 0 for scalar inputs, 1 for vector inputs.  Entries past
-// a row are neutral: zero normals, cos(lat) 1.
-__global__ void k_pack_sgeo(DevMesh m, int vec, i32x4 *__restrict__ dst) {
+// Packs the wave-specialised kernels' per-position records (after the scales
+// are derived): `vec` 0 for scalar inputs, 1 for vector inputs; by position
+// or by node.  Entries past a row are neutral: zero normals, cos(lat) 1.
+__global__ void k_pack_sgeo(DevMesh m, int vec, int by_node, i32x4 *__restrict__ dst) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= m.V) return;
   const PosRec pr = m.pos[p];
   const int n = pr.r1 - pr.r0;
-  const double sc[2] = {pr.alpha, vec ? m.coslat[pr.node] : pr.beta};
-  int w[4];
-  __builtin_memcpy(w, sc, 16);
-  i32x4 *o = dst + (size_t)p * (vec ? kSgeoWordsV : kSgeoWordsS);
+  const double sc[3] = {pr.alpha, vec ? m.coslat[pr.node] : pr.beta, m.coslat[pr.node]};
+  int w[6];
+  __builtin_memcpy(w, sc, 24);
+  i32x4 *o = dst + (size_t)(by_node ? pr.node : p) * (vec ? kSgeoWordsV : kSgeoWordsS);
   o[0] = i32x4{pr.node, 0, w[0], w[1]};
-  o[1] = i32x4{w[2], w[3], 0, 0};
+  o[1] = i32x4{w[2], w[3], w[4], w[5]};
   for (int j = 0; j < 6; ++j) {  // halved normals (exact)
     const double2 v = j < n ? make_double2(0.5 * m.S[pr.r0 + j].x, 0.5 * m.S[pr.r0 + j].y)
                             : make_double2(0.0, 0.0);
@@ -2873,16 +2845,18 @@ atlas_status pack_lapl_geometry(MeshStore &m, int64_t ngrec) {
 }
 
 atlas_status pack_sweep_geometry(MeshStore &m) {
-  for (int vec = 0; vec < 2; ++vec) {
+  // by position for scalar and vector inputs, by node for the Laplacian
+  for (int k = 0; k < (m.lcuts.empty() ? 2 : 3); ++k) {
+    const int vec = k == 1;
     void *g = nullptr;
     const size_t gb = (size_t)m.d.V * (vec ? kSgeoWordsV : kSgeoWordsS) * 16;
     if (hipMalloc(&g, gb) != hipSuccess) return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
     m.allocations.push_back(g);
     m.bytes += gb;
     hipLaunchKernelGGL(k_pack_sgeo, dim3((m.d.V + 255) / 256), dim3(256), 0, 0, m.d, vec,
-                       static_cast<i32x4 *>(g));
+                       k == 2 ? 1 : 0, static_cast<i32x4 *>(g));
     ATLASX_HIP(hipGetLastError());
-    (vec ? m.d.sgeo_v : m.d.sgeo) = static_cast<const int4 *>(g);
+    (k == 0 ? m.d.sgeo : k == 1 ? m.d.sgeo_v : m.d.sgeo_n) = static_cast<const int4 *>(g);
   }
   return ATLAS_OK;
 }
@@ -3047,6 +3021,13 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
   return true;
 }
 
+struct FusedwPlan {
+  int cut = 0, vpc = 0, nchunk = 0, lpn = 0, ne = 0, block = 0;
+  size_t lds = 0;
+};
+template <class T>
+static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, FusedwPlan *fp);
+
 LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt) {
   LaunchShape s;
   s.variant = nlev >= 24 ? ATLAS_VARIANT_COLUMN : ATLAS_VARIANT_FLAT;
@@ -3058,19 +3039,27 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   // the wave-specialised sweep needs the packed geometry and rows of 4..6
   const bool sweepw_fits = m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow;
   if (op == ATLAS_OP_LAPLACIAN) {
-    // large meshes: the fused one-pass form, wave-specialised (it moves a
-    // third of the two passes' field bytes; measured faster than the two
-    // passes up to 137 levels at O640 and O1280 in both precisions from 17
-    // levels in FP64 and 33 in FP32).  Shorter columns take the two passes,
-    // each on its own sweep with several positions per wavefront (O1280
-    // FP64 16 levels: 1.61 against 1.89 ms; FP32 32 levels: 2.05 against
-    // 2.57)
-    if (nlev >= (dt == ATLAS_F64 ? 17 : 33) && m.d.l2_ok && m.d.ntiles >= kSweepMinTiles &&
-        m.d.maxdeg <= 6 && m.d.mindeg >= kMinRow) {
-      s.variant = ATLAS_VARIANT_FUSED;
-      s.block = 1024;
-      s.nodes_per_block = 0;
-      return s;
+    // the fused one-pass form, wave-specialised, where it beats the two
+    // passes on their own shapes: on large meshes from 4 levels in FP64
+    // (O1280, 10 levels: 1.03 against 1.09 ms, 137: 7.2 against 9.4) and from
+    // 64 in FP32 (24 levels: 1.46 against 1.22 ms, 137: 4.85 against 5.65);
+    // on small ones with work enough to hide its longer walk (FP64: O160, 137
+    // levels, 187 against 245 us, 37 levels 77 against 62; O320, 37 levels,
+    // 158 against 291; FP32: O240, 137 levels, 254 against 291, O160 151
+    // against 122)
+    const bool f64 = dt == ATLAS_F64;
+    const int64_t values = (int64_t)m.d.V * nlev;
+    const bool worth = m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 64)
+                       : f64                        ? values >= 5000000
+                                                    : values >= 25000000 && nlev >= 64;
+    FusedwPlan fw;
+    LaunchShape fs;
+    fs.variant = ATLAS_VARIANT_FUSED;
+    fs.block = kLswBlock;
+    if (worth && m.d.ntiles >= 64 &&
+        (f64 ? fusedw_plan<double>(m, nlev, fs, &fw) : fusedw_plan<float>(m, nlev, fs, &fw))) {
+      fs.block = max(512, fw.block);
+      return fs;
     }
     s.per_pass = 1;
     return s;
@@ -3511,55 +3500,76 @@ static bool fused_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fus
 }
 
 // The wave-specialised fused Laplacian's plan (blocks_per_cu 0, 16-byte
-// lanes, at least one consumer wavefront): the level chunk shrinks until
-// the three rings fit in LDS; false where it cannot run.  The field ring
-// has five slots, or four where five would take one more level chunk
-// (FP64 at 137 levels on O1280's tiles: three chunks of 23 lane vectors
-// instead of four of 18); nodes_per_block 4 or 5 sets it.
-struct FusedwPlan {
-  int vpc, nchunk, fcap, gcap, ocap, fslots;
-  size_t lds;
-};
+// vectors, at least one consumer wavefront): the cut of the tiles with the
+// fewest level chunks (then the fewest parts, then the fewest steps until
+// the last round of workgroups is done); false where none fits in LDS.
+// (nodes_per_block 4 and 5 chose a ring in earlier forms and are taken as 0.)
 template <class T>
 static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, FusedwPlan *fp) {
   const DevMesh &m = ms.d;
   constexpr int NVW = (int)(16 / sizeof(T));
-  if (!m.l2_ok || m.maxdeg > 6 || m.mindeg < kMinRow || !m.l2_ggeo || !m.l2_lgeo) return false;
+  if (ms.lcuts.empty() || m.mindeg < kMinRow || !m.sgeo_n) return false;
   if (sh.blocks_per_cu != 0 || sh.level_vec == 1 || nlev < NVW) return false;
-  if (sh.block < 64 * (kLswProducers + 1)) return false;
-  if (m.l2_gmax > 64 || m.l2_pmax > 64) return false;  // one record of each kind per lane
-  const int nvec = (nlev + NVW - 1) / NVW;
-  int vpc = sh.level_chunk > 0 ? min(64, (sh.level_chunk + NVW - 1) / NVW) : 64;
-  vpc = min(vpc, nvec);
-  int nch = (nvec + vpc - 1) / vpc;
-  vpc = (nvec + nch - 1) / nch;
-  auto r64 = [](int64_t x) { return (int)((x + 63) / 64 * 64); };
-  const int LGW = sizeof(T) == 8 ? kLGeoWords64 : kLGeoWords;
-  const int gcap = r64((int64_t)m.l2_gmax * kGGeoWords), ocap = r64((int64_t)m.l2_pmax * LGW);
-  auto bytes = [&](int v, int fs) {
-    return (size_t)16 * ((size_t)fs * r64((int64_t)m.l2_fmax * v) +
-                         (size_t)kLswGSlots * 2 * m.l2_gmax * v +
-                         (size_t)kLswGeoSlots * (gcap + ocap));
-  };
+  if (sh.block < 320) return false;
   if (sh.nodes_per_block != 0 && sh.nodes_per_block != 4 && sh.nodes_per_block != 5) return false;
-  int fs = sh.nodes_per_block ? sh.nodes_per_block : kLswFSlots;
-  while (vpc > 1 && bytes(vpc, fs) > kMaxLds) {
-    if (!sh.nodes_per_block && fs == kLswFSlots && bytes(vpc, 4) <= kMaxLds) {
-      fs = 4;  // four slots save this chunk
-      break;
+  const int nvec = (nlev + NVW - 1) / NVW;
+  const int most = 32 * kLswMaxNe / 2;
+  const int want = sh.level_chunk > 0 ? (sh.level_chunk + NVW - 1) / NVW : most;
+  const int cus = device_cu_count();
+  int64_t best_steps = 0;
+  bool any = false;
+  for (size_t k = 0; k < ms.lcuts.size(); ++k) {
+    const LaplView &v = ms.lcuts[k];
+    auto bytes = [&](int c) {
+      return (size_t)16 * ((size_t)kLswFieldSlots * v.fmax * c +
+                           (size_t)kLswGradSlots * v.gmax * 2 * c +
+                           (size_t)kLswRecSlots * v.gmax * kSgeoWordsS +
+                           (size_t)kLswRefSlots * (v.gmax + v.pmax)) +
+             (sizeof(T) == 4 ? (size_t)8 * kLswGradSlots * v.gmax : 0) + kSweepwLdsTail;
+    };
+    FusedwPlan p;
+    p.cut = (int)k;
+    p.vpc = min(min(want, most), nvec);
+    p.nchunk = (nvec + p.vpc - 1) / p.vpc;
+    p.vpc = (nvec + p.nchunk - 1) / p.nchunk;
+    // (a field run is loaded by one wavefront's kRunLoads instructions)
+    auto fits = [&](int c) {
+      return bytes(c) <= kMaxLds && v.fmax * c <= kRunLoads * 64 * kLswGroupWaves;
+    };
+    while (p.vpc > 1 && !fits(p.vpc)) {
+      ++p.nchunk;
+      p.vpc = (nvec + p.nchunk - 1) / p.nchunk;
     }
-    ++nch;
-    vpc = (nvec + nch - 1) / nch;
+    p.nchunk = (nvec + p.vpc - 1) / p.vpc;
+    p.lds = bytes(p.vpc);
+    if (!fits(p.vpc)) continue;
+    if (any && (p.nchunk > fp->nchunk ||
+                (p.nchunk == fp->nchunk && v.parts > ms.lcuts[fp->cut].parts)))
+      continue;
+    const int nel = p.vpc * 2;
+    int cost = INT_MAX;
+    for (int l : {8, 16, 32}) {
+      const int e = (nel + l - 1) / l;
+      if (e <= kLswMaxNe && (e + 3) * l < cost) {
+        cost = (e + 3) * l;
+        p.lpn = l;
+        p.ne = e;
+      }
+    }
+    const int npn = 64 / p.lpn;
+    const int tasks = (v.gmax + npn - 1) / npn + (v.pmax + npn - 1) / npn;
+    p.block = min(kLswBlock, 64 * (kLswProducers + tasks));
+    const int64_t places = (int64_t)cus * max(1, min((int)(kMaxLds / p.lds), 1024 / p.block));
+    const int64_t steps =
+        ((int64_t)v.ntiles * p.nchunk + places - 1) / places * (v.rings + 6);
+    if (!any || p.nchunk < fp->nchunk || v.parts < ms.lcuts[fp->cut].parts ||
+        steps < best_steps) {
+      *fp = p;
+      best_steps = steps;
+      any = true;
+    }
   }
-  if (bytes(vpc, fs) > kMaxLds) return false;
-  fp->vpc = vpc;
-  fp->nchunk = (nvec + vpc - 1) / vpc;
-  fp->fcap = r64((int64_t)m.l2_fmax * vpc);
-  fp->gcap = gcap;
-  fp->ocap = ocap;
-  fp->fslots = fs;
-  fp->lds = bytes(vpc, fs);
-  return true;
+  return any;
 }
 
 bool lapl_fused_runs(const MeshStore &ms, int nlev, atlas_dtype dt, const LaunchShape &sh) {
@@ -3581,15 +3591,14 @@ atlas_status launch_lapl_fused(const MeshStore &ms, const T *in, int nlev, T *ou
   constexpr int NVW = (int)(16 / sizeof(T));
   FusedwPlan fw;
   if (fusedw_plan<T>(ms, nlev, sh, &fw)) {
-    // wave-specialised: consumers take one lane vector per lane, vpc lanes
-    // per node
-    const int units = m.ntiles * fw.nchunk;
-    const int per = (units + 7) / 8;
-    auto kern = fw.fslots == 4 ? k_lsweepw<T, NVW, 4> : k_lsweepw<T, NVW, 5>;
+    const LaplView &v = ms.lcuts[fw.cut];
+    const int64_t units = (int64_t)v.ntiles * fw.nchunk;
+    const int per = (int)((units + 7) / 8);
+    auto kern = lsweepw_kernel<T>(fw.lpn, fw.ne);
     ATLASX_HIP(hipFuncSetAttribute((const void *)kern,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)fw.lds));
-    hipLaunchKernelGGL(kern, dim3(per * 8), dim3(sh.block), fw.lds, st, m, in, out, nlev, fw.vpc,
-                       m.ntiles, per, fw.vpc, fw.fcap, fw.gcap, fw.ocap);
+    hipLaunchKernelGGL(kern, dim3(per * 8), dim3(min(sh.block, kLswBlock)), fw.lds, st, v, m.sgeo_n, in, out, nlev,
+                       fw.vpc, per);
     ATLASX_HIP(hipGetLastError());
     *ran = true;
     return ATLAS_OK;
