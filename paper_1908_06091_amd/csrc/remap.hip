@@ -212,6 +212,66 @@ __global__ void __launch_bounds__(kApplyBlock)
   out[e] = (T)s;
 }
 
+// Rows of several 16-byte vectors: a workgroup takes a few consecutive
+// targets, their records in LDS, and its threads the targets'
+// vectors one after another, so every lane moves 16 bytes in each access
+// whatever the row's length, and a workgroup writes one contiguous piece of
+// the output.  A row's last vector is clamped to its end: the columns it
+// repeats get the same bits.  What bounds a remap that writes more rows than
+// it reads is the address path, some 28 cycles for each wavefront access: a
+// row of 137 FP64 columns takes 4.3 accesses here, 12 with a wavefront per
+// row and 8 bytes per lane (O640 to O1280: FP64 3.55 -> 2.83, FP32 2.94 -> 1.37 ms).
+// Elements go through the flat form's arithmetic.
+constexpr int kVecTargets = 64, kVecUnroll = 4;  // targets: at most
+template <class T>
+__global__ void __launch_bounds__(kApplyBlock)
+    k_remap_vec(const RemapRec *__restrict__ rec, const T *__restrict__ in, int32_t ncol,
+                int32_t nvec, uint32_t magic, int targets, int64_t nt, int64_t per_xcd,
+                T *__restrict__ out) {
+  constexpr int NV = 16 / (int)sizeof(T);
+  struct Vec {
+    T v[NV];
+  };
+  __shared__ RemapRec recs[kVecTargets];
+  const int64_t g = blockIdx.x;
+  const int64_t t0 = ((g % kXcds) * per_xcd + g / kXcds) * targets;
+  if (t0 >= nt) return;
+  const int n = (int)min((int64_t)targets, nt - t0);
+  constexpr int RW = (int)sizeof(RemapRec) / 16;
+  for (int i = threadIdx.x; i < n * RW; i += kApplyBlock)
+    reinterpret_cast<int4 *>(recs)[i] = reinterpret_cast<const int4 *>(rec + t0)[i];
+  __syncthreads();
+  const uint32_t items = (uint32_t)n * (uint32_t)nvec;
+  const size_t row = (size_t)ncol * sizeof(T);
+  const unsigned char *src = reinterpret_cast<const unsigned char *>(in);
+  unsigned char *dst = reinterpret_cast<unsigned char *>(out) + (size_t)t0 * row;
+  for (uint32_t i0 = threadIdx.x; i0 < items; i0 += kApplyBlock * kVecUnroll) {
+    Vec x[kVecUnroll][3];
+    uint32_t t[kVecUnroll], c[kVecUnroll];
+#pragma unroll
+    for (int u = 0; u < kVecUnroll; ++u) {
+      const uint32_t i = min(i0 + (uint32_t)(u * kApplyBlock), items - 1);
+      t[u] = __umulhi(i, magic);  // i / nvec
+      const uint32_t k = i - t[u] * (uint32_t)nvec;
+      c[u] = min(k * NV, (uint32_t)(ncol - NV)) * (uint32_t)sizeof(T);
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        __builtin_memcpy(&x[u][j], src + (size_t)(uint32_t)recs[t[u]].i[j] * row + c[u], 16);
+    }
+#pragma unroll
+    for (int u = 0; u < kVecUnroll; ++u) {
+      if (i0 + (uint32_t)(u * kApplyBlock) >= items) break;
+      const double w0 = recs[t[u]].w[0], w1 = recs[t[u]].w[1], w2 = recs[t[u]].w[2];
+      Vec o;
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+        o.v[v] = (T)(w0 * (double)x[u][0].v[v] + w1 * (double)x[u][1].v[v] +
+                     w2 * (double)x[u][2].v[v]);
+      __builtin_memcpy(dst + (size_t)t[u] * row + c[u], &o, 16);
+    }
+  }
+}
+
 // Long rows (ncol >= 64): one wavefront per target row, lanes over its
 // columns, four column blocks of 64 in flight per lane; the record is read
 // once per row with scalar loads.  Same arithmetic per element as the flat
@@ -313,6 +373,37 @@ atlas_status build_plan(const MeshStore &src, const double *tlon, const double *
 
 atlas_status remap_launch(const RemapPlan &p, const void *in, int32_t ncol, atlas_dtype dt,
                           void *out, hipStream_t st) {
+  const int nv = dt == ATLAS_F64 ? 2 : 4;
+  const int32_t nvec = (ncol + nv - 1) / nv;
+  // Vectors per lane in FP32 from 5 columns (8 to fewer points; two vectors; O640 to O1280: 97
+  // against 148 us, 16 columns 158 against 416) and in FP64 from 8 where more
+  // rows are written than read (157 against 284 us; 3 columns 131 against
+  // 108); a remap to fewer points reads most rows once, streams, and keeps
+  // the scalar forms in FP64 (O1280 to O640, 137 columns: 1.32 against 1.45
+  // ms).  items / nvec by a multiplication: exact for 32 nvec^2 < 2^32.
+  const bool more = p.nt > p.touched;
+  const bool vec = dt == ATLAS_F64 ? ncol >= 8 && more : ncol >= (more ? 5 : 8);
+  if (vec && nvec < 8192) {
+    // targets per workgroup: enough vectors to fill its threads, few enough
+    // that the targets in flight on an XCD share their source rows in its L2
+    // (O640 to O1280, FP64, 137 columns: 8 targets 2.83 ms, 32 3.27; 8
+    // columns: 64 targets 157 us, 8 457)
+    const int targets = nvec >= 40 ? 8 : nvec >= 24 ? 16 : nvec >= 16 ? 32 : 64;
+    const int64_t nblk = (p.nt + targets - 1) / targets;
+    const int64_t per_xcd = (nblk + kXcds - 1) / kXcds;
+    const unsigned grid = (unsigned)(per_xcd * kXcds);
+    const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + nvec - 1) / nvec);
+    if (dt == ATLAS_F64)
+      hipLaunchKernelGGL(k_remap_vec<double>, dim3(grid), dim3(kApplyBlock), 0, st, p.rec,
+                         static_cast<const double *>(in), ncol, nvec, magic, targets, p.nt, per_xcd,
+                         static_cast<double *>(out));
+    else
+      hipLaunchKernelGGL(k_remap_vec<float>, dim3(grid), dim3(kApplyBlock), 0, st, p.rec,
+                         static_cast<const float *>(in), ncol, nvec, magic, targets, p.nt, per_xcd,
+                         static_cast<float *>(out));
+    ATLASX_HIP(hipGetLastError());
+    return ATLAS_OK;
+  }
   if (ncol >= 64) {
     const int64_t nblk = (p.nt + kApplyBlock / 64 - 1) / (kApplyBlock / 64);
     const int64_t per_xcd = (nblk + kXcds - 1) / kXcds;
