@@ -56,6 +56,7 @@ constexpr int kIncPad = 8;               // incidence arrays carry one extra gro
 constexpr int32_t kLrefPole = 1 << 30;  // sweep reference of a pole edge
 constexpr int kGRefs = 8;               // references per gradient node (two-ring plan)
 constexpr int kSweepMinTiles = 1024;  // tiles with which a mesh counts as a large one
+constexpr int kSweepFewTiles = 64;    // tiles below which no built-in shape sweeps
 constexpr int kDefaultBand = 32;   // parallels per band of the processing order
 constexpr int kDefaultWidth = 32;  // nodes per sector of a band's widest parallel
 

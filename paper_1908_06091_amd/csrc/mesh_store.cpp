@@ -847,9 +847,13 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   const bool l2_ok = sweep_ok && lapl_plan(rings_of(d), perm, tile_ptr, rowp, nbr, lp);
   if (!l2_ok) lp = LaplPlan();
   // the sweep's cuts: longitude parts for columns too long for whole tiles;
-  // bands as well where the mesh has too few tiles to fill the chip
+  // bands as well where the mesh has too few tiles to fill the chip (below
+  // kSweepFewTiles no built-in shape would use them: O16's upload 1.28 ms
+  // with them, 1.1 without)
+  const int64_t nt = (int64_t)tile_ptr.size() - 1;
+  const bool bands = nt >= kSweepFewTiles && nt < kSweepMinTiles;
   std::vector<std::pair<int, int>> shapes = {{1, 1}, {2, 1}, {3, 1}};
-  if ((int64_t)tile_ptr.size() - 1 < kSweepMinTiles)
+  if (bands)
     shapes = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {1, 6}, {2, 1}, {2, 2}, {3, 1}, {3, 2}};
   std::vector<CutPlan> cuts(sweep_ok ? shapes.size() : 0);
   if (sweep_ok) {
@@ -863,7 +867,7 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
         cuts.clear();
   }
   std::vector<std::pair<int, int>> lshapes = {{1, 1}, {2, 1}};
-  if ((int64_t)tile_ptr.size() - 1 < kSweepMinTiles)
+  if (bands)
     lshapes = {{1, 1}, {1, 2}, {1, 4}, {2, 1}, {2, 2}, {2, 4}};
   std::vector<LaplCutPlan> lcuts(cuts.empty() ? 0 : lshapes.size());
   if (!lcuts.empty()) {

@@ -3001,7 +3001,7 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
   const bool grad = op == ATLAS_OP_GRADIENT;
   if (!grad && op != ATLAS_OP_DIVERGENCE && op != ATLAS_OP_CURL) return false;
   const int nv = dt == ATLAS_F64 ? (grad ? 2 : 1) : (grad ? 4 : 2);  // levels per vector
-  if (nlev < nv || m.ntiles < 64) return false;
+  if (nlev < nv || m.ntiles < kSweepFewTiles) return false;
   const bool large = m.ntiles >= kSweepMinTiles;
   if (!large && (int64_t)m.V * nlev < 1500000) return false;
   const SweepwPlan p = dt == ATLAS_F64 ? (grad ? sweepw_plan<double, OP_GRAD, false>(ms, nlev, 0)
@@ -3056,7 +3056,7 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     LaunchShape fs;
     fs.variant = ATLAS_VARIANT_FUSED;
     fs.block = kLswBlock;
-    if (worth && m.d.ntiles >= 64 &&
+    if (worth && m.d.ntiles >= kSweepFewTiles &&
         (f64 ? fusedw_plan<double>(m, nlev, fs, &fw) : fusedw_plan<float>(m, nlev, fs, &fw))) {
       fs.block = max(512, fw.block);
       return fs;
