@@ -2919,6 +2919,16 @@ static SweepwPlan sweepw_plan(const MeshStore &ms, bool vec, bool whole, int epv
   const int cus = device_cu_count();
   SweepwPlan best;
   int64_t best_steps = 0;
+  // tiles refused as too large: runs so long that even a one-vector chunk
+  // leaves no room for the records of as many positions (above 224 nodes, 164 with
+  // vector inputs; a regular grid's polar rows take half a parallel)
+  const size_t seg = (size_t)max(1, ms.d.segmax);
+  auto lines = [](size_t words) { return (words + 63) / 64 * 64; };
+  if (16 * (kSweepwSlots * lines(seg) + kSweepwGeoSlots * lines(seg * (vec ? 14 : 10))) >
+      kMaxLds) {
+    best.lds = kMaxLds + 1;
+    return best;
+  }
   for (size_t k = 0; k < ms.cuts.size(); ++k) {
     const SweepView &v = ms.cuts[k];
     if (whole && v.parts > 1) continue;
@@ -3037,7 +3047,12 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   const bool sweep_fits = m.d.sweep_ok && m.d.ntiles >= kSweepMinTiles &&
                           max(1, m.d.segmax) * kGeoWords <= 768;
   // the wave-specialised sweep needs the packed geometry and rows of 4..6
-  const bool sweepw_fits = m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow;
+  // and runs about as long as a tile's own rows: a regular grid's polar rows
+  // refer to the far half of their parallel, and rings of such runs leave no
+  // room for columns (F640, 20 levels: FP64 gradient 2.95 against 1.06 ms for
+  // the flat form, divergence 6.3 against 1.12)
+  const bool sweepw_fits = m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow &&
+                           max(1, m.d.segmax) * kGeoWords <= 768;
   if (op == ATLAS_OP_LAPLACIAN) {
     // the fused one-pass form, wave-specialised, where it beats the two
     // passes on their own shapes: on large meshes from 4 levels in FP64
@@ -3512,6 +3527,10 @@ static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fu
   if (sh.blocks_per_cu != 0 || sh.level_vec == 1 || nlev < NVW) return false;
   if (sh.block < 320) return false;
   if (sh.nodes_per_block != 0 && sh.nodes_per_block != 4 && sh.nodes_per_block != 5) return false;
+  // (field runs far longer than the tiles' own rows, as a regular grid's
+  // polar rows need, leave room for a level or two: F640, 37 levels, 17.2
+  // against 2.8 ms for the two passes)
+  if (ms.lcuts[0].fmax > 2 * ms.lcuts[0].pmax + 16) return false;
   const int nvec = (nlev + NVW - 1) / NVW;
   const int most = 32 * kLswMaxNe / 2;
   const int want = sh.level_chunk > 0 ? (sh.level_chunk + NVW - 1) / NVW : most;
