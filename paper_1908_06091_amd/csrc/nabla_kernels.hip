@@ -877,8 +877,8 @@ __global__ void __launch_bounds__(512)
 }
 
 // Levels per lane of the level-vector form for (T, OP, nlev).  FP64 (bound
-// by memory traffic): 16-byte lanes.  FP32 (its compensated sums make the
-// arithmetic the larger cost): the width (1..4 levels, at most 32 bytes per
+// by memory traffic): 16-byte lanes.  FP32 (its FP64 sums and conversions
+// weigh more against half the bytes): the width (1..4 levels, at most 32 bytes per
 // lane) that needs the fewest level slots per lane (NV x chunks of 64
 // lanes; the arithmetic runs once per slot), then the fewest load
 // instructions per column.  `want` > 0 forces a width.  0 when the form
@@ -1323,10 +1323,15 @@ __global__ void __launch_bounds__(1024) k_sweepv(DevMesh m, const T *__restrict_
 // place and the neighbours' cos(lat) at the end.
 constexpr int kSgeoWordsS = 8, kSgeoWordsV = 11;
 // Elements per lane: at most what 128 registers hold (one workgroup of up to
-// 1024 threads per compute unit).
+// 1024 threads per compute unit).  FP32 vector inputs stop at three, since
+// four spill 3 to 9 registers: O731, FP32 divergence, 110 levels, 1230 us
+// with four of them and 870 with three, 64 levels 662 and 470; divergence and
+// curl, 32 levels, 486 and 390.  (Five spill 2 to 4 of the FP64 divergence's
+// and the FP32 gradient's and still win: 947 against 992 us, 80 levels, and
+// 776 against 788, 130 levels.)
 template <class T, int OP, bool DC>
 constexpr int sweepw_max_ne() {
-  return sizeof(T) == 8 ? (DC ? 3 : 5) : OP == OP_GRAD ? 5 : 4;
+  return sizeof(T) == 8 ? (DC ? 3 : 5) : OP == OP_GRAD ? 5 : 3;
 }
 // Levels of an element.
 template <class T, bool DC>
@@ -2119,7 +2124,7 @@ __global__ void __launch_bounds__(1024) k_lsweep(DevMesh m, const T *__restrict_
 // Fused Laplacian, wave-specialised: the register-staged kernel above waits
 // at every parallel for the loads it issued one parallel earlier, one
 // memory round trip per step.  Here, as in the wave-specialised sweep, two
-// producer groups of two wavefronts load straight into LDS two steps ahead
+// producer groups of one wavefront load straight into LDS two steps ahead
 // and never store, and the consumer wavefronts only compute and store.
 //
 // Step q forms the gradients of the g-run of parallel q (from field runs
@@ -3057,14 +3062,15 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     // the fused one-pass form, wave-specialised, where it beats the two
     // passes on their own shapes: on large meshes from 4 levels in FP64
     // (O1280, 10 levels: 1.03 against 1.09 ms, 137: 7.2 against 9.4) and from
-    // 64 in FP32 (24 levels: 1.46 against 1.22 ms, 137: 4.85 against 5.65);
+    // 33 in FP32 (24 levels: 1.46 against 1.22 ms, 40: 1.78 against 1.75,
+    // 63: 2.19 against 3.15, 137: 4.85 against 5.65; it needs no workspace);
     // on small ones with work enough to hide its longer walk (FP64: O160, 137
     // levels, 187 against 245 us, 37 levels 77 against 62; O320, 37 levels,
     // 158 against 291; FP32: O240, 137 levels, 254 against 291, O160 151
     // against 122)
     const bool f64 = dt == ATLAS_F64;
     const int64_t values = (int64_t)m.d.V * nlev;
-    const bool worth = m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 64)
+    const bool worth = m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 33)
                        : f64                        ? values >= 5000000
                                                     : values >= 25000000 && nlev >= 64;
     FusedwPlan fw;
@@ -3085,8 +3091,8 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   // band's parallels in turn: only a mesh of many tiles fills the chip
   if (nlev < 48) {
     if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT && sweep_fits) {
-      // register-staged sweep: it keeps one level per lane at these lengths
-      // (37 levels at O1280: 1.9 ms against 3.6 ms for 16-byte lanes)
+      // without the packed geometry: the register-staged sweep, one level per
+      // lane (37 levels at O1280: 1.9 ms against 3.6 ms for 16-byte lanes)
       s.variant = ATLAS_VARIANT_SWEEP;
       s.block = 768;
       s.nodes_per_block = 0;
@@ -3098,10 +3104,8 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   }
   if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT) {
     s.level_vec = 1;
-    // up to ~80 levels the register-staged sweep's single read of each
-    // column wins over the compensated sums' lane work (64 levels: 2.1 ms
-    // against 2.5 ms at O1280); beyond, one level per lane (91 levels: 3.02
-    // against 3.30 ms)
+    // without the packed geometry: up to ~80 levels the register-staged
+    // sweep's single read of each column wins over the column form
     if (nlev < 80 && sweep_fits) {
       s.variant = ATLAS_VARIANT_SWEEP;
       s.block = 768;
