@@ -2889,12 +2889,12 @@ size_t flux_ws_bytes(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt) 
 // Built-in shape (the autotuner can replace it per mesh and class), from
 // measurements: the wave-specialised sweep wherever its pieces fill the chip
 // (sweepw_default).  Elsewhere, below 24 levels the flat form over blocks of
-// 64 positions (512 threads), from 24 levels the column form over blocks of
-// 16 consecutive positions (a run of one parallel, so the neighbour columns
-// of consecutive blocks overlap in L2), one level per lane up to 47 levels
-// (FP64 divergence and curl: the automatic lane-vector width) and for the
-// FP32 gradient.  The Laplacian takes the fused form or each pass's own
-// shape.
+// 64 positions (512 threads; larger ones on large meshes), from 24 levels the
+// column form over blocks of 16 consecutive positions (a run of one parallel,
+// so the neighbour columns of consecutive blocks overlap in L2), at the
+// automatic lane-vector width except the FP64 gradient to 47 levels and the
+// FP32 one above (one level per lane).  The Laplacian takes the fused form or
+// each pass's own shape.
 constexpr size_t kMaxLds = 160 * 1024;
 
 // How the wave-specialised sweep runs a column: the cut of the tiles, the
@@ -3049,6 +3049,15 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   s.block = nlev >= 24 ? 256 : 512;
   s.nodes_per_block = nlev >= 24 ? 16 : 64;
   s.level_vec = 0;
+  if (nlev < 24 && m.d.ntiles >= kSweepMinTiles) {
+    // large meshes have blocks enough: more positions in each fetch fewer
+    // neighbours from other blocks (O1280, FP32 gradient, 3 levels: 426 us at
+    // 64 positions on 512 threads, 372 at 256 on 1024; one level, FP64: 333,
+    // 321 at 128, 341 at 256; F640, FP64 gradient, 2 levels 190 and 170, 20
+    // levels 1059 and 992)
+    s.block = 1024;
+    s.nodes_per_block = nlev == 1 ? 128 : 256;
+  }
   const bool sweep_fits = m.d.sweep_ok && m.d.ntiles >= kSweepMinTiles &&
                           max(1, m.d.segmax) * kGeoWords <= 768;
   // the wave-specialised sweep needs the packed geometry and rows of 4..6
@@ -3097,7 +3106,10 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
       s.block = 768;
       s.nodes_per_block = 0;
       s.blocks_per_cu = 1;
-    } else if (!(dt == ATLAS_F64 && (op == ATLAS_OP_DIVERGENCE || op == ATLAS_OP_CURL))) {
+    } else if (dt == ATLAS_F64 && op == ATLAS_OP_GRADIENT) {
+      // one level per lane (O100, 30 levels, 14.4 against 15.7 us); FP32 takes
+      // lane vectors (F300, 37 levels, gradient 155 against 172 us; F640, 47
+      // levels, divergence 1197 against 1286)
       s.level_vec = 1;
     }
     return s;

@@ -35,3 +35,22 @@ def test_builtin_shapes(mesh, op, nlev, dtype):
     elif op == "div" and nlev >= 2:
         with pytest.raises(P.AtlasError, match="too large"):
             mesh.apply(code, x, launch=P.Launch(P.VARIANT_SWEEP, 512, 0, 0, 0, 0))
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("nlev", [1, 2, 3, 23, 24, 47])
+@pytest.mark.parametrize("op", ["grad", "div"])
+def test_many_tiles(op, nlev, dtype):
+    """Short columns on a mesh of many tiles: larger blocks of the flat form,
+    and 24 to 47 levels on lane vectors; block ends inside and past rows."""
+    m = P.Mesh(nx=P.regular_gaussian_nx(48), layout=(2, 8))
+    code = _OPS[op]
+    g = torch.Generator().manual_seed(nlev)
+    shape = (m.nnodes, nlev) + ((2,) if op == "div" else ())
+    x = torch.randn(shape, generator=g, dtype=torch.float64).to(dtype).cuda()
+    sh = m.shape_of(code, nlev, x)
+    if nlev < 24:
+        assert (sh["variant"], sh["block_threads"]) == (P.VARIANT_FLAT, 1024)
+    got = m.apply(code, x)
+    assert torch.equal(got, m.apply(code, x, launch=P.Launch(P.VARIANT_FLAT, 256, 32, 0, 0, 0)))
+    m.close()
