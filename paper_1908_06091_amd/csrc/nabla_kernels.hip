@@ -3043,7 +3043,10 @@ struct FusedwPlan {
 template <class T>
 static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, FusedwPlan *fp);
 
-LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt) {
+// `packed`: the mesh's packed records may be used (they hold the physical
+// scales).
+LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt,
+                          bool packed) {
   LaunchShape s;
   s.variant = nlev >= 24 ? ATLAS_VARIANT_COLUMN : ATLAS_VARIANT_FLAT;
   s.block = nlev >= 24 ? 256 : 512;
@@ -3065,7 +3068,7 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   // refer to the far half of their parallel, and rings of such runs leave no
   // room for columns (F640, 20 levels: FP64 gradient 2.95 against 1.06 ms for
   // the flat form, divergence 6.3 against 1.12)
-  const bool sweepw_fits = m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow &&
+  const bool sweepw_fits = packed && m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow &&
                            max(1, m.d.segmax) * kGeoWords <= 768;
   if (op == ATLAS_OP_LAPLACIAN) {
     // the fused one-pass form, wave-specialised, where it beats the two
@@ -3095,18 +3098,24 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     return s;
   }
   if (sweepw_fits && sweepw_default(m, op, dt, nlev, &s)) return s;
+  // Without the packed records the sweep is the register-staged one: one
+  // workgroup per tile and level chunk, each walking its band's parallels in
+  // turn, so only a mesh of many tiles fills the chip (O160, 37 levels, FP64
+  // gradient: 100 us on 130 tiles, 30 for the column form), and only columns
+  // long enough to hide each step's loads repay the walk.  FP32 gradient:
+  // 20 to 79 levels (O1280: 16 levels 1560 against 1370 us for the flat form,
+  // 20: 1589 against 1785, 37: 1590 against 2177 for the column form, 64: 1834
+  // against 2380, 80: 2682 against 2618); FP64 gradient from 48 (below).
+  if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT && sweep_fits && nlev >= 20 && nlev < 80) {
+    s.variant = ATLAS_VARIANT_SWEEP;
+    s.block = 768;
+    s.nodes_per_block = 0;
+    s.blocks_per_cu = 1;
+    return s;
+  }
   if (nlev < 24) return s;
-  // the sweep runs one workgroup per tile and level chunk, each walking its
-  // band's parallels in turn: only a mesh of many tiles fills the chip
   if (nlev < 48) {
-    if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT && sweep_fits) {
-      // without the packed geometry: the register-staged sweep, one level per
-      // lane (37 levels at O1280: 1.9 ms against 3.6 ms for 16-byte lanes)
-      s.variant = ATLAS_VARIANT_SWEEP;
-      s.block = 768;
-      s.nodes_per_block = 0;
-      s.blocks_per_cu = 1;
-    } else if (dt == ATLAS_F64 && op == ATLAS_OP_GRADIENT) {
+    if (dt == ATLAS_F64 && op == ATLAS_OP_GRADIENT) {
       // one level per lane (O100, 30 levels, 14.4 against 15.7 us); FP32 takes
       // lane vectors (F300, 37 levels, gradient 155 against 172 us; F640, 47
       // levels, divergence 1197 against 1286)
@@ -3114,20 +3123,10 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     }
     return s;
   }
-  if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT) {
-    s.level_vec = 1;
-    // without the packed geometry: up to ~80 levels the register-staged
-    // sweep's single read of each column wins over the column form
-    if (nlev < 80 && sweep_fits) {
-      s.variant = ATLAS_VARIANT_SWEEP;
-      s.block = 768;
-      s.nodes_per_block = 0;
-      s.level_vec = 0;
-      s.blocks_per_cu = 1;
-    }
-  }
+  if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT) s.level_vec = 1;
   if (dt == ATLAS_F64 && op == ATLAS_OP_GRADIENT && sweep_fits) {
-    // without the packed geometry: the register-staged sweep on 768 threads
+    // (O1280: 64 levels 2953 against 3205 us for the column form, 137: 5891
+    // against 7185)
     s.variant = ATLAS_VARIANT_SWEEP;
     s.block = 768;
     s.nodes_per_block = 0;
@@ -3715,13 +3714,9 @@ atlas_status gradient_lonlat(MeshStore &ms, atlas_dtype dt, const void *in, int 
       ms.comp_ready = true;
     }
   }
-  // the built-in gradient shape, except the wave-specialised sweep (its
-  // packed geometry carries the physical scales): the register-staged one
-  LaunchShape sh = default_shape(ms, ATLAS_OP_GRADIENT, nlev, dt);
-  if (sh.variant == ATLAS_VARIANT_SWEEP) {
-    sh.blocks_per_cu = 1;
-    sh.block = 768;
-  }
+  // the built-in gradient shape among the forms that read the scales by
+  // position
+  const LaunchShape sh = default_shape(ms, ATLAS_OP_GRADIENT, nlev, dt, false);
   if (dt == ATLAS_F64)
     return launch_typed<double, OP_GRAD>(ms, static_cast<const double *>(in), nlev,
                                          static_cast<double *>(out), nullptr, sh, st, &ms.dcomp);

@@ -1,0 +1,34 @@
+"""d/dlon and d/dlat on both sides of their built-in forms' switches: the
+gradient's components times R cos(lat) and R.  Both sum the same terms in the
+same order, so they differ by the roundings of the scales (four products and
+quotients of one or two ulps each: 8 ulps) and of the result."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1908_06091_amd as P
+    return P
+
+
+@pytest.mark.parametrize("N", [160, 500])
+def test_scaled_gradient(P, N):
+    desc = P.mesh_desc_octahedral(N, 2.5)
+    gm = P.Mesh(N, radius=2.5)
+    scale = torch.ones(gm.nnodes, 1, 2, dtype=torch.float64)
+    scale[:, 0, 0] = torch.from_numpy(desc["cos_lat"])
+    scale = 2.5 * scale.cuda()
+    for nlev in (1, 19, 20, 24, 47, 48, 79, 80):
+        for dtype, bound in ((torch.float64, 8 * 2.0 ** -52), (torch.float32, 2.0 ** -23)):
+            print(f"lonlat O{N} nlev={nlev} {dtype}", flush=True)
+            g = torch.Generator(device="cuda")
+            g.manual_seed(nlev)
+            x = torch.randn(gm.nnodes, nlev, dtype=dtype, device="cuda", generator=g)
+            want = gm.gradient(x.double()) * scale
+            got = gm.gradient_lonlat(x).double()
+            assert bool(((got - want).abs() <= bound * want.abs()).all()), (nlev, dtype)
