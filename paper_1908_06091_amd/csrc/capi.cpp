@@ -443,17 +443,21 @@ size_t atlas_flux_workspace_bytes(atlas_mesh_t mesh, atlas_op op, int32_t nlev,
 }  // extern "C"
 
 namespace atlasx {
+bool tuned_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt, LaunchShape *s) {
+  MeshStore &ms = const_cast<MeshStore &>(m);
+  std::lock_guard<std::mutex> g(ms.tune_mu);
+  auto it = ms.tuned.find(TuneKey{(int)op, (int)dt, nlev});
+  if (it == ms.tuned.end()) return false;
+  *s = it->second;
+  return true;
+}
+
 LaunchShape shape_from(const atlas_launch *l, const MeshStore &m, atlas_op op, int nlev,
                        atlas_dtype dt) {
   LaunchShape s = default_shape(m, op, nlev, dt);
-  if (!l || l->variant == ATLAS_VARIANT_AUTO) {
-    // an autotuned shape for this (op, dtype, nlev), if any (for the
-    // Laplacian: the fused form, or the two passes each with its own shape)
-    MeshStore &ms = const_cast<MeshStore &>(m);
-    std::lock_guard<std::mutex> g(ms.tune_mu);
-    auto it = ms.tuned.find(TuneKey{(int)op, (int)dt, nlev});
-    if (it != ms.tuned.end()) s = it->second;
-  }
+  // an autotuned shape for this (op, dtype, nlev), if any (for the
+  // Laplacian: the fused form, or the two passes each with its own shape)
+  if (!l || l->variant == ATLAS_VARIANT_AUTO) (void)tuned_shape(m, op, nlev, dt, &s);
   if (l && l->variant != ATLAS_VARIANT_AUTO) {
     s.per_pass = 0;  // an explicit shape serves both Laplacian passes
     s.variant = l->variant;

@@ -295,6 +295,8 @@ atlas_status pack_lapl_geometry(MeshStore &m, int64_t ngrec);
 // Packs the wave-specialised sweep's per-position geometry (after
 // derive_scales; a mesh with a sweep plan).
 atlas_status pack_sweep_geometry(MeshStore &m);
+// The autotuned shape for this operator, if there is one.
+bool tuned_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt, LaunchShape *s);
 // The shape a call with launch `l` (NULL: tuned, else built-in) runs with.
 LaunchShape shape_from(const atlas_launch *l, const MeshStore &m, atlas_op op, int nlev,
                        atlas_dtype dt);

@@ -3004,13 +3004,33 @@ static SweepwPlan sweepw_plan(const MeshStore &m, int nlev, int level_chunk) {
 // wherever its pieces fill the chip.  Columns that leave room for two
 // workgroups per compute unit ask for 64 tiles (in up to six bands each;
 // O160 has 130: 37 levels, FP32 divergence 27.7 against 32 us for the column
-// form; O80 has 28: 16 against 11 us) and 1.5 M values to hide the walk's
-// latency behind (O160, 10 levels, FP64 gradient: 17.6 against 16.2 us; O200:
-// 23.3 against 26.5), longer ones and those above 48 levels (O160, 91 levels,
-// FP32 gradient: 43 against 34 us) for 600 parts and chunks of whole bands
-// (O320 has 920: 137 levels, FP64 gradient 335 against 466 us; O200 has 570:
-// FP64 divergence 195 against 190 us).
-static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int nlev,
+// form; O80 has 39: 16 against 11 us), longer ones and those above 48 levels
+// (O160, 91 levels, FP32 gradient: 43 against 34 us) for 600 pieces and chunks
+// of whole bands (O320 has 460 tiles: 920 pieces, 137 levels, FP64 gradient
+// 335 against 466 us; O200 has 194, 582 pieces: FP64 divergence 195 against
+// 190 us).
+//
+// Short columns leave it bound by what a piece costs whatever its levels: the
+// records of its nodes, 144 bytes each, which the flat form's blocks read
+// less of and share in the caches, and each tile's walk (O320 cut in 3360
+// tiles of 125 nodes: 45 us against 29.5 on its 460 own ones).  `pair`: for two
+// results (the one-pass divergence and curl, which the flat form takes twice
+// as long for: O500, 2 levels, 71 against 155 us), from its first vector on.
+// For one: from 5 levels (6 of an FP32 scalar, 4 to a vector) and a number of
+// values that grows with the tiles, FP32 scalars' a little larger (O500 FP64
+// gradient 2 levels 58 against 44 us, 4: 60 against 55, 5: 60 against 75; O320
+// FP32 gradient 4 levels 31 against 24 us, 6: 31.1 against 31.5; O160 10 levels,
+// FP64 gradient 18 against 15.3 us; O200 10 levels 22.7 against 25.8).  On
+// meshes above 1.5 M nodes, whose geometry the caches no longer hold, from
+// fewer (O640, FP32 divergence 2 levels 90 against 80 us, FP64 gradient 3 levels
+// 89 against 98; O900 2 levels 155 against 171), and vector columns in FP64 at
+// once (O1280, one level, 304 against 377 us).
+//
+// Tiles of fewer than 96 nodes are left to the other forms (O160 in tiles of
+// 61 nodes, 60 levels, FP64 gradient 46 against 33 us), and FP32 vector columns
+// above 96 levels, which take several chunks, those of fewer than 192 (O320 in
+// tiles of 125, 200 levels, divergence 391 against 370).
+static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int nlev, bool pair,
                            LaunchShape *s) {
   const DevMesh &m = ms.d;
   const bool grad = op == ATLAS_OP_GRADIENT;
@@ -3018,7 +3038,17 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
   const int nv = dt == ATLAS_F64 ? (grad ? 2 : 1) : (grad ? 4 : 2);  // levels per vector
   if (nlev < nv || m.ntiles < kSweepFewTiles) return false;
   const bool large = m.ntiles >= kSweepMinTiles;
-  if (!large && (int64_t)m.V * nlev < 1500000) return false;
+  const bool f32 = dt == ATLAS_F32;
+  const int64_t values = (int64_t)m.V * nlev, tiles = m.ntiles;
+  if (m.V < 96 * tiles || (f32 && !grad && nlev > 96 && m.V < 192 * tiles)) return false;
+  if (pair) {
+    if (!large && values < 1500000) return false;
+  } else if (m.V >= 1500000) {
+    if (values < (f32 || grad ? 3000000 : 0) + 900 * tiles) return false;
+  } else if (nlev < (f32 && grad ? 6 : 5) ||
+             values < (f32 && grad ? 1800000 : 1300000) + 900 * tiles) {
+    return false;
+  }
   const SweepwPlan p = dt == ATLAS_F64 ? (grad ? sweepw_plan<double, OP_GRAD, false>(ms, nlev, 0)
                                                : sweepw_plan<double, OP_DIV, false>(ms, nlev, 0))
                                        : (grad ? sweepw_plan<float, OP_GRAD, false>(ms, nlev, 0)
@@ -3034,6 +3064,17 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
   s->blocks_per_cu = 0;
   s->level_vec = 0;
   return true;
+}
+
+// The wave-specialised sweep needs the packed records, rows of 4..6, and runs
+// about as long as a tile's own rows: a regular grid's polar rows refer to the
+// far half of their parallel, and rings of such runs leave no room for columns
+// (F640, 20 levels: FP64 gradient 2.95 against 1.06 ms for the flat form,
+// divergence 6.3 against 1.12).
+static bool sweepw_builtin(const MeshStore &m, atlas_op op, atlas_dtype dt, int nlev, bool pair,
+                           LaunchShape *s) {
+  return m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow &&
+         max(1, m.d.segmax) * kGeoWords <= 768 && sweepw_default(m, op, dt, nlev, pair, s);
 }
 
 struct FusedwPlan {
@@ -3057,19 +3098,16 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     // neighbours from other blocks (O1280, FP32 gradient, 3 levels: 426 us at
     // 64 positions on 512 threads, 372 at 256 on 1024; one level, FP64: 333,
     // 321 at 128, 341 at 256; F640, FP64 gradient, 2 levels 190 and 170, 20
-    // levels 1059 and 992)
+    // levels 1059 and 992).  (Smaller meshes in smaller tiles: O320 one level
+    // 21.3 us, 23.8 at 128, 22.0 at 256.)
     s.block = 1024;
-    s.nodes_per_block = nlev == 1 ? 128 : 256;
+    s.nodes_per_block = nlev == 1 && m.d.V >= 750000 ? 128 : 256;
   }
+  // (the register-staged sweep; on tiles of 250 nodes O640, 60 levels, FP64
+  // gradient 1177 against 765 us for the column form)
   const bool sweep_fits = m.d.sweep_ok && m.d.ntiles >= kSweepMinTiles &&
+                          m.d.V >= 512 * (int64_t)m.d.ntiles &&
                           max(1, m.d.segmax) * kGeoWords <= 768;
-  // the wave-specialised sweep needs the packed geometry and rows of 4..6
-  // and runs about as long as a tile's own rows: a regular grid's polar rows
-  // refer to the far half of their parallel, and rings of such runs leave no
-  // room for columns (F640, 20 levels: FP64 gradient 2.95 against 1.06 ms for
-  // the flat form, divergence 6.3 against 1.12)
-  const bool sweepw_fits = packed && m.d.sgeo && !m.cuts.empty() && m.d.mindeg >= kMinRow &&
-                           max(1, m.d.segmax) * kGeoWords <= 768;
   if (op == ATLAS_OP_LAPLACIAN) {
     // the fused one-pass form, wave-specialised, where it beats the two
     // passes on their own shapes: on large meshes from 4 levels in FP64
@@ -3097,7 +3135,7 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     s.per_pass = 1;
     return s;
   }
-  if (sweepw_fits && sweepw_default(m, op, dt, nlev, &s)) return s;
+  if (packed && sweepw_builtin(m, op, dt, nlev, false, &s)) return s;
   // Without the packed records the sweep is the register-staged one: one
   // workgroup per tile and level chunk, each walking its band's parallels in
   // turn, so only a mesh of many tiles fills the chip (O160, 37 levels, FP64
@@ -3404,10 +3442,8 @@ static atlas_status launch_dtype(const MeshStore &ms, atlas_op op, const void *i
 // Shape of one Laplacian pass: the autotuned one for that operator, else the
 // built-in one.
 static LaunchShape pass_shape(const MeshStore &ms, atlas_op op, int nlev, atlas_dtype dt) {
-  MeshStore &m = const_cast<MeshStore &>(ms);
-  std::lock_guard<std::mutex> g(m.tune_mu);
-  auto it = m.tuned.find(TuneKey{(int)op, (int)dt, nlev});
-  return it != m.tuned.end() ? it->second : default_shape(ms, op, nlev, dt);
+  LaunchShape s;
+  return tuned_shape(ms, op, nlev, dt, &s) ? s : default_shape(ms, op, nlev, dt);
 }
 
 // Laplacian: gradient into the workspace [V][nlev][2], then its divergence;
@@ -3421,9 +3457,13 @@ static atlas_status launch_div_curl_typed(const MeshStore &ms, atlas_dtype dt, c
                                           int nlev, T *od, T *oc, hipStream_t st) {
   const DevMesh &m = ms.d;
   {
-    // where the divergence runs the wave-specialised sweep, the curl rides
-    // on the same loads
-    LaunchShape sh = shape_from(nullptr, ms, ATLAS_OP_DIVERGENCE, nlev, dt);
+    // where the wave-specialised sweep pays for the divergence, or for the
+    // two together, the curl rides on the same loads (a tuned divergence keeps
+    // its form)
+    LaunchShape sh;
+    if (!tuned_shape(ms, ATLAS_OP_DIVERGENCE, nlev, dt, &sh) &&
+        !sweepw_builtin(ms, ATLAS_OP_DIVERGENCE, dt, nlev, true, &sh))
+      sh = default_shape(ms, ATLAS_OP_DIVERGENCE, nlev, dt);
     if (sh.variant == ATLAS_VARIANT_SWEEP && sweepw_applies<T, OP_DIV>(m, nlev, sh)) {
       // (FP32 columns of several chunks: on large meshes only; O1280, 137
       // levels 4.93 against 5.31 ms for the column form, O320 380 against

@@ -1,7 +1,9 @@
 """d/dlon and d/dlat on both sides of their built-in forms' switches: the
 gradient's components times R cos(lat) and R.  Both sum the same terms in the
 same order, so they differ by the roundings of the scales (four products and
-quotients of one or two ulps each: 8 ulps) and of the result."""
+quotients of one or two ulps each: 8 ulps) and of the result; FP32 sums are
+fused and the FP64 reference's are not, which adds 2^-40 of the largest
+value where terms cancel."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -24,11 +26,13 @@ def test_scaled_gradient(P, N):
     scale[:, 0, 0] = torch.from_numpy(desc["cos_lat"])
     scale = 2.5 * scale.cuda()
     for nlev in (1, 19, 20, 24, 47, 48, 79, 80):
-        for dtype, bound in ((torch.float64, 8 * 2.0 ** -52), (torch.float32, 2.0 ** -23)):
+        for dtype, bound, floor in ((torch.float64, 8 * 2.0 ** -52, 0.0),
+                                    (torch.float32, 2.0 ** -23, 2.0 ** -40)):
             print(f"lonlat O{N} nlev={nlev} {dtype}", flush=True)
             g = torch.Generator(device="cuda")
             g.manual_seed(nlev)
             x = torch.randn(gm.nnodes, nlev, dtype=dtype, device="cuda", generator=g)
             want = gm.gradient(x.double()) * scale
             got = gm.gradient_lonlat(x).double()
-            assert bool(((got - want).abs() <= bound * want.abs()).all()), (nlev, dtype)
+            limit = bound * want.abs() + floor * want.abs().max()
+            assert bool(((got - want).abs() <= limit).all()), (nlev, dtype)

@@ -31,3 +31,51 @@ result = [(nlev, dt, launches(L.atlas_nabla_gradient_lonlat, m.handle, IN, nlev,
         staged = nlev >= 48 if dt == 1 else 20 <= nlev < 80
         want = "k_sweepv" if staged else "k_flat" if nlev < 24 else "k_col"
         assert want in kernel, (nlev, dt, kernel)
+
+
+def _forms(N, layout, calls):
+    return on_host(f"""
+m = P.Mesh({N}, layout={layout!r})
+result = [apply(m, op, nlev, dt)[-1][0] for op, nlev, dt in {calls!r}]
+""")
+
+
+@pytest.mark.parametrize("N,layout,calls", [
+    # (operator, levels, dtype) of calls too short for the sweep, and the
+    # shortest that take it
+    (500, None, [(0, 2, 1), (0, 4, 1), (1, 2, 0), (1, 4, 0), (0, 5, 0)]),
+    (320, None, [(0, 4, 1), (0, 5, 0), (1, 4, 0), (1, 1, 1)]),
+    (640, None, [(0, 2, 1), (1, 2, 0)]),
+    (320, (8, 16), [(0, 3, 1), (0, 8, 0), (1, 3, 0), (1, 1, 1)]),
+    (160, (8, 8), [(0, 3, 1), (0, 10, 0), (1, 20, 0), (1, 1, 1)]),
+])
+def test_short_columns_keep_the_flat_form(N, layout, calls):
+    for call, kernel in zip(calls, _forms(N, layout, calls)):
+        assert "k_flat" in kernel, (call, kernel)
+
+
+@pytest.mark.parametrize("N,layout,calls", [
+    (500, None, [(0, 5, 1), (1, 5, 1), (0, 6, 0), (1, 5, 0)]),
+    (320, None, [(0, 5, 1), (0, 6, 0), (1, 5, 0)]),
+    (640, None, [(0, 3, 1), (1, 1, 1), (1, 3, 0), (0, 4, 0)]),
+    (320, (8, 16), [(0, 20, 1), (0, 20, 0), (1, 60, 0)]),
+])
+def test_longer_columns_take_the_sweep(N, layout, calls):
+    for call, kernel in zip(calls, _forms(N, layout, calls)):
+        assert "k_sweepw" in kernel, (call, kernel)
+
+
+def test_columns_on_small_tiles_keep_the_column_form():
+    for kernel in _forms(160, (8, 8), [(0, 60, 1), (1, 137, 0), (0, 200, 1)]):
+        assert "k_col" in kernel, kernel
+
+
+def test_one_pass_divergence_and_curl_of_short_columns():
+    """Two results from one read: the sweep from the first vector."""
+    result = on_host("""
+m = P.Mesh(500)
+result = [launches(L.atlas_nabla_div_curl, m.handle, IN, nlev, dt, OUT, OUT2, None)
+          for nlev, dt in ((1, F64), (2, F64), (2, F32), (4, F32))]
+""")
+    for calls in result:
+        assert len(calls) == 1 and "k_sweepw" in calls[0][0], calls
