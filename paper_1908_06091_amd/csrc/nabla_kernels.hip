@@ -226,6 +226,9 @@ template <> struct Pol<float, OP_GRAD> {
     s.gt = use ? t.gt : s.gt;
   }
   static __device__ __forceinline__ void settle(St &s) { asm volatile("" : "+v"(s.gl), "+v"(s.gt)); }
+  // (not volatile: a volatile statement counts as a write to memory, and the
+  // uniform loads after it would become vector loads)
+  static __device__ __forceinline__ void hold(St &s) { asm("" : "+v"(s.gl), "+v"(s.gt)); }
 };
 
 template <int OP> struct PolDC32 {
@@ -263,6 +266,7 @@ template <int OP> struct PolDC32 {
     s.acc = use ? t.acc : s.acc;
   }
   static __device__ __forceinline__ void settle(St &s) { asm volatile("" : "+v"(s.acc)); }
+  static __device__ __forceinline__ void hold(St &s) { asm("" : "+v"(s.acc)); }
 };
 template <> struct Pol<float, OP_DIV> : PolDC32<OP_DIV> {};
 template <> struct Pol<float, OP_CURL> : PolDC32<OP_CURL> {};
@@ -370,15 +374,15 @@ __device__ __forceinline__ void column_group(const DevMesh &m, const typename P:
 template <class T, int OP, int NCH, int G, bool ONE_GROUP>
 __device__ __forceinline__ void column_node(const DevMesh &m, const T *__restrict__ in,
                                             T *__restrict__ out, int nlev, const PosRec &pr,
-                                            int lane) {
+                                            int k0) {
   using P = Pol<T, OP>;
   using V = typename P::V;
   const V *vin = reinterpret_cast<const V *>(in);
   const size_t L = (size_t)nlev;
   const int node = pr.node, r0 = pr.r0, r1 = pr.r1;
-  int kk[NCH];
+  int kk[NCH];  // the lane's levels k0, k0 + 64, ..., clamped to the column
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) kk[c] = min(lane + 64 * c, nlev - 1);  // clamped, in bounds
+  for (int c = 0; c < NCH; ++c) kk[c] = min(k0 + 64 * c, nlev - 1);
   const double ci = P::kVecIn ? m.coslat[node] : 0.0;
   typename P::St st[NCH];
 #pragma unroll
@@ -389,21 +393,36 @@ __device__ __forceinline__ void column_node(const DevMesh &m, const T *__restric
     for (int rb = r0; rb < r1; rb += G) column_group<P, NCH, G>(m, vin, L, kk, rb, min(G, r1 - rb), st);
   }
   const double al = pr.alpha, be = P::kVecOut ? pr.beta : 0.0;
+  // (FP32: the sums are held here.  Else they move into the branch around the
+  // store, and the normals' loads with them, behind the wait for the columns:
+  // 720x360 quadrilaterals, gradient, 37 levels 61.7 against 55.2 us)
+  if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) P::hold(st[c]);
+  }
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
-    if (lane + 64 * c < nlev) P::store(out, (size_t)node * L + lane + 64 * c, st[c], al, be);
+    if (k0 + 64 * c < nlev) P::store(out, (size_t)node * L + k0 + 64 * c, st[c], al, be);
 }
 
 template <class T, int OP, int NCH, int G>
 __device__ __forceinline__ void column_pos(const DevMesh &m, const T *__restrict__ in,
                                            T *__restrict__ out, int nlev, int p,
                                            const PosRec &pr, int lane) {
-  if (NCH > 0) {
-    // G = 6: one load group covers every row of a mesh of degree <= 6 (the
-    // octahedral mesh, pole edge included); G = 8: rows in groups
-    column_node<T, OP, (NCH > 0 ? NCH : 1), G, G == 6>(m, in, out, nlev, pr, lane);
+  // G = 6: one load group covers every row of a mesh of degree <= 6 (the
+  // octahedral mesh, pole edge included); G = 8: rows in groups
+  if constexpr (NCH > 0) {
+    column_node<T, OP, NCH, G, G == 6>(m, in, out, nlev, pr, lane);
+  } else if constexpr (sizeof(T) == 4) {
+    // any nlev: 256 levels at a time (vector columns 192; 64 at a time, each
+    // incidence's loads waited for on their own, 720x360 quadrilaterals, 300
+    // levels, took 451 us for the gradient and 476 for the divergence, 271 and
+    // 434 this way)
+    constexpr int N = Pol<T, OP>::kVecIn ? 3 : 4;
+    for (int k0 = lane; k0 - lane < nlev; k0 += 64 * N)
+      column_node<T, OP, N, G, G == 6>(m, in, out, nlev, pr, k0);
   } else {
-    // any nlev: chunks of 64 levels one after another
+    // any nlev: 64 levels after another (256 at a time: 721 against 590 us)
     for (int k = lane; k < nlev; k += 64) element<T, OP>(m, in, out, nlev, p, pr.node, pr.r0, pr.r1, k);
   }
 }
@@ -881,7 +900,9 @@ __global__ void __launch_bounds__(512)
 // weigh more against half the bytes): the width (1..4 levels, at most 32 bytes per
 // lane) that needs the fewest level slots per lane (NV x chunks of 64
 // lanes; the arithmetic runs once per slot), then the fewest load
-// instructions per column.  `want` > 0 forces a width.  0 when the form
+// instructions per column, then one chunk (193 to 256 levels of a vector
+// column on four levels per lane or two chunks of two: F640, 200 levels,
+// divergence 2713 against 3373 us).  `want` > 0 forces a width.  0 when the form
 // does not apply (mesh degree above 6 or a row shorter than kMinRow, no
 // width fitting the column, more than 4 chunks) and the one-level-per-lane
 // column kernel runs instead.
@@ -898,7 +919,8 @@ __host__ __device__ inline int auto_level_vec(int nlev, int maxdeg, int mindeg, 
     const int bytes = nv * vb;
     const int pieces = bytes / 16 + ((bytes % 16) ? 1 : 0);  // 16/12/8/4-byte accesses
     const int slots = nv * nch, loads = nch * pieces;
-    if (slots < best_slots || (slots == best_slots && loads < best_loads)) {
+    if (slots < best_slots ||
+        (slots == best_slots && (loads < best_loads || (loads == best_loads && nch == 1)))) {
       best = nv;
       best_slots = slots;
       best_loads = loads;
@@ -2893,8 +2915,8 @@ size_t flux_ws_bytes(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt) 
 // column form over blocks of 16 consecutive positions (a run of one parallel,
 // so the neighbour columns of consecutive blocks overlap in L2), at the
 // automatic lane-vector width except the FP64 gradient to 47 levels and the
-// FP32 one above (one level per lane).  The Laplacian takes the fused form or
-// each pass's own shape.
+// FP32 one from there to 256 (one level per lane).  The Laplacian takes the
+// fused form or each pass's own shape.
 constexpr size_t kMaxLds = 160 * 1024;
 
 // How the wave-specialised sweep runs a column: the cut of the tiles, the
@@ -3040,7 +3062,9 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
   const bool large = m.ntiles >= kSweepMinTiles;
   const bool f32 = dt == ATLAS_F32;
   const int64_t values = (int64_t)m.V * nlev, tiles = m.ntiles;
-  if (m.V < 96 * tiles || (f32 && !grad && nlev > 96 && m.V < 192 * tiles)) return false;
+  // (the one pass over 20 to 47 levels, which has no column form, on smaller
+  // tiles too: O160 in tiles of 61 nodes, 37 levels, FP64 58 against 69 us)
+  if (m.V < (pair && nlev >= 20 && nlev < 48 ? 48 : 96) * tiles || (f32 && !grad && nlev > 96 && m.V < 192 * tiles)) return false;
   if (pair) {
     if (!large && values < 1500000) return false;
   } else if (m.V >= 1500000) {
@@ -3161,7 +3185,10 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     }
     return s;
   }
-  if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT) s.level_vec = 1;
+  // FP32 gradient: one level per lane to 256 levels (F640, 137 levels, 1566
+  // against 1652 us on lane vectors, 256: 2692 against 2945); above, that form
+  // walks the column in single steps (300: 7765 against 4222)
+  if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT && nlev <= 256) s.level_vec = 1;
   if (dt == ATLAS_F64 && op == ATLAS_OP_GRADIENT && sweep_fits) {
     // (O1280: 64 levels 2953 against 3205 us for the column form, 137: 5891
     // against 7185)
@@ -3469,7 +3496,7 @@ static atlas_status launch_div_curl_typed(const MeshStore &ms, atlas_dtype dt, c
       // levels 4.93 against 5.31 ms for the column form, O320 380 against
       // 345 us)
       const SweepwPlan p = sweepw_plan<T, OP_DIV, true>(ms, nlev, sh.level_chunk);
-      if (p.lds <= kMaxLds && (p.nchunk == 1 || sizeof(T) == 8 || m.ntiles >= kSweepMinTiles)) {
+      if (p.lds <= kMaxLds && (p.nchunk == 1 || sizeof(T) == 8 || m.V >= 750000)) {
         sh.block = max(512, p.block);
         return launch_sweepw<T, OP_DIV, true>(ms, in, od, oc, nlev, sh, st);
       }

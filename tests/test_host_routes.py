@@ -79,3 +79,17 @@ result = [launches(L.atlas_nabla_div_curl, m.handle, IN, nlev, dt, OUT, OUT2, No
 """)
     for calls in result:
         assert len(calls) == 1 and "k_sweepw" in calls[0][0], calls
+
+
+def test_long_fp32_columns_on_lane_vectors():
+    """FP32 vector columns of 193 to 256 levels in one chunk of four levels
+    per lane; FP32 gradients above 256 levels on lane vectors."""
+    result = on_host("""
+m = P.Mesh(nx=P.regular_gaussian_nx(24))
+result = [apply(m, op, nlev, F32)[0][0] for op, nlev in ((DIV, 193), (CURL, 256), (GRAD, 257), (GRAD, 300))]
+result.append(launches(L.atlas_nabla_div_curl, m.handle, IN, 200, F32, OUT, OUT2, None)[0][0])
+""")
+    div, curl, g257, g300, both = result
+    assert "k_colvIfLi1ELi4ELi1E" in div and "k_colvIfLi2ELi4ELi1E" in curl
+    assert "k_colvIfLi0E" in g257 and "k_colvIfLi0E" in g300
+    assert "k_colv_dcIfLi4ELi1E" in both
