@@ -3078,8 +3078,10 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
                                        : (grad ? sweepw_plan<float, OP_GRAD, false>(ms, nlev, 0)
                                                : sweepw_plan<float, OP_DIV, false>(ms, nlev, 0));
   if (p.lds > kMaxLds) return false;
+  // (FP32 columns of several chunks fill the chip no better than one: O200,
+  // 582 parts, 220 levels, divergence 180 against 151 us for the column form)
   if (!large && (nlev > 48 || 2 * p.lds > kMaxLds) &&
-      m.ntiles * ms.cuts[p.cut].parts * p.nchunk < 600)
+      m.ntiles * ms.cuts[p.cut].parts * (f32 ? 1 : p.nchunk) < 600)
     return false;
   s->variant = ATLAS_VARIANT_SWEEP;
   s->block = max(512, p.block);
@@ -3138,15 +3140,20 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     // (O1280, 10 levels: 1.03 against 1.09 ms, 137: 7.2 against 9.4) and from
     // 33 in FP32 (24 levels: 1.46 against 1.22 ms, 40: 1.78 against 1.75,
     // 63: 2.19 against 3.15, 137: 4.85 against 5.65; it needs no workspace);
-    // on small ones with work enough to hide its longer walk (FP64: O160, 137
-    // levels, 187 against 245 us, 37 levels 77 against 62; O320, 37 levels,
-    // 158 against 291; FP32: O240, 137 levels, 254 against 291, O160 151
-    // against 122)
+    // on small ones with work enough to hide its longer walk and pieces enough
+    // to fill the chip (FP64: O320, 37 levels, 158 against 291 us; O200 has 194
+    // tiles: 60 levels 119 against 140; O160 130: 80 levels 119 against 113, 100
+    // 157 against 137, 137 levels, which the passes' columns take in three chunks
+    // of lanes, 187 against 245; O120 79: 129 levels 111 against 106, 170 118
+    // against 141; FP32: O320, 80 levels 268 against 363; O256 has
+    // 304: 120 levels 223 against 274; O200, 200 levels, 305 against 280, 300 349
+    // against 643; O160 151 against 122)
     const bool f64 = dt == ATLAS_F64;
     const int64_t values = (int64_t)m.d.V * nlev;
-    const bool worth = m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 33)
-                       : f64                        ? values >= 5000000
-                                                    : values >= 25000000 && nlev >= 64;
+    const bool worth =
+        m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 33)
+        : f64 ? values >= 5000000 && (m.d.ntiles >= 180 || nlev > (m.d.ntiles >= 100 ? 128 : 160))
+              : values >= (m.d.ntiles >= 300 ? 25000000 : 36000000) && nlev >= 64;
     FusedwPlan fw;
     LaunchShape fs;
     fs.variant = ATLAS_VARIANT_FUSED;
@@ -3599,7 +3606,8 @@ static bool fused_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fus
 // The wave-specialised fused Laplacian's plan (blocks_per_cu 0, 16-byte
 // vectors, at least one consumer wavefront): the cut of the tiles with the
 // fewest level chunks (then the fewest parts, then the fewest steps until
-// the last round of workgroups is done); false where none fits in LDS.
+// the last round of workgroups is done), and chunks for two workgroups per
+// compute unit before that; false where none fits in LDS.
 // (nodes_per_block 4 and 5 chose a ring in earlier forms and are taken as 0.)
 template <class T>
 static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, FusedwPlan *fp) {
@@ -3619,6 +3627,7 @@ static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fu
   const int cus = device_cu_count();
   int64_t best_steps = 0;
   bool any = false;
+  bool two = false;  // the plan so far lets two workgroups share a compute unit
   for (size_t k = 0; k < ms.lcuts.size(); ++k) {
     const LaplView &v = ms.lcuts[k];
     auto bytes = [&](int c) {
@@ -3628,30 +3637,59 @@ static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fu
                            (size_t)kLswRefSlots * (v.gmax + v.pmax)) +
              (sizeof(T) == 4 ? (size_t)8 * kLswGradSlots * v.gmax : 0) + kSweepwLdsTail;
     };
-    FusedwPlan p;
-    p.cut = (int)k;
-    p.vpc = min(min(want, most), nvec);
-    p.nchunk = (nvec + p.vpc - 1) / p.vpc;
-    p.vpc = (nvec + p.nchunk - 1) / p.nchunk;
     // (a field run is loaded by one wavefront's kRunLoads instructions)
     auto fits = [&](int c) {
       return bytes(c) <= kMaxLds && v.fmax * c <= kRunLoads * 64 * kLswGroupWaves;
     };
-    while (p.vpc > 1 && !fits(p.vpc)) {
-      ++p.nchunk;
-      p.vpc = (nvec + p.nchunk - 1) / p.nchunk;
+    int vpc = min(min(want, most), nvec);
+    int nchunk = (nvec + vpc - 1) / vpc;
+    vpc = (nvec + nchunk - 1) / nchunk;
+    while (vpc > 1 && !fits(vpc)) {
+      ++nchunk;
+      vpc = (nvec + nchunk - 1) / nchunk;
     }
-    p.nchunk = (nvec + p.vpc - 1) / p.vpc;
-    p.lds = bytes(p.vpc);
-    if (!fits(p.vpc)) continue;
-    if (any && (p.nchunk > fp->nchunk ||
-                (p.nchunk == fp->nchunk && v.parts > ms.lcuts[fp->cut].parts)))
+    nchunk = (nvec + vpc - 1) / vpc;
+    if (!fits(vpc)) continue;
+    // One workgroup on a compute unit waits out each step's barrier and
+    // loads; two of eight wavefronts hide them.  A column that one or two more
+    // chunks bring down to 13 to 16 vectors (two elements on 16 lanes; 17 and
+    // 18 leave a third of the lanes idle) takes them, on the cut where two
+    // such workgroups fit (O1280: FP64, 80 levels in three chunks of 14 on half
+    // tiles 4.47 ms, two of 20 5.60; 60 levels 3.02 against 3.19, 120 5.96 against
+    // 6.41; 100 levels in three of 17 8.01 against 6.36, in four of 13 5.96; FP32,
+    // 170 levels 5.82 against 7.04, 100 3.91 against 4.20).
+    bool pair = false;
+    if (sh.level_chunk == 0 && 2 * bytes(vpc) > kMaxLds) {
+      for (int n = nchunk + 1; n <= nchunk + 2 && !pair; ++n) {
+        const int c = (nvec + n - 1) / n;
+        if (c >= 13 && c <= 16 && fits(c) && 2 * bytes(c) <= kMaxLds) {
+          vpc = c;
+          pair = true;
+        }
+      }
+      if (pair) nchunk = (nvec + vpc - 1) / vpc;
+    }
+    FusedwPlan p;
+    p.cut = (int)k;
+    p.vpc = vpc;
+    p.nchunk = nchunk;
+    p.lds = bytes(vpc);
+    const bool better = !any || pair > two ||
+                        (pair == two && (nchunk < fp->nchunk ||
+                                         (nchunk == fp->nchunk &&
+                                          v.parts < ms.lcuts[fp->cut].parts)));
+    if (!better && (pair < two || nchunk > fp->nchunk || v.parts > ms.lcuts[fp->cut].parts))
       continue;
+    // Lanes per position and elements per lane: the cheapest pair that holds
+    // the chunk, as in the sweep -- but not eight lanes with four elements or
+    // more: eight positions a wavefront leave a run of 34 to four or five of
+    // the wavefronts, each with a long chain (O1280, 30 levels, 1.91 ms, on 16
+    // lanes 1.60; O500, 37 levels, 522 against 468 us).
     const int nel = p.vpc * 2;
     int cost = INT_MAX;
     for (int l : {8, 16, 32}) {
       const int e = (nel + l - 1) / l;
-      if (e <= kLswMaxNe && (e + 3) * l < cost) {
+      if (e <= (l == 8 ? 3 : kLswMaxNe) && (e + 3) * l < cost) {
         cost = (e + 3) * l;
         p.lpn = l;
         p.ne = e;
@@ -3659,14 +3697,14 @@ static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fu
     }
     const int npn = 64 / p.lpn;
     const int tasks = (v.gmax + npn - 1) / npn + (v.pmax + npn - 1) / npn;
-    p.block = min(kLswBlock, 64 * (kLswProducers + tasks));
+    p.block = pair ? 512 : min(kLswBlock, 64 * (kLswProducers + tasks));
     const int64_t places = (int64_t)cus * max(1, min((int)(kMaxLds / p.lds), 1024 / p.block));
     const int64_t steps =
         ((int64_t)v.ntiles * p.nchunk + places - 1) / places * (v.rings + 6);
-    if (!any || p.nchunk < fp->nchunk || v.parts < ms.lcuts[fp->cut].parts ||
-        steps < best_steps) {
+    if (better || steps < best_steps) {
       *fp = p;
       best_steps = steps;
+      two = pair;
       any = true;
     }
   }

@@ -89,7 +89,44 @@ m = P.Mesh(nx=P.regular_gaussian_nx(24))
 result = [apply(m, op, nlev, F32)[0][0] for op, nlev in ((DIV, 193), (CURL, 256), (GRAD, 257), (GRAD, 300))]
 result.append(launches(L.atlas_nabla_div_curl, m.handle, IN, 200, F32, OUT, OUT2, None)[0][0])
 """)
-    div, curl, g257, g300, both = result
+    result.append(_forms(200, None, [(1, 220, 0)])[0])
+    div, curl, g257, g300, both, o200 = result
+    assert "k_colvIfLi1ELi4ELi1E" in o200
     assert "k_colvIfLi1ELi4ELi1E" in div and "k_colvIfLi2ELi4ELi1E" in curl
     assert "k_colvIfLi0E" in g257 and "k_colvIfLi0E" in g300
     assert "k_colv_dcIfLi4ELi1E" in both
+
+
+@pytest.mark.parametrize("N,nlev,dt,lanes,elements,pieces,lds", [
+    # chunks of 13 to 16 vectors, two workgroups to a compute unit: on half
+    # tiles, two elements on 16 lanes
+    (640, 80, 1, 16, 2, 3440 * 3, 68320),
+    (640, 60, 1, 16, 2, 3440 * 2, 72224),
+    (640, 120, 1, 16, 2, 3440 * 4, 72224),
+    (640, 100, 1, 16, 2, 3440 * 4, 64416),
+    (640, 170, 0, 16, 2, 3440 * 3, 72800),
+    # 72 levels would leave chunks of 12
+    (640, 72, 1, 16, 5, 3440, 154208),
+    # not eight lanes with four or five elements
+    (640, 30, 1, 16, 2, 1720, 133920),
+    (640, 80, 0, 16, 3, 3440, 92320),
+])
+def test_fused_laplacian_chunks(N, nlev, dt, lanes, elements, pieces, lds):
+    (name, blocks, threads, used), = on_host(f"""
+m = P.Mesh({N})
+result = apply(m, LAPL, {nlev}, {dt})
+""")
+    assert f"k_lsweepwI{'d' if dt else 'f'}Li{lanes}ELi{elements}E" in name
+    assert (blocks, used) == ((pieces + 7) // 8 * 8, lds)
+    assert threads == 512 or 2 * lds > 160 * 1024
+
+
+@pytest.mark.parametrize("N,nlev,dt,fused", [
+    (160, 47, 1, False), (160, 80, 1, False), (160, 128, 1, False), (160, 129, 1, True),
+    (120, 100, 1, False), (120, 160, 1, False), (120, 161, 1, True),
+    (200, 60, 1, True), (320, 37, 1, True),
+    (200, 170, 0, False), (200, 300, 0, True), (320, 80, 0, True), (256, 137, 0, True),
+])
+def test_fused_laplacian_on_few_tiles(N, nlev, dt, fused):
+    names = [k[0] for k in on_host(f"m = P.Mesh({N})\nresult = apply(m, LAPL, {nlev}, {dt})")]
+    assert len(names) == (1 if fused else 2) and ("k_lsweepw" in names[0]) == fused, names
