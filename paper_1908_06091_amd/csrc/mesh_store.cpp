@@ -193,11 +193,12 @@ static void processing_order(const atlas_mesh_desc *d, int band, int width,
   }
 }
 
-// Work over `n` items on the host's threads: how many to use (a few
-// thousand items each at least), and fn(w) for w = 0 .. count - 1 on them.
+// Work over `n` tiles on the host's threads: how many to use (eight tiles each
+// at least, some eight thousand nodes), and fn(w) for w = 0 .. count - 1 on
+// them.
 static int host_threads(int64_t n) {
   const int64_t hw = std::max(1u, std::thread::hardware_concurrency());
-  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(hw, 16), n / 64));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(hw, 16), n / 8));
 }
 template <class F>
 static void on_threads(int count, const F &fn) {
@@ -222,6 +223,53 @@ static void on_threads(int count, const F &fn) {
   for (auto &e : err)
     if (e) std::rethrow_exception(e);
 }
+
+// Indices of nodes on a parallel, as bits: a plan adds every neighbour of a
+// tile's nodes, each some seven times over, and asks for the run that holds
+// them (lists sorted and made unique took most of an upload).
+struct RunSet {
+  std::vector<uint64_t> bits;
+  std::vector<int32_t> words;  // the words with bits set
+  void add(int32_t i) {
+    const size_t w = (size_t)i >> 6;
+    if (w >= bits.size()) bits.resize(w + 1, 0);
+    if (!bits[w]) words.push_back((int32_t)w);
+    bits[w] |= (uint64_t)1 << (i & 63);
+  }
+  // The shortest cyclic run of a parallel of nx nodes that holds the indices,
+  // the complement of their widest gap; the set is empty afterwards.  False
+  // if the run's slots would not fit 16 bits.
+  bool run(int32_t nx, int32_t &lo, int32_t &len) {
+    std::sort(words.begin(), words.end());
+    int32_t count = 0, first = 0, last = 0, best = -1, after = 0;
+    for (int32_t w : words) {
+      for (uint64_t b = bits[w]; b; b &= b - 1) {
+        const int32_t i = w * 64 + __builtin_ctzll(b);
+        if (count++ == 0) {
+          first = i;
+        } else if (i - last > best) {
+          best = i - last;
+          after = i;
+        }
+        last = i;
+      }
+      bits[w] = 0;
+    }
+    words.clear();
+    if (count == 0 || count == nx) {
+      lo = 0;
+      len = count;
+    } else {
+      if (first + nx - last > best) {
+        best = first + nx - last;
+        after = first;
+      }
+      lo = after;
+      len = nx - best + 1;
+    }
+    return len < 65536;
+  }
+};
 
 // Parallel-sweep plan.  For every tile: the parallels it owns plus one
 // above and one below, each reduced to the shortest cyclic run of nodes that
@@ -249,7 +297,7 @@ static bool sweep_plan(const std::vector<int64_t> &off, const std::vector<int32_
   sp.tile_seg.assign(1, 0);
   sp.selfslot.assign(V, 0);
   sp.lref.assign(nbr.size(), -1);
-  std::vector<std::vector<int32_t>> need;
+  std::vector<RunSet> need;
   for (int64_t t = 0; t < T; ++t) {
     const int32_t p0 = tile_ptr[t], p1 = tile_ptr[t + 1];
     int32_t jmin = INT32_MAX, jmax = -1;
@@ -261,38 +309,23 @@ static bool sweep_plan(const std::vector<int64_t> &off, const std::vector<int32_
     }
     const int32_t rlo = std::max<int32_t>(0, jmin - 1);
     const int32_t rhi = std::min<int32_t>((int32_t)nr - 1, jmax + 1);
-    need.assign(rhi - rlo + 1, {});
+    if ((int64_t)need.size() < rhi - rlo + 1) need.resize(rhi - rlo + 1);
     std::vector<int2> pos(rhi - rlo + 1, make_int2(0, 0));
     for (int32_t p = p0; p < p1; ++p) {
       const int32_t i = perm[p], j = ring_of[i];
-      need[j - rlo].push_back((int32_t)(i - off[j]));
+      need[j - rlo].add((int32_t)(i - off[j]));
       if (pos[j - rlo].y == 0) pos[j - rlo] = make_int2(p, p + 1);
       else pos[j - rlo].y = p + 1;
       for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r) {
         const int32_t n = (int32_t)((uint32_t)nbr[r] & ~kPoleBit), jn = ring_of[n];
         if (jn < j - 1 || jn > j + 1) return false;
-        need[jn - rlo].push_back((int32_t)(n - off[jn]));
+        need[jn - rlo].add((int32_t)(n - off[jn]));
       }
     }
     std::vector<int32_t> lo(rhi - rlo + 1), len(rhi - rlo + 1);
     for (int32_t q = 0; q <= rhi - rlo; ++q) {
       const int32_t nx = (int32_t)(off[rlo + q + 1] - off[rlo + q]);
-      auto &a = need[q];
-      std::sort(a.begin(), a.end());
-      a.erase(std::unique(a.begin(), a.end()), a.end());
-      if (a.empty()) { lo[q] = 0; len[q] = 0; }
-      else if ((int32_t)a.size() == nx) { lo[q] = 0; len[q] = nx; }
-      else {
-        // the run is the complement of the widest cyclic gap
-        int32_t best = -1, at = 0;
-        for (size_t k = 0; k < a.size(); ++k) {
-          const int32_t g = (k + 1 < a.size()) ? a[k + 1] - a[k] : a[0] + nx - a[k];
-          if (g > best) { best = g; at = (int32_t)k; }
-        }
-        lo[q] = a[(at + 1) % a.size()];
-        len[q] = nx - best + 1;
-      }
-      if (len[q] >= 65536) return false;
+      if (!need[q].run(nx, lo[q], len[q])) return false;
       sp.segmax = std::max(sp.segmax, len[q]);
       sp.seg.push_back(make_int4((int32_t)off[rlo + q], nx, lo[q], len[q]));
       sp.seg_pos.push_back(pos[q]);
@@ -318,32 +351,6 @@ static bool sweep_plan(const std::vector<int64_t> &off, const std::vector<int32_
     }
   }
   return true;
-}
-
-// The shortest cyclic run of a parallel of nx nodes that holds the indices
-// `a` (sorted here).
-static bool cyclic_run(std::vector<int32_t> &a, int32_t nx, int32_t &lo, int32_t &len) {
-  std::sort(a.begin(), a.end());
-  a.erase(std::unique(a.begin(), a.end()), a.end());
-  if (a.empty()) {
-    lo = 0;
-    len = 0;
-  } else if ((int32_t)a.size() == nx) {
-    lo = 0;
-    len = nx;
-  } else {
-    int32_t best = -1, at = 0;  // the run is the complement of the widest gap
-    for (size_t k = 0; k < a.size(); ++k) {
-      const int32_t g = (k + 1 < a.size()) ? a[k + 1] - a[k] : a[0] + nx - a[k];
-      if (g > best) {
-        best = g;
-        at = (int32_t)k;
-      }
-    }
-    lo = a[(at + 1) % a.size()];
-    len = nx - best + 1;
-  }
-  return len < 65536;
 }
 
 // The sweep's tiles cut into `parts` longitude parts (part k owns the k-th
@@ -379,7 +386,7 @@ static bool cut_plan(const std::vector<int64_t> &off, const std::vector<int32_t>
   auto runs = [&](int w) {
     Part &o = done[w];
     std::vector<int2> own, pos;
-    std::vector<std::vector<int32_t>> need;
+    std::vector<RunSet> need;
     for (int64_t t = T * w / nthr; t < T * (w + 1) / nthr && o.ok; ++t) {
       // the tile's positions on each of its parallels
       const int32_t j0 = ring_of[perm[tile_ptr[t]]];
@@ -395,7 +402,7 @@ static bool cut_plan(const std::vector<int64_t> &off, const std::vector<int32_t>
         const int32_t qa = (int32_t)(nq * b / bands), qb = (int32_t)(nq * (b + 1) / bands);
         o.rings = std::max(o.rings, qb - qa);
         const int32_t rlo = std::max(0, j0 + qa - 1), rhi = std::min(nr - 1, j0 + qb);
-        need.assign(rhi - rlo + 1, {});
+        if ((int64_t)need.size() < rhi - rlo + 1) need.resize(rhi - rlo + 1);
         pos.assign(rhi - rlo + 1, make_int2(0, 0));
         for (int32_t q = qa; q < qb; ++q) {
           const int32_t n = own[q].y - own[q].x;
@@ -404,17 +411,17 @@ static bool cut_plan(const std::vector<int64_t> &off, const std::vector<int32_t>
           pos[j0 + q - rlo] = pr;
           o.pmax = std::max(o.pmax, pr.y - pr.x);
           for (int32_t p = pr.x; p < pr.y; ++p) {
-            need[j0 + q - rlo].push_back((int32_t)(perm[p] - off[j0 + q]));
+            need[j0 + q - rlo].add((int32_t)(perm[p] - off[j0 + q]));
             if (rowp[p + 1] - rowp[p] > 6) o.ok = false;
             for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r)
-              need[ring_of[nb(r)] - rlo].push_back((int32_t)(nb(r) - off[ring_of[nb(r)]]));
+              need[ring_of[nb(r)] - rlo].add((int32_t)(nb(r) - off[ring_of[nb(r)]]));
           }
         }
         o.nseg.push_back(rhi - rlo + 1);
         for (int32_t q = 0; q <= rhi - rlo; ++q) {
           const int32_t nx = (int32_t)(off[rlo + q + 1] - off[rlo + q]);
           int32_t lo = 0, len = 0;
-          if (!cyclic_run(need[q], nx, lo, len)) o.ok = false;
+          if (!need[q].run(nx, lo, len)) o.ok = false;
           o.segmax = std::max(o.segmax, len);
           o.seg.push_back(make_int4((int32_t)off[rlo + q], nx, lo, len));
           o.seg_pos.push_back(pos[q]);
@@ -494,20 +501,18 @@ struct LaplPlan {
   int32_t fmax = 0, gmax = 0, pmax = 0;
 };
 
-static bool lapl_plan(const std::vector<int64_t> &off, const std::vector<int32_t> &perm,
+static bool lapl_plan(const std::vector<int64_t> &off, const std::vector<int32_t> &ring_of,
+                      const std::vector<int32_t> &perm, const std::vector<int32_t> &inv,
                       const std::vector<int32_t> &tile_ptr, const std::vector<int32_t> &rowp,
                       const std::vector<int32_t> &nbr, LaplPlan &lp) {
   const int64_t V = (int64_t)perm.size();
   const int32_t nr = (int32_t)off.size() - 1;
-  std::vector<int32_t> ring_of(V), inv(V);
-  for (int32_t j = 0; j < nr; ++j)
-    for (int64_t i = off[j]; i < off[j + 1]; ++i) ring_of[i] = j;
-  for (int64_t p = 0; p < V; ++p) inv[perm[p]] = (int32_t)p;
   const int64_t T = (int64_t)tile_ptr.size() - 1;
   lp.tile_seg.assign(1, 0);
   lp.lref.assign(nbr.size(), 1 << 16);
   lp.lself.assign(V, 0);
   auto nb = [&](int32_t r) { return (int32_t)((uint32_t)nbr[r] & ~kPoleBit); };
+  std::vector<RunSet> gneed, fneed;
   for (int64_t t = 0; t < T; ++t) {
     const int32_t p0 = tile_ptr[t], p1 = tile_ptr[t + 1];
     int32_t ja = INT32_MAX, jb = -1;
@@ -519,40 +524,43 @@ static bool lapl_plan(const std::vector<int64_t> &off, const std::vector<int32_t
     }
     const int32_t rlo = std::max(0, ja - 2), rhi = std::min(nr - 1, jb + 2);
     const int32_t W = rhi - rlo + 1;
-    std::vector<std::vector<int32_t>> gneed(W), fneed(W);
+    if ((int64_t)gneed.size() < W) {
+      gneed.resize(W);
+      fneed.resize(W);
+    }
     std::vector<int2> pos(W, make_int2(0, 0));
     auto local = [&](int32_t node) { return (int32_t)(node - off[ring_of[node]]); };
     for (int32_t p = p0; p < p1; ++p) {
       const int32_t i = perm[p], j = ring_of[i];
-      gneed[j - rlo].push_back(local(i));
+      gneed[j - rlo].add(local(i));
       if (pos[j - rlo].y == 0) pos[j - rlo] = make_int2(p, p + 1);
       else pos[j - rlo].y = p + 1;
       for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r) {
         const int32_t n = nb(r), jn = ring_of[n];
         if (jn < j - 1 || jn > j + 1) return false;
-        gneed[jn - rlo].push_back(local(n));
+        gneed[jn - rlo].add(local(n));
       }
     }
     std::vector<int32_t> glo(W), glen(W), flo(W), flen(W);
     for (int32_t q = 0; q < W; ++q) {
       const int32_t nx = (int32_t)(off[rlo + q + 1] - off[rlo + q]);
-      if (!cyclic_run(gneed[q], nx, glo[q], glen[q])) return false;
+      if (!gneed[q].run(nx, glo[q], glen[q])) return false;
       // every node of the g-run gets a gradient: its field and its
       // neighbours' fields are read
       for (int32_t s = 0; s < glen[q]; ++s) {
         const int32_t i = (int32_t)off[rlo + q] + (glo[q] + s) % nx;
         const int32_t p = inv[i], j = rlo + q;
-        fneed[q].push_back(local(i));
+        fneed[q].add(local(i));
         for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r) {
           const int32_t n = nb(r), jn = ring_of[n];
           if (jn < j - 1 || jn > j + 1 || jn < rlo || jn > rhi) return false;
-          fneed[jn - rlo].push_back(local(n));
+          fneed[jn - rlo].add(local(n));
         }
       }
     }
     for (int32_t q = 0; q < W; ++q) {
       const int32_t nx = (int32_t)(off[rlo + q + 1] - off[rlo + q]);
-      if (!cyclic_run(fneed[q], nx, flo[q], flen[q])) return false;
+      if (!fneed[q].run(nx, flo[q], flen[q])) return false;
     }
     auto fslot = [&](int32_t node) {
       const int32_t q = ring_of[node] - rlo;
@@ -643,7 +651,7 @@ static bool lapl_cut_plan(const std::vector<int64_t> &off, const std::vector<int
   on_threads(nthr, [&](int w) {
     Part &o = done[w];
     std::vector<int2> own;
-    std::vector<std::vector<int32_t>> gneed, fneed;
+    std::vector<RunSet> gneed, fneed;
     for (int64_t t = T * w / nthr; t < T * (w + 1) / nthr && o.ok; ++t) {
       const int32_t j0 = ring_of[perm[tile_ptr[t]]];
       own.clear();
@@ -659,8 +667,10 @@ static bool lapl_cut_plan(const std::vector<int64_t> &off, const std::vector<int
         o.rings = std::max(o.rings, qb - qa);
         const int32_t rlo = std::max(0, j0 + qa - 2), rhi = std::min(nr - 1, j0 + qb + 1);
         const int32_t W = rhi - rlo + 1;
-        gneed.assign(W, {});
-        fneed.assign(W, {});
+        if ((int64_t)gneed.size() < W) {
+          gneed.resize(W);
+          fneed.resize(W);
+        }
         const size_t s0 = o.seg_pos.size();
         for (int32_t q = 0; q < W; ++q) o.seg_pos.push_back(make_int2(0, 0));
         for (int32_t q = qa; q < qb; ++q) {
@@ -670,24 +680,24 @@ static bool lapl_cut_plan(const std::vector<int64_t> &off, const std::vector<int
           o.seg_pos[s0 + j - rlo] = pr;
           o.pmax = std::max(o.pmax, pr.y - pr.x);
           for (int32_t p = pr.x; p < pr.y; ++p) {
-            gneed[j - rlo].push_back((int32_t)(perm[p] - off[j]));
+            gneed[j - rlo].add((int32_t)(perm[p] - off[j]));
             for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r)  // (no pole edge in a divergence)
               if (!((uint32_t)nbr[r] & kPoleBit))
-                gneed[ring_of[nb(r)] - rlo].push_back((int32_t)(nb(r) - off[ring_of[nb(r)]]));
+                gneed[ring_of[nb(r)] - rlo].add((int32_t)(nb(r) - off[ring_of[nb(r)]]));
           }
         }
         o.nseg.push_back(W);
         for (int32_t q = 0; q < W; ++q) {
           const int32_t j = rlo + q, nx = (int32_t)(off[j + 1] - off[j]);
           int32_t lo = 0, len = 0;
-          if (!cyclic_run(gneed[q], nx, lo, len)) o.ok = false;
+          if (!gneed[q].run(nx, lo, len)) o.ok = false;
           o.gmax = std::max(o.gmax, len);
           o.gseg.push_back(make_int4(lo, len, o.ng, 0));
           o.ng += len;
           // every node of the g-run gets a gradient
           for (int32_t s = 0; s < len; ++s) {
             const int32_t i = (int32_t)off[j] + (lo + s) % nx, p = inv[i];
-            fneed[q].push_back(i - (int32_t)off[j]);
+            fneed[q].add(i - (int32_t)off[j]);
             if (rowp[p + 1] - rowp[p] > 6) o.ok = false;
             for (int32_t r = rowp[p]; r < rowp[p + 1]; ++r) {
               const int32_t jn = ring_of[nb(r)];
@@ -695,14 +705,14 @@ static bool lapl_cut_plan(const std::vector<int64_t> &off, const std::vector<int
                 o.ok = false;
                 break;
               }
-              fneed[jn - rlo].push_back((int32_t)(nb(r) - off[jn]));
+              fneed[jn - rlo].add((int32_t)(nb(r) - off[jn]));
             }
           }
         }
         for (int32_t q = 0; q < W; ++q) {
           const int32_t nx = (int32_t)(off[rlo + q + 1] - off[rlo + q]);
           int32_t lo = 0, len = 0;
-          if (!cyclic_run(fneed[q], nx, lo, len)) o.ok = false;
+          if (!fneed[q].run(nx, lo, len)) o.ok = false;
           o.fmax = std::max(o.fmax, len);
           o.fseg.push_back(make_int4((int32_t)off[rlo + q], nx, lo, len));
         }
@@ -767,18 +777,60 @@ static bool lapl_cut_plan(const std::vector<int64_t> &off, const std::vector<int
   return true;
 }
 
-template <class T>
-static atlas_status upload_array(MeshStore &m, const std::vector<T> &h, const T **dptr) {
-  void *p = nullptr;
-  const size_t bytes = std::max<size_t>(1, h.size() * sizeof(T));
-  hipError_t e = hipMalloc(&p, bytes);
-  if (e != hipSuccess) return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
-  m.allocations.push_back(p);
-  m.bytes += bytes;
-  if (!h.empty()) ATLASX_HIP(hipMemcpy(p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
-  *dptr = static_cast<const T *>(p);
-  return ATLAS_OK;
-}
+// Arrays on their way to the device: one allocation for all of them, and one
+// copy for all but large ones (an allocation and a copy for each array of a
+// small mesh took most of its upload: O16 1.4 ms).
+class Upload {
+ public:
+  template <class T>
+  void add(const std::vector<T> &h, const T **dptr) {
+    items_.push_back({h.data(), h.size() * sizeof(T), total_, dptr});
+    total_ += (h.size() * sizeof(T) + 255) / 256 * 256;
+  }
+  atlas_status commit(MeshStore &m) {
+    void *p = nullptr;
+    const size_t bytes = std::max<size_t>(256, total_);
+    if (hipMalloc(&p, bytes) != hipSuccess)
+      return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
+    m.allocations.push_back(p);
+    m.bytes += bytes;
+    char *base = static_cast<char *>(p);
+    constexpr size_t kLarge = (size_t)1 << 20;
+    for (size_t k = 0; k < items_.size();) {
+      // a run of smaller arrays goes by way of one host buffer
+      size_t e = k;
+      while (e < items_.size() && items_[e].bytes <= kLarge) ++e;
+      if (e > k) {
+        const size_t first = items_[k].offset;
+        std::vector<char> buf(items_[e - 1].offset + items_[e - 1].bytes - first);
+        for (size_t i = k; i < e; ++i)
+          if (items_[i].bytes)
+            std::memcpy(buf.data() + (items_[i].offset - first), items_[i].src, items_[i].bytes);
+        if (!buf.empty())
+          ATLASX_HIP(hipMemcpy(base + first, buf.data(), buf.size(), hipMemcpyHostToDevice));
+        k = e;
+      } else {
+        ATLASX_HIP(hipMemcpy(base + items_[k].offset, items_[k].src, items_[k].bytes,
+                             hipMemcpyHostToDevice));
+        ++k;
+      }
+    }
+    for (const Item &it : items_) {
+      const void *q = base + it.offset;
+      std::memcpy(it.dptr, &q, sizeof(q));
+    }
+    return ATLAS_OK;
+  }
+
+ private:
+  struct Item {
+    const void *src;
+    size_t bytes, offset;
+    void *dptr;  // the typed pointer to set
+  };
+  std::vector<Item> items_;
+  size_t total_ = 0;
+};
 
 atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStore **out) {
   atlas_status st = validate(d);
@@ -843,44 +895,50 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   SweepPlan sp;
   const bool sweep_ok = nrings <= V / 4 && sweep_plan(rings_of(d), perm, tile_ptr, rowp, nbr, sp);
   if (!sweep_ok) sp = SweepPlan();
-  LaplPlan lp;
-  const bool l2_ok = sweep_ok && lapl_plan(rings_of(d), perm, tile_ptr, rowp, nbr, lp);
-  if (!l2_ok) lp = LaplPlan();
   // the sweep's cuts: longitude parts for columns too long for whole tiles;
   // bands as well where the mesh has too few tiles to fill the chip (below
-  // kSweepFewTiles no built-in shape would use them: O16's upload 1.28 ms
-  // with them, 1.1 without)
+  // kSweepFewTiles no built-in shape would use them)
   const int64_t nt = (int64_t)tile_ptr.size() - 1;
   const bool bands = nt >= kSweepFewTiles && nt < kSweepMinTiles;
   std::vector<std::pair<int, int>> shapes = {{1, 1}, {2, 1}, {3, 1}};
   if (bands)
     shapes = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {1, 6}, {2, 1}, {2, 2}, {3, 1}, {3, 2}};
-  std::vector<CutPlan> cuts(sweep_ok ? shapes.size() : 0);
-  if (sweep_ok) {
-    const std::vector<int64_t> off = rings_of(d);
-    std::vector<int32_t> ring_of(V);
-    for (size_t j = 0; j + 1 < off.size(); ++j)
-      for (int64_t i = off[j]; i < off[j + 1]; ++i) ring_of[i] = (int32_t)j;
-    for (size_t k = 0; k < cuts.size(); ++k)
-      if (!cut_plan(off, ring_of, perm, tile_ptr, rowp, nbr, shapes[k].first, shapes[k].second,
-                    cuts[k]))
-        cuts.clear();
-  }
   std::vector<std::pair<int, int>> lshapes = {{1, 1}, {2, 1}};
-  if (bands)
-    lshapes = {{1, 1}, {1, 2}, {1, 4}, {2, 1}, {2, 2}, {2, 4}};
-  std::vector<LaplCutPlan> lcuts(cuts.empty() ? 0 : lshapes.size());
-  if (!lcuts.empty()) {
+  if (bands)  // (thinner bands form too many gradients twice: no plan took them)
+    lshapes = {{1, 1}, {1, 2}, {2, 1}, {2, 2}};
+  LaplPlan lp;
+  bool l2_ok = false;
+  std::vector<CutPlan> cuts(sweep_ok ? shapes.size() : 0);
+  std::vector<LaplCutPlan> lcuts(sweep_ok ? lshapes.size() : 0);
+  if (sweep_ok) {
     const std::vector<int64_t> off = rings_of(d);
     std::vector<int32_t> ring_of(V), inv(V);
     for (size_t j = 0; j + 1 < off.size(); ++j)
       for (int64_t i = off[j]; i < off[j + 1]; ++i) ring_of[i] = (int32_t)j;
     for (int64_t p = 0; p < V; ++p) inv[perm[p]] = (int32_t)p;
-    for (size_t k = 0; k < lcuts.size(); ++k)
-      if (!lapl_cut_plan(off, ring_of, perm, inv, tile_ptr, rowp, nbr, lshapes[k].first,
-                         lshapes[k].second, lcuts[k]))
-        lcuts.clear();
+    // the three plans on threads of their own (O160's
+    // upload 44 ms; one by one, and with two cuts more, 55)
+    const int nthr = host_threads(nt) > 1 ? 3 : 1;
+    on_threads(nthr, [&](int w) {
+      for (int task = w; task < 3; task += nthr) {
+        if (task == 0) {
+          l2_ok = lapl_plan(off, ring_of, perm, inv, tile_ptr, rowp, nbr, lp);
+        } else if (task == 1) {
+          for (size_t k = 0; k < cuts.size(); ++k)
+            if (!cut_plan(off, ring_of, perm, tile_ptr, rowp, nbr, shapes[k].first,
+                          shapes[k].second, cuts[k]))
+              cuts.clear();
+        } else {
+          for (size_t k = 0; k < lcuts.size(); ++k)
+            if (!lapl_cut_plan(off, ring_of, perm, inv, tile_ptr, rowp, nbr, lshapes[k].first,
+                               lshapes[k].second, lcuts[k]))
+              lcuts.clear();
+        }
+      }
+    });
   }
+  if (!l2_ok) lp = LaplPlan();
+  if (cuts.empty()) lcuts.clear();
   // cos(lat) of every incidence's neighbour, so a node's row is read with
   // contiguous loads
   std::vector<double> ncos(nbr.size());
@@ -921,46 +979,68 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   m->d.l2_pmax = lp.pmax;
   const double *vol_d = nullptr, *cos_pd = nullptr;
   std::vector<double> zeros(V, 0.0);
-  if ((st = upload_array(*m, perm, &m->d.perm)) != ATLAS_OK ||
-      (st = upload_array(*m, rowp, &m->d.rowp)) != ATLAS_OK ||
-      (st = upload_array(*m, nbr, &m->d.nbr)) != ATLAS_OK ||
-      (st = upload_array(*m, S, &m->d.S)) != ATLAS_OK ||
-      (st = upload_array(*m, inc_edge, &m->d.inc_edge)) != ATLAS_OK ||
-      (st = upload_array(*m, zeros, &m->d.alpha)) != ATLAS_OK ||
-      (st = upload_array(*m, zeros, &m->d.beta)) != ATLAS_OK ||
-      (st = upload_array(*m, cos_n, &m->d.coslat)) != ATLAS_OK ||
-      (st = upload_array(*m, tile_ptr, &m->d.tile_ptr)) != ATLAS_OK ||
-      (st = upload_array(*m, e2n, &m->d.e2n)) != ATLAS_OK ||
-      (st = upload_array(*m, eS, &m->d.eS)) != ATLAS_OK ||
-      (st = upload_array(*m, vol_p, &vol_d)) != ATLAS_OK ||
-      (st = upload_array(*m, cos_p, &cos_pd)) != ATLAS_OK ||
-      (st = upload_array(*m, sp.tile_seg, &m->d.tile_seg)) != ATLAS_OK ||
-      (st = upload_array(*m, sp.seg, &m->d.seg)) != ATLAS_OK ||
-      (st = upload_array(*m, sp.seg_pos, &m->d.seg_pos)) != ATLAS_OK ||
-      (st = upload_array(*m, sp.selfslot, &m->d.selfslot)) != ATLAS_OK ||
-      (st = upload_array(*m, sp.lref, &m->d.lref)) != ATLAS_OK ||
-      (st = upload_array(*m, ncos, &m->d.ncos)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.tile_seg, &m->d.l2_tile_seg)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.fseg, &m->d.l2_fseg)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.gseg, &m->d.l2_gseg)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.seg_pos, &m->d.l2_seg_pos)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.gnode, &m->d.l2_gnode)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.glref, &m->d.l2_glref)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.lref, &m->d.l2_lref)) != ATLAS_OK ||
-      (st = upload_array(*m, lp.lself, &m->d.l2_lself)) != ATLAS_OK) {
-    delete m;
-    return st;
+  std::vector<PosRec> pos(V);
+  for (int64_t p = 0; p < V; ++p) {
+    pos[p].node = perm[p];
+    pos[p].r0 = rowp[p];
+    pos[p].r1 = rowp[p + 1];
+    pos[p].selfslot = sweep_ok ? sp.selfslot[p] : 0;
+    pos[p].alpha = 0.0;  // derived on the device below
+    pos[p].beta = 0.0;
+  }
+  // node coordinates by node id (remap targets and sources), and the
+  // parallels of a mesh a remap can start from
+  const std::vector<double> lon_n(d->lon, d->lon + V), lat_n(d->lat, d->lat + V);
+  const std::vector<int64_t> rings = rings_of(d);
+  std::vector<double> rlat;
+  if (zipper_conforming(d, rings)) {
+    rlat.resize(rings.size() - 1);
+    for (size_t j = 0; j + 1 < rings.size(); ++j) rlat[j] = d->lat[rings[j]];
+    m->rs.nrings = (int32_t)rlat.size();
+    m->rs.ok = 1;
+  }
+  Upload up;
+  up.add(perm, &m->d.perm);
+  up.add(rowp, &m->d.rowp);
+  up.add(nbr, &m->d.nbr);
+  up.add(S, &m->d.S);
+  up.add(inc_edge, &m->d.inc_edge);
+  up.add(zeros, &m->d.alpha);
+  up.add(zeros, &m->d.beta);
+  up.add(cos_n, &m->d.coslat);
+  up.add(tile_ptr, &m->d.tile_ptr);
+  up.add(e2n, &m->d.e2n);
+  up.add(eS, &m->d.eS);
+  up.add(vol_p, &vol_d);
+  up.add(cos_p, &cos_pd);
+  up.add(sp.tile_seg, &m->d.tile_seg);
+  up.add(sp.seg, &m->d.seg);
+  up.add(sp.seg_pos, &m->d.seg_pos);
+  up.add(sp.selfslot, &m->d.selfslot);
+  up.add(sp.lref, &m->d.lref);
+  up.add(ncos, &m->d.ncos);
+  up.add(lp.tile_seg, &m->d.l2_tile_seg);
+  up.add(lp.fseg, &m->d.l2_fseg);
+  up.add(lp.gseg, &m->d.l2_gseg);
+  up.add(lp.seg_pos, &m->d.l2_seg_pos);
+  up.add(lp.gnode, &m->d.l2_gnode);
+  up.add(lp.glref, &m->d.l2_glref);
+  up.add(lp.lref, &m->d.l2_lref);
+  up.add(lp.lself, &m->d.l2_lself);
+  up.add(pos, &m->d.pos);
+  up.add(lon_n, &m->node_lon);
+  up.add(lat_n, &m->node_lat);
+  if (m->rs.ok) {
+    up.add(rings, &m->rs.ring_off);
+    up.add(rlat, &m->rs.ring_lat);
   }
   m->cuts.resize(cuts.size());
   for (size_t k = 0; k < cuts.size(); ++k) {
     SweepView &v = m->cuts[k];
-    if ((st = upload_array(*m, cuts[k].tile_seg, &v.tile_seg)) != ATLAS_OK ||
-        (st = upload_array(*m, cuts[k].seg, &v.seg)) != ATLAS_OK ||
-        (st = upload_array(*m, cuts[k].seg_pos, &v.seg_pos)) != ATLAS_OK ||
-        (st = upload_array(*m, cuts[k].refs, &v.refs)) != ATLAS_OK) {
-      delete m;
-      return st;
-    }
+    up.add(cuts[k].tile_seg, &v.tile_seg);
+    up.add(cuts[k].seg, &v.seg);
+    up.add(cuts[k].seg_pos, &v.seg_pos);
+    up.add(cuts[k].refs, &v.refs);
     v.segmax = cuts[k].segmax;
     v.pmax = cuts[k].pmax;
     v.rings = cuts[k].rings;
@@ -971,15 +1051,12 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   m->lcuts.resize(lcuts.size());
   for (size_t k = 0; k < lcuts.size(); ++k) {
     LaplView &v = m->lcuts[k];
-    if ((st = upload_array(*m, lcuts[k].tile_seg, &v.tile_seg)) != ATLAS_OK ||
-        (st = upload_array(*m, lcuts[k].fseg, &v.fseg)) != ATLAS_OK ||
-        (st = upload_array(*m, lcuts[k].gseg, &v.gseg)) != ATLAS_OK ||
-        (st = upload_array(*m, lcuts[k].seg_pos, &v.seg_pos)) != ATLAS_OK ||
-        (st = upload_array(*m, lcuts[k].grefs, &v.grefs)) != ATLAS_OK ||
-        (st = upload_array(*m, lcuts[k].orefs, &v.orefs)) != ATLAS_OK) {
-      delete m;
-      return st;
-    }
+    up.add(lcuts[k].tile_seg, &v.tile_seg);
+    up.add(lcuts[k].fseg, &v.fseg);
+    up.add(lcuts[k].gseg, &v.gseg);
+    up.add(lcuts[k].seg_pos, &v.seg_pos);
+    up.add(lcuts[k].grefs, &v.grefs);
+    up.add(lcuts[k].orefs, &v.orefs);
     v.fmax = lcuts[k].fmax;
     v.gmax = lcuts[k].gmax;
     v.pmax = lcuts[k].pmax;
@@ -988,52 +1065,12 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
     v.bands = lshapes[k].second;
     v.ntiles = (int32_t)lcuts[k].tile_seg.size() - 1;
   }
-  std::vector<PosRec> pos(V);
-  for (int64_t p = 0; p < V; ++p) {
-    pos[p].node = perm[p];
-    pos[p].r0 = rowp[p];
-    pos[p].r1 = rowp[p + 1];
-    pos[p].selfslot = sweep_ok ? sp.selfslot[p] : 0;
-    pos[p].alpha = 0.0;  // derived on the device below
-    pos[p].beta = 0.0;
-  }
-  if ((st = upload_array(*m, pos, &m->d.pos)) != ATLAS_OK) {
+  if ((st = up.commit(*m)) != ATLAS_OK ||
+      (st = derive_scales(*m, vol_d, cos_pd, d->radius)) != ATLAS_OK ||
+      (l2_ok && (st = pack_lapl_geometry(*m, (int64_t)lp.gnode.size())) != ATLAS_OK) ||
+      (!cuts.empty() && (st = pack_sweep_geometry(*m)) != ATLAS_OK)) {
     delete m;
     return st;
-  }
-  if ((st = derive_scales(*m, vol_d, cos_pd, d->radius)) != ATLAS_OK) {
-    delete m;
-    return st;
-  }
-  if (l2_ok && (st = pack_lapl_geometry(*m, (int64_t)lp.gnode.size())) != ATLAS_OK) {
-    delete m;
-    return st;
-  }
-  if (!cuts.empty() && (st = pack_sweep_geometry(*m)) != ATLAS_OK) {
-    delete m;
-    return st;
-  }
-  // node coordinates by node id (remap targets and sources), and the
-  // parallels of a mesh a remap can start from
-  {
-    std::vector<double> lon_n(d->lon, d->lon + V), lat_n(d->lat, d->lat + V);
-    if ((st = upload_array(*m, lon_n, &m->node_lon)) != ATLAS_OK ||
-        (st = upload_array(*m, lat_n, &m->node_lat)) != ATLAS_OK) {
-      delete m;
-      return st;
-    }
-    const std::vector<int64_t> off = rings_of(d);
-    if (zipper_conforming(d, off)) {
-      std::vector<double> rlat(off.size() - 1);
-      for (size_t j = 0; j + 1 < off.size(); ++j) rlat[j] = d->lat[off[j]];
-      if ((st = upload_array(*m, off, &m->rs.ring_off)) != ATLAS_OK ||
-          (st = upload_array(*m, rlat, &m->rs.ring_lat)) != ATLAS_OK) {
-        delete m;
-        return st;
-      }
-      m->rs.nrings = (int32_t)rlat.size();
-      m->rs.ok = 1;
-    }
   }
   // the volumes stay (diagnostics); cos by position was only for the scales
   m->d.vol = vol_d;

@@ -130,3 +130,13 @@ result = apply(m, LAPL, {nlev}, {dt})
 def test_fused_laplacian_on_few_tiles(N, nlev, dt, fused):
     names = [k[0] for k in on_host(f"m = P.Mesh({N})\nresult = apply(m, LAPL, {nlev}, {dt})")]
     assert len(names) == (1 if fused else 2) and ("k_lsweepw" in names[0]) == fused, names
+
+
+@pytest.mark.parametrize("N", [2, 16, 160])
+def test_upload_takes_few_allocations(N):
+    """A small mesh's upload is bound by its allocations and copies: its arrays
+    come in one, beside the packed records'."""
+    assert on_host(f"""
+m = P.Mesh({N})
+result = H.host_hip_allocs()
+""") <= 10
