@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstring>
 #include <exception>
+#include <memory>
 #include <numeric>
 #include <string>
 #include <thread>
@@ -787,14 +788,22 @@ class Upload {
     items_.push_back({h.data(), h.size() * sizeof(T), total_, dptr});
     total_ += (h.size() * sizeof(T) + 255) / 256 * 256;
   }
-  atlas_status commit(MeshStore &m) {
+  // *block: the allocation (the caller's to free); nothing is left on failure
+  atlas_status commit(void **block) {
     void *p = nullptr;
-    const size_t bytes = std::max<size_t>(256, total_);
-    if (hipMalloc(&p, bytes) != hipSuccess)
+    if (hipMalloc(&p, std::max<size_t>(256, total_)) != hipSuccess) {
+      (void)hipGetLastError();
       return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
-    m.allocations.push_back(p);
-    m.bytes += bytes;
-    char *base = static_cast<char *>(p);
+    }
+    const atlas_status st = copy(static_cast<char *>(p));
+    if (st != ATLAS_OK) (void)hipFree(p);
+    else *block = p;
+    return st;
+  }
+  size_t bytes() const { return std::max<size_t>(256, total_); }
+
+ private:
+  atlas_status copy(char *base) {
     constexpr size_t kLarge = (size_t)1 << 20;
     for (size_t k = 0; k < items_.size();) {
       // a run of smaller arrays goes by way of one host buffer
@@ -821,8 +830,6 @@ class Upload {
     }
     return ATLAS_OK;
   }
-
- private:
   struct Item {
     const void *src;
     size_t bytes, offset;
@@ -952,7 +959,7 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   sp.lref.resize(sp.lref.size() + kIncPad, 1 << 16);
   if (l2_ok) lp.lref.resize(lp.lref.size() + kIncPad, 1 << 16);
 
-  MeshStore *m = new (std::nothrow) MeshStore();
+  std::unique_ptr<MeshStore> m(new (std::nothrow) MeshStore());
   if (!m) return fail(ATLAS_ENOMEM, "out of host memory");
   (void)hipGetDevice(&m->device);
   m->d.V = (int32_t)V;
@@ -963,6 +970,7 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   m->radius = d->radius;
   m->nrings = nrings;
   m->max_degree = maxdeg;
+  m->allocations.reserve(8);
   for (size_t t = 0; t + 1 < tile_ptr.size(); ++t)
     m->max_tile = std::max<int64_t>(m->max_tile, tile_ptr[t + 1] - tile_ptr[t]);
   if (sweep_ok) {
@@ -1012,7 +1020,6 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   up.add(e2n, &m->d.e2n);
   up.add(eS, &m->d.eS);
   up.add(vol_p, &vol_d);
-  up.add(cos_p, &cos_pd);
   up.add(sp.tile_seg, &m->d.tile_seg);
   up.add(sp.seg, &m->d.seg);
   up.add(sp.seg_pos, &m->d.seg_pos);
@@ -1023,10 +1030,6 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   up.add(lp.fseg, &m->d.l2_fseg);
   up.add(lp.gseg, &m->d.l2_gseg);
   up.add(lp.seg_pos, &m->d.l2_seg_pos);
-  up.add(lp.gnode, &m->d.l2_gnode);
-  up.add(lp.glref, &m->d.l2_glref);
-  up.add(lp.lref, &m->d.l2_lref);
-  up.add(lp.lself, &m->d.l2_lself);
   up.add(pos, &m->d.pos);
   up.add(lon_n, &m->node_lon);
   up.add(lat_n, &m->node_lat);
@@ -1034,13 +1037,37 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
     up.add(rings, &m->rs.ring_off);
     up.add(rlat, &m->rs.ring_lat);
   }
+  // what only the packing below reads
+  Upload tmp;
+  tmp.add(cos_p, &cos_pd);
+  tmp.add(lp.gnode, &m->d.l2_gnode);
+  tmp.add(lp.glref, &m->d.l2_glref);
+  tmp.add(lp.lref, &m->d.l2_lref);
+  tmp.add(lp.lself, &m->d.l2_lself);
+  void *block = nullptr;
+  if ((st = up.commit(&block)) != ATLAS_OK) return st;
+  m->allocations.push_back(block);
+  m->bytes += up.bytes();
+  if ((st = tmp.commit(&block)) != ATLAS_OK) return st;
+  if ((st = derive_scales(*m, vol_d, cos_pd, d->radius)) == ATLAS_OK && l2_ok)
+    st = pack_lapl_geometry(*m, (int64_t)lp.gnode.size());
+  (void)hipDeviceSynchronize();
+  (void)hipFree(block);
+  m->d.l2_gnode = nullptr;
+  m->d.l2_glref = m->d.l2_lref = m->d.l2_lself = nullptr;
+  if (st != ATLAS_OK) return st;
+
+  // The wave-specialised forms' plans and records.  They are the larger part of
+  // the store beside the register-staged Laplacian's: a mesh that fits the
+  // device without them goes without, on the other forms.
+  Upload opt;
   m->cuts.resize(cuts.size());
   for (size_t k = 0; k < cuts.size(); ++k) {
     SweepView &v = m->cuts[k];
-    up.add(cuts[k].tile_seg, &v.tile_seg);
-    up.add(cuts[k].seg, &v.seg);
-    up.add(cuts[k].seg_pos, &v.seg_pos);
-    up.add(cuts[k].refs, &v.refs);
+    opt.add(cuts[k].tile_seg, &v.tile_seg);
+    opt.add(cuts[k].seg, &v.seg);
+    opt.add(cuts[k].seg_pos, &v.seg_pos);
+    opt.add(cuts[k].refs, &v.refs);
     v.segmax = cuts[k].segmax;
     v.pmax = cuts[k].pmax;
     v.rings = cuts[k].rings;
@@ -1051,12 +1078,12 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
   m->lcuts.resize(lcuts.size());
   for (size_t k = 0; k < lcuts.size(); ++k) {
     LaplView &v = m->lcuts[k];
-    up.add(lcuts[k].tile_seg, &v.tile_seg);
-    up.add(lcuts[k].fseg, &v.fseg);
-    up.add(lcuts[k].gseg, &v.gseg);
-    up.add(lcuts[k].seg_pos, &v.seg_pos);
-    up.add(lcuts[k].grefs, &v.grefs);
-    up.add(lcuts[k].orefs, &v.orefs);
+    opt.add(lcuts[k].tile_seg, &v.tile_seg);
+    opt.add(lcuts[k].fseg, &v.fseg);
+    opt.add(lcuts[k].gseg, &v.gseg);
+    opt.add(lcuts[k].seg_pos, &v.seg_pos);
+    opt.add(lcuts[k].grefs, &v.grefs);
+    opt.add(lcuts[k].orefs, &v.orefs);
     v.fmax = lcuts[k].fmax;
     v.gmax = lcuts[k].gmax;
     v.pmax = lcuts[k].pmax;
@@ -1065,21 +1092,31 @@ atlas_status upload_mesh(const atlas_mesh_desc *d, int band, int width, MeshStor
     v.bands = lshapes[k].second;
     v.ntiles = (int32_t)lcuts[k].tile_seg.size() - 1;
   }
-  if ((st = up.commit(*m)) != ATLAS_OK ||
-      (st = derive_scales(*m, vol_d, cos_pd, d->radius)) != ATLAS_OK ||
-      (l2_ok && (st = pack_lapl_geometry(*m, (int64_t)lp.gnode.size())) != ATLAS_OK) ||
-      (!cuts.empty() && (st = pack_sweep_geometry(*m)) != ATLAS_OK)) {
-    delete m;
-    return st;
+  if (!cuts.empty()) {
+    if ((st = opt.commit(&block)) == ATLAS_OK) {
+      st = pack_sweep_geometry(*m);
+      if (st == ATLAS_ENOMEM) {
+        (void)hipFree(block);
+      } else {
+        m->allocations.push_back(block);
+        m->bytes += opt.bytes();
+      }
+    }
+    if (st == ATLAS_ENOMEM) {
+      m->cuts.clear();
+      m->lcuts.clear();
+    } else if (st != ATLAS_OK) {
+      return st;
+    }
   }
-  // the volumes stay (diagnostics); cos by position was only for the scales
+  // the volumes stay (diagnostics)
   m->d.vol = vol_d;
   (void)hipDeviceSynchronize();
   // bytes one operator pass reads from the mesh store (column/flat forms):
   // per position perm + rowp + alpha/beta; per incidence nbr + S;
   // per node cos(lat) (div/curl)
   m->geometry_bytes = (double)V * (4 + 4 + 16) + (double)m->nincid * (4 + 16);
-  *out = m;
+  *out = m.release();
   return ATLAS_OK;
 }
 

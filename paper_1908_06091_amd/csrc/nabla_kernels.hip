@@ -2873,17 +2873,23 @@ atlas_status pack_lapl_geometry(MeshStore &m, int64_t ngrec) {
 
 atlas_status pack_sweep_geometry(MeshStore &m) {
   // by position for scalar and vector inputs, by node for the Laplacian
-  for (int k = 0; k < (m.lcuts.empty() ? 2 : 3); ++k) {
-    const int vec = k == 1;
-    void *g = nullptr;
-    const size_t gb = (size_t)m.d.V * (vec ? kSgeoWordsV : kSgeoWordsS) * 16;
-    if (hipMalloc(&g, gb) != hipSuccess) return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
-    m.allocations.push_back(g);
-    m.bytes += gb;
-    hipLaunchKernelGGL(k_pack_sgeo, dim3((m.d.V + 255) / 256), dim3(256), 0, 0, m.d, vec,
-                       k == 2 ? 1 : 0, static_cast<i32x4 *>(g));
+  const int sets = m.lcuts.empty() ? 2 : 3;
+  auto words = [&](int k) { return (size_t)m.d.V * (k == 1 ? kSgeoWordsV : kSgeoWordsS); };
+  size_t total = 0;
+  for (int k = 0; k < sets; ++k) total += words(k) * 16;
+  void *p = nullptr;
+  if (hipMalloc(&p, total) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
+  }
+  m.allocations.push_back(p);
+  m.bytes += total;
+  i32x4 *g = static_cast<i32x4 *>(p);
+  for (int k = 0; k < sets; g += words(k), ++k) {
+    hipLaunchKernelGGL(k_pack_sgeo, dim3((m.d.V + 255) / 256), dim3(256), 0, 0, m.d, k == 1,
+                       k == 2 ? 1 : 0, g);
     ATLASX_HIP(hipGetLastError());
-    (k == 0 ? m.d.sgeo : k == 1 ? m.d.sgeo_v : m.d.sgeo_n) = static_cast<const int4 *>(g);
+    (k == 0 ? m.d.sgeo : k == 1 ? m.d.sgeo_v : m.d.sgeo_n) = reinterpret_cast<const int4 *>(g);
   }
   return ATLAS_OK;
 }

@@ -14,16 +14,16 @@ typedef struct { uint32_t x, y, z; } dim3_t;
 #define OUT_OF_MEMORY 2
 
 static long long g_used, g_limit = -1; /* bytes; -1: no limit */
-static int g_allocs;
+static int g_allocs, g_error; /* the error the next hipGetLastError returns */
 void host_hip_limit(long long bytes) { g_limit = bytes; }
 long long host_hip_used(void) { return g_used; }
 int host_hip_allocs(void) { return g_allocs; }
 
 int hipMalloc(void **p, size_t n) {
   *p = NULL;
-  if (g_limit >= 0 && g_used + (long long)n > g_limit) return OUT_OF_MEMORY;
+  if (g_limit >= 0 && g_used + (long long)n > g_limit) return g_error = OUT_OF_MEMORY;
   size_t *b = aligned_alloc(256, (n + 256 + 255) / 256 * 256);
-  if (!b) return OUT_OF_MEMORY;
+  if (!b) return g_error = OUT_OF_MEMORY;
   b[0] = n;
   g_used += (long long)n;
   ++g_allocs;
@@ -46,7 +46,7 @@ int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)k;
 int hipGetDevice(int *d) { *d = 0; return OK; }
 int hipSetDevice(int d) { (void)d; return OK; }
 int hipDeviceSynchronize(void) { return OK; }
-int hipGetLastError(void) { return OK; }
+int hipGetLastError(void) { const int e = g_error; g_error = OK; return e; }
 const char *hipGetErrorString(int e) { return e == OUT_OF_MEMORY ? "out of memory" : "error"; }
 int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return OK; } /* compute units */
 int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return OK; }

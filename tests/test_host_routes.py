@@ -140,3 +140,47 @@ def test_upload_takes_few_allocations(N):
 m = P.Mesh({N})
 result = H.host_hip_allocs()
 """) <= 10
+
+
+@pytest.mark.parametrize("N,share", [(160, 0.9), (160, 0.73), (500, 0.83)])
+def test_a_mesh_that_fits_without_the_sweeps_plans(N, share):
+    """Where the device has no room for the wave-specialised forms' plans and
+    records, a mesh goes without them and its calls take the other forms."""
+    result = on_host(f"""
+m = P.Mesh({N})
+full = H.host_hip_used()
+m.close()
+left = H.host_hip_used()
+H.host_hip_limit(int({share} * full))
+m = P.Mesh({N})
+used = H.host_hip_used() - left
+names = [apply(m, op, nlev, dt)[-1][0] for op in (GRAD, DIV, CURL) for dt in (F64, F32)
+         for nlev in (1, 5, 37, 137, 300)]
+names += [launches(L.atlas_nabla_div_curl, m.handle, IN, nlev, dt, OUT, OUT2, None)[-1][0]
+          for dt in (F64, F32) for nlev in (5, 37, 137)]
+H.host_hip_limit(-1)  # (two passes ask for their intermediate)
+names += [apply(m, LAPL, nlev, dt)[-1][0] for dt in (F64, F32) for nlev in (1, 37, 137)]
+result = [int(m.info.device_bytes), used, left, names]
+""")
+    assert result[0] == result[1] and result[2] == 0
+    assert not [n for n in result[3] if "sweepw" in n], result[3]
+
+
+def test_a_mesh_too_large_for_the_device_is_refused():
+    assert on_host("""
+H.host_hip_limit(20 << 20)
+try:
+    P.Mesh(160)
+    result = "uploaded"
+except P.AtlasError as e:
+    result = [str(e), H.host_hip_used()]
+""")[1] == 0
+
+
+def test_arrays_read_once_leave_the_store():
+    """What only the packing of the records reads is freed after it."""
+    used, wide = on_host("""
+m = P.Mesh(320)
+result = [H.host_hip_used(), int(m.info.nnodes)]
+""")
+    assert used < 1550 * wide
