@@ -274,8 +274,9 @@ typedef enum {
   ATLAS_VARIANT_FLUX = 3,   /* two kernels: edge fluxes into an [E][nlev]
                                buffer (EdgeColumns-like), then the gather.
                                FP32 fields run the column form instead
-                               (their FP64 terms do not fit the buffer) and
-                               leave the flux workspace untouched          */
+                               (their FP64 terms do not fit the buffer):
+                               no flux workspace is allocated for them, and
+                               a caller's is left untouched                */
   ATLAS_VARIANT_SWEEP = 4,  /* one workgroup per (tile, level chunk) walks
                                its band parallel by parallel, keeping three
                                consecutive parallels' columns in LDS       */

@@ -143,8 +143,12 @@ atlas_status apply(atlas_mesh_t mesh, atlas_op op, const void *in, int32_t nlev,
     need += lapl_ws_bytes(m, nlev, dt);  // the fused form needs none
   if (sh.variant == ATLAS_VARIANT_FLUX) need += flux_ws_bytes(m, op, nlev, dt);
   void *ws = workspace;
-  if (need && !ws) {
-    st = internal_ws(m, need, &ws);
+  // (the flux form of an FP32 field runs the column form: a workspace that the
+  // caller gives for it is checked like one, but none is taken for it)
+  const size_t own = need - (sh.variant == ATLAS_VARIANT_FLUX && dt == ATLAS_F32
+                                 ? flux_ws_bytes(m, op, nlev, dt) : 0);
+  if (own && !ws) {
+    st = internal_ws(m, own, &ws);
     if (st != ATLAS_OK) return st;
   }
   if (ws && !aligned(ws, 16)) return fail(ATLAS_EINVAL, "workspace must be 16-byte aligned");

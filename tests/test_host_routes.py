@@ -184,3 +184,22 @@ m = P.Mesh(320)
 result = [H.host_hip_used(), int(m.info.nnodes)]
 """)
     assert used < 1550 * wide
+
+
+@pytest.mark.parametrize("op", [0, 1, 2, 3])
+def test_fp32_flux_form_takes_no_flux_workspace(op):
+    """FP32 fields run the column form in its place: only a Laplacian's
+    gradient needs memory."""
+    used, flux64 = on_host(f"""
+m = P.Mesh(80)
+flux = P.Launch(P.VARIANT_FLUX, 256, 0, 0, 0, 0)
+before = H.host_hip_used()
+names = apply(m, {op}, 40, F32, flux)
+used = H.host_hip_used() - before
+assert all("k_col" in n[0] for n in names), names
+assert any("flux" in n[0] for n in apply(m, {op}, 40, F64, flux))
+result = [used, H.host_hip_used() - before]
+""")
+    V = sum(4 * (20 + 4 * j) for j in range(80)) // 2
+    assert used <= (V * 40 * 8 + 4096 if op == 3 else 0)
+    assert flux64 > used
