@@ -307,25 +307,32 @@ atlas_status autotune(atlas_mesh_t mesh, atlas_op op, const void *in, int nlev, 
       LaunchShape win;
       win.variant = ATLAS_VARIANT_COLUMN;
       win.per_pass = 1;
-      if (m.d.l2_ok) {
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess) {
-          for (int b : {1024, 768}) {
-            const atlas_launch c{ATLAS_VARIANT_FUSED, b, 0, 0, 0, 0};
-            const float t = time_shape(mesh, op, in, nlev, dt, out, grad, c, st, e0, e1);
-            if (t >= 0.0f && t < bt) {
-              bt = t;
-              bl = c;
-              win = LaunchShape();
-              win.variant = ATLAS_VARIANT_FUSED;
-              win.block = b;
-              win.nodes_per_block = 0;
-            }
+      // (the built-in block first: it also says whether two workgroups share
+      // a compute unit; then the others that launch differently)
+      std::vector<int> blocks{512, 768, 1024}, tried;
+      const LaunchShape d = default_shape(m, op, nlev, dt);
+      if (d.variant == ATLAS_VARIANT_FUSED) blocks.insert(blocks.begin(), d.block);
+      hipEvent_t e0 = nullptr, e1 = nullptr;
+      if (hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess) {
+        for (int b : blocks) {
+          LaunchShape fs;
+          fs.variant = ATLAS_VARIANT_FUSED;
+          fs.block = b;
+          fs.nodes_per_block = 0;
+          const int runs = lapl_fused_block(m, nlev, dt, fs);
+          if (!runs || std::find(tried.begin(), tried.end(), runs) != tried.end()) continue;
+          tried.push_back(runs);
+          const atlas_launch c{ATLAS_VARIANT_FUSED, b, 0, 0, 0, 0};
+          const float t = time_shape(mesh, op, in, nlev, dt, out, grad, c, st, e0, e1);
+          if (t >= 0.0f && t < bt) {
+            bt = t;
+            bl = c;
+            win = fs;
           }
         }
-        if (e0) (void)hipEventDestroy(e0);
-        if (e1) (void)hipEventDestroy(e1);
       }
+      if (e0) (void)hipEventDestroy(e0);
+      if (e1) (void)hipEventDestroy(e1);
       std::lock_guard<std::mutex> g(m.tune_mu);
       m.tuned[TuneKey{(int)op, (int)dt, nlev}] = win;
     }

@@ -280,8 +280,9 @@ atlas_status derive_scales(MeshStore &m, const double *vol_by_pos,
 atlas_status bandwidth_probe(const void *in, void *out, int64_t n, int elem, hipStream_t st);
 LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype dt,
                           bool packed = true);
-// True if a Laplacian launched with `sh` runs the fused one-pass form
-// (which needs no workspace) rather than falling back to the two passes.
+// The block that a Laplacian launched with `sh` runs the fused one-pass form
+// with (which needs no workspace), 0 where the two passes run instead.
+int lapl_fused_block(const MeshStore &ms, int nlev, atlas_dtype dt, const LaunchShape &sh);
 bool lapl_fused_runs(const MeshStore &ms, int nlev, atlas_dtype dt, const LaunchShape &sh);
 // (d phi / d lon, d phi / d lat) of a scalar field, [V][nlev][2].
 atlas_status gradient_lonlat(MeshStore &ms, atlas_dtype dt, const void *in, int nlev, void *out,

@@ -3717,13 +3717,19 @@ static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fu
   return any;
 }
 
-bool lapl_fused_runs(const MeshStore &ms, int nlev, atlas_dtype dt, const LaunchShape &sh) {
-  if (sh.variant != ATLAS_VARIANT_FUSED) return false;
+int lapl_fused_block(const MeshStore &ms, int nlev, atlas_dtype dt, const LaunchShape &sh) {
+  if (sh.variant != ATLAS_VARIANT_FUSED) return 0;
   FusedPlan fp;
   FusedwPlan fw;
-  return dt == ATLAS_F64
-             ? fusedw_plan<double>(ms, nlev, sh, &fw) || fused_plan<double>(ms, nlev, sh, &fp)
-             : fusedw_plan<float>(ms, nlev, sh, &fw) || fused_plan<float>(ms, nlev, sh, &fp);
+  if (dt == ATLAS_F64 ? fusedw_plan<double>(ms, nlev, sh, &fw)
+                      : fusedw_plan<float>(ms, nlev, sh, &fw))
+    return min(sh.block, kLswBlock);
+  return (dt == ATLAS_F64 ? fused_plan<double>(ms, nlev, sh, &fp)
+                          : fused_plan<float>(ms, nlev, sh, &fp)) ? sh.block : 0;
+}
+
+bool lapl_fused_runs(const MeshStore &ms, int nlev, atlas_dtype dt, const LaunchShape &sh) {
+  return lapl_fused_block(ms, nlev, dt, sh) != 0;
 }
 
 // The fused Laplacian on the two-ring plan; *ran = false (nothing

@@ -203,3 +203,45 @@ result = [used, H.host_hip_used() - before]
     V = sum(4 * (20 + 4 * j) for j in range(80)) // 2
     assert used <= (V * 40 * 8 + 4096 if op == 3 else 0)
     assert flux64 > used
+
+
+_TUNE = """
+import ctypes
+def tune(m, nlev, dt):
+    best, ms = P.Launch(), ctypes.c_float()
+    names = launches(L.atlas_autotune, m.handle, LAPL, IN, nlev, dt, OUT, OUT2, None,
+                     ctypes.byref(best), ctypes.byref(ms))
+    return best, [(n, t) for n, g, t, l in names if "lsweep" in n]
+"""
+
+
+def test_autotuned_laplacian_tries_the_built_in_block():
+    """... and every block once that the fused form launches differently with."""
+    result = on_host(_TUNE + """
+m = P.Mesh(320)
+result = []
+for nlev, dt in ((137, F64), (80, F64), (37, F64), (200, F32)):
+    built = apply(m, LAPL, nlev, dt)[-1]
+    best, fused = tune(m, nlev, dt)
+    result.append([built, best.variant, best.block_threads, fused, apply(m, LAPL, nlev, dt)[-1]])
+""")
+    for built, variant, block, fused, now in result:
+        assert "k_lsweepw" in built[0] and variant == 5
+        assert fused[0][1] == built[2] == block  # (all equal on this clock: the first is kept)
+        blocks = [t for _, t in fused]
+        assert sorted(set(blocks)) == sorted({512, 768, built[2]})
+        assert len(blocks) == 4 * len(set(blocks))  # a warm-up and three timed
+        assert now == built
+
+
+def test_autotuned_laplacian_keeps_the_faster_form():
+    """The two passes where the fused form is slower."""
+    result = on_host(_TUNE + """
+H.host_hip_slow(b"k_lsweep")
+m = P.Mesh(320)
+best, fused = tune(m, 137, F64)
+names = [n[0] for n in apply(m, LAPL, 137, F64)]
+result = [best.variant, len(fused), names]
+""")
+    assert result[0] != 5 and result[1] > 0 and len(result[2]) == 2
+    assert not [n for n in result[2] if "lsweep" in n]
