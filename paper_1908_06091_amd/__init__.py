@@ -77,11 +77,15 @@ def _dtype_code(t):
 # The smallest calls are bound by the host (a call on O16 took 8.3 us, of which
 # the library's own launch 3.2): pointers go to ctypes as plain integers, and
 # the current stream is asked for as a handle (0.2 us) instead of through a
-# torch.cuda.Stream object (2.7 us).
+# torch.cuda.Stream object (2.7 us), where this torch has the two calls (they
+# are not part of its documented interface).
 def _stream(stream):
     if stream is None:
-        c = _torch()._C
-        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+        torch = _torch()
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 
