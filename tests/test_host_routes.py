@@ -245,3 +245,46 @@ result = [best.variant, len(fused), names]
 """)
     assert result[0] != 5 and result[1] > 0 and len(result[2]) == 2
     assert not [n for n in result[2] if "lsweep" in n]
+
+
+@pytest.mark.parametrize("layout", [(92, 24), (63, 40), (62, 16), (64, 9)])
+def test_tall_bands_run_the_wave_specialised_forms(layout):
+    """The layouts of test_gpu_tall_bands.py, by explicit launch shapes."""
+    result = on_host(f"""
+m = P.Mesh(46, layout={layout!r})
+result = []
+for nlev in (4, 5, 37, 96, 137):
+    for dt in (F64, F32):
+        for block in (512, 1024):
+            result += [apply(m, op, nlev, dt, P.Launch(P.VARIANT_SWEEP, block, 0, 0, 0, 0))[-1][0]
+                       for op in (GRAD, DIV, CURL)]
+        for block in (512, 768):
+            result.append(apply(m, LAPL, nlev, dt, P.Launch(P.VARIANT_FUSED, block, 0, 0, 0, 0))[-1][0])
+""")
+    assert len(result) == 80
+    for name in result:
+        assert "sweepw" in name, name
+
+
+def test_built_in_forms_of_the_parity_cases():
+    """Which of the sizes that other tests compare as "built in" take the
+    one-pass Laplacian (FP64 first) and the one-pass sweep."""
+    fused, dc = on_host("""
+fused = []
+for N, nlev in ((160, 45), (160, 137), (240, 24), (240, 137)):
+    m = P.Mesh(N)
+    for dt in (F64, F32):
+        names = [n[0] for n in apply(m, LAPL, nlev, dt)]
+        fused.append("k_lsweepw" in names[0] if len(names) == 1 else False)
+    m.close()
+m = P.Mesh(320)
+dc = [launches(L.atlas_nabla_div_curl, m.handle, IN, nlev, dt, OUT, OUT2, None)
+      for nlev in (2, 5, 16, 37, 47, 64, 91, 96, 97, 137) for dt in (F64, F32)]
+result = [fused, [[n[0] for n in c] for c in dc]]
+""")
+    assert fused == [False, False, True, False, True, False, True, False]
+    # 2 levels: flat; 37 and 47 (FP32: 47): two column passes; FP32 above: one
+    forms = ["".join(sorted({f for f in ("flat", "sweepw", "colv_dc", "colvI") if f in "".join(c)}))
+             for c in dc]
+    assert forms == (["flat"] * 2 + ["sweepw"] * 4 + ["colvI", "sweepw"] + ["colvI"] * 2 +
+                     ["sweepw", "colv_dc"] * 5)
