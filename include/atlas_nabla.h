@@ -315,7 +315,7 @@ typedef struct {
                                wave-specialised workgroups (four waves load
                                the next parallels straight into LDS, the
                                others compute and store; 16-byte lane
-                               vectors, at least 256 threads, level_vec 0
+                               vectors, at least 512 threads, level_vec 0
                                or the 16-byte width); > 0 = every wave
                                stages loads through registers.  Fused
                                form: 0 = wave-specialised (two wavefronts

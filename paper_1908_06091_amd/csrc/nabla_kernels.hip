@@ -1365,7 +1365,10 @@ constexpr int kSweepwGroupWaves = 2; // waves of a group
 constexpr int kSweepwLead = kSweepwSlots - 2;     // run q + lead issued at step q; field
                                                   // ring: runs q-1 .. q+lead
 constexpr int kSweepwGeoSlots = kSweepwLead + 1;  // record ring: runs q .. q+lead
-// lanes past a short last chunk read up to this far past their row
+// Lanes without an element read past their row: LPN * NE elements from its
+// start, less than LPN (32) more than the plan's chunk has.  Rows of a shorter
+// last chunk start earlier by more than they are shorter, so no read ends
+// further than this past the space of its ring.
 constexpr int kSweepwLdsTail = 32 * 16;
 
 __device__ __forceinline__ void lds_dma16(const i32x4 &rsrc, void *lds_wave_base, int voff) {
@@ -2944,7 +2947,8 @@ struct SweepwPlan {
 // on whole tiles 5.19 ms, whole columns on thirds 5.44).  Of a small mesh's
 // cuts of the bands the one whose rounds of workgroups take the fewest
 // steps (a last round that is nearly empty costs a whole one: O160, 37
-// levels, FP32 divergence, 520 pieces on 512 places 33 us, 500 pieces 23).
+// levels, FP32 divergence, 520 pieces on 512 places 33.8 us, 390 27.5, 260
+// 35.6).
 // `want`: at most so many vectors per chunk; epv: elements per vector.
 static SweepwPlan sweepw_plan(const MeshStore &ms, bool vec, bool whole, int epv, int max_ne,
                               int nvec, int want) {
@@ -3031,7 +3035,7 @@ static SweepwPlan sweepw_plan(const MeshStore &m, int nlev, int level_chunk) {
 // Where the wave-specialised sweep is the built-in shape: on large meshes, and
 // wherever its pieces fill the chip.  Columns that leave room for two
 // workgroups per compute unit ask for 64 tiles (in up to six bands each;
-// O160 has 130: 37 levels, FP32 divergence 27.7 against 32 us for the column
+// O160 has 130: 37 levels, FP32 divergence 27.5 against 35.6 us for the column
 // form; O80 has 39: 16 against 11 us), longer ones and those above 48 levels
 // (O160, 91 levels, FP32 gradient: 43 against 34 us) for 600 pieces and chunks
 // of whole bands (O320 has 460 tiles: 920 pieces, 137 levels, FP64 gradient
@@ -3129,11 +3133,14 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     // large meshes have blocks enough: more positions in each fetch fewer
     // neighbours from other blocks (O1280, FP32 gradient, 3 levels: 426 us at
     // 64 positions on 512 threads, 372 at 256 on 1024; one level, FP64: 333,
-    // 321 at 128, 341 at 256; F640, FP64 gradient, 2 levels 190 and 170, 20
-    // levels 1059 and 992).  (Smaller meshes in smaller tiles: O320 one level
-    // 21.3 us, 23.8 at 128, 22.0 at 256.)
+    // 321 at 128, 341 at 256; F640, FP64 gradient, 2 levels 190 and 170), but
+    // from 5 levels no more than one value per thread: 256 positions of 5 leave
+    // three quarters of the second pass idle (O500, FP32 gradient: 73.1 us, 69.7
+    // at 64 on 512 threads, 64.6 at 204; F640 288, 279, 236; 9 levels 450, 447,
+    // 394; FP64, 20 levels 992, 1060, 958).  (Smaller meshes in smaller tiles:
+    // O320 one level 21.3 us, 23.8 at 128, 22.0 at 256.)
     s.block = 1024;
-    s.nodes_per_block = nlev == 1 && m.d.V >= 750000 ? 128 : 256;
+    s.nodes_per_block = nlev == 1 && m.d.V >= 750000 ? 128 : min(256, 1024 / nlev);
   }
   // (the register-staged sweep; on tiles of 250 nodes O640, 60 levels, FP64
   // gradient 1177 against 765 us for the column form)

@@ -288,3 +288,15 @@ result = [fused, [[n[0] for n in c] for c in dc]]
              for c in dc]
     assert forms == (["flat"] * 2 + ["sweepw"] * 4 + ["colvI", "sweepw"] + ["colvI"] * 2 +
                      ["sweepw", "colv_dc"] * 5)
+
+
+@pytest.mark.parametrize("nlev,positions", [(2, 256), (3, 256), (4, 256), (5, 204)])
+def test_flat_blocks_of_large_meshes(nlev, positions):
+    """A block's values are one pass of its threads, or a part of one."""
+    V, launch = on_host(f"""
+m = P.Mesh(500)
+result = [int(m.info.nnodes), apply(m, GRAD, {nlev}, F32)[-1]]
+""")
+    name, blocks, threads, _ = launch
+    per = (V + positions - 1) // positions
+    assert "k_flat" in name and threads == 1024 and blocks == (per + 7) // 8 * 8
