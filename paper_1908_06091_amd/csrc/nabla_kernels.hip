@@ -3167,11 +3167,20 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
         m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 33)
         : f64 ? values >= 5000000 && (m.d.ntiles >= 180 || nlev > (m.d.ntiles >= 100 ? 128 : 160))
               : values >= (m.d.ntiles >= 300 ? 25000000 : 36000000) && nlev >= 64;
+    // Small tiles form most gradients several times over: from 48 nodes a tile,
+    // in FP64 with values enough for each tile's walk (O320 in tiles of 63: 4
+    // levels 117 against 62 us, 8: 113 against 103, 16: 142 against 190; in tiles
+    // of 125, 4 levels 73 against 61, 8: 71 against 101; in tiles of 16, 37
+    // levels 519 against 337, 260: 4612 against 2027), in FP32 below 96 nodes up
+    // to 96 levels (tiles of 63: 64 levels 249 against 273, 100: 569 against 385).
+    const int64_t tiles = m.d.ntiles;
+    const bool wide = m.d.V >= 48 * tiles &&
+                      (f64 ? values >= 700 * tiles : m.d.V >= 96 * tiles || nlev <= 96);
     FusedwPlan fw;
     LaunchShape fs;
     fs.variant = ATLAS_VARIANT_FUSED;
     fs.block = kLswBlock;
-    if (worth && m.d.ntiles >= kSweepFewTiles &&
+    if (worth && wide && m.d.ntiles >= kSweepFewTiles &&
         (f64 ? fusedw_plan<double>(m, nlev, fs, &fw) : fusedw_plan<float>(m, nlev, fs, &fw))) {
       fs.block = max(512, fw.block);
       return fs;

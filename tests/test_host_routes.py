@@ -300,3 +300,19 @@ result = [int(m.info.nnodes), apply(m, GRAD, {nlev}, F32)[-1]]
     name, blocks, threads, _ = launch
     per = (V + positions - 1) // positions
     assert "k_flat" in name and threads == 1024 and blocks == (per + 7) // 8 * 8
+
+
+def test_fused_laplacian_on_small_tiles():
+    """Tiles of few nodes form most gradients several times over: two passes,
+    except for column lengths that repay it."""
+    result = on_host("""
+result = []
+for layout, calls in (((4, 4), [(4, F64), (37, F64), (260, F64), (64, F32)]),
+                      ((8, 8), [(4, F64), (8, F64), (12, F64), (137, F64), (64, F32), (96, F32),
+                                (97, F32), (260, F32)]),
+                      ((8, 16), [(4, F64), (6, F64), (137, F32)])):
+    m = P.Mesh(320, layout=layout)
+    result += [len(apply(m, LAPL, nlev, dt)) for nlev, dt in calls]
+    m.close()
+""")
+    assert result == [2, 2, 2, 2] + [2, 2, 1, 1, 1, 1, 2, 2] + [2, 1, 1]
