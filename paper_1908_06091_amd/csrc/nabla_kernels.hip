@@ -3045,23 +3045,41 @@ static SweepwPlan sweepw_plan(const MeshStore &m, int nlev, int level_chunk) {
 // Short columns leave it bound by what a piece costs whatever its levels: the
 // records of its nodes, 144 bytes each, which the flat form's blocks read
 // less of and share in the caches, and each tile's walk (O320 cut in 3360
-// tiles of 125 nodes: 45 us against 29.5 on its 460 own ones).  `pair`: for two
-// results (the one-pass divergence and curl, which the flat form takes twice
+// tiles of 125 nodes, 4 levels: 45 us against 32 for the flat form).  `pair`: for
+// two results (the one-pass divergence and curl, which the flat form takes twice
 // as long for: O500, 2 levels, 71 against 155 us), from its first vector on.
-// For one: from 5 levels (6 of an FP32 scalar, 4 to a vector) and a number of
-// values that grows with the tiles, FP32 scalars' a little larger (O500 FP64
-// gradient 2 levels 58 against 44 us, 4: 60 against 55, 5: 60 against 75; O320
-// FP32 gradient 4 levels 31 against 24 us, 6: 31.1 against 31.5; O160 10 levels,
-// FP64 gradient 18 against 15.3 us; O200 10 levels 22.7 against 25.8).  On
-// meshes above 1.5 M nodes, whose geometry the caches no longer hold, from
-// fewer (O640, FP32 divergence 2 levels 90 against 80 us, FP64 gradient 3 levels
-// 89 against 98; O900 2 levels 155 against 171), and vector columns in FP64 at
-// once (O1280, one level, 304 against 377 us).
+// For one: from a few levels and a number of values that grows with the tiles
+// (inputs that are not in the caches; FP64 gradient: O320 4 levels 31 against
+// 30 us, O400 39 against 45; O500 3 levels 61 against 57, but the Laplacian's two
+// passes 129 against 144; 3360 tiles, 8 levels 49
+// against 50, 10: 55 against 64; divergence: O320 4 levels 29 against 34; 3360
+// tiles, 5 levels 44 against 42, 7: 45 against 54; FP32 gradient: O160 14 levels
+// 16 against 18, O256 6 levels 24 against 22, 7: 24 against 26; 3360 tiles, 8
+// levels 49 against 42, 10: 49 against 54; divergence: 3360 tiles, 6 levels 46
+// against 44, 7: 46 against 52).  On meshes above 1.5 M nodes, whose geometry the
+// caches no longer hold, from a little less (O640, FP32 divergence 2 levels 90
+// against 80 us, FP64 gradient 3 levels 89 against 98; O900 2 levels 155 against
+// 171), and vector columns in FP64 at once (O1280, one level, 304 against 377 us).
 //
-// Tiles of fewer than 96 nodes are left to the other forms (O160 in tiles of
-// 61 nodes, 60 levels, FP64 gradient 46 against 33 us), and FP32 vector columns
-// above 96 levels, which take several chunks, those of fewer than 192 (O320 in
-// tiles of 125, 200 levels, divergence 391 against 370).
+// Tiles of fewer than 96 nodes read more records than columns: they are left
+// to the other forms (O160 in tiles of 61 nodes, FP32, 60 levels: divergence 49
+// against 39 us, gradient 52 against 36; FP64: divergence 57 against 53), except
+// where those read the columns in several passes or parts (sweepw_least_nodes).
+static int sweepw_least_nodes(bool pair, bool grad, bool f32, int nlev) {
+  if (pair) {
+    // no one-pass column form from 16 to 47 levels (tiles of 32, O320: FP64, 37
+    // levels, 257 against 354 us), nor a flat one (tiles of 61, O160: 14 levels
+    // 47 against 53); FP64 above 256: columns in parts (323 against 692)
+    if ((nlev >= 16 && nlev < 48) || (!f32 && nlev > 256)) return 30;
+    return nlev >= 5 && nlev < 16 ? 48 : 96;
+  }
+  if (!grad) return !f32 && nlev > 256 ? 30 : 96;  // (tiles of 61: 217 against 348)
+  // gradients: FP64 from 42 levels (tiles of 61: 60 levels 51 against 59 us, 137:
+  // 103 against 121; of 32 nodes, 91 levels 252 against 290, 137: 471 against
+  // 444), FP32 from 161 to 240 (170 levels 61 against 73, 137: 73 against 61)
+  if (f32) return nlev > 160 && nlev <= 240 ? 48 : 96;
+  return nlev < 42 ? 96 : nlev <= 112 ? 30 : 48;
+}
 static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int nlev, bool pair,
                            LaunchShape *s) {
   const DevMesh &m = ms.d;
@@ -3072,15 +3090,23 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
   const bool large = m.ntiles >= kSweepMinTiles;
   const bool f32 = dt == ATLAS_F32;
   const int64_t values = (int64_t)m.V * nlev, tiles = m.ntiles;
-  // (the one pass over 20 to 47 levels, which has no column form, on smaller
-  // tiles too: O160 in tiles of 61 nodes, 37 levels, FP64 58 against 69 us)
-  if (m.V < (pair && nlev >= 20 && nlev < 48 ? 48 : 96) * tiles || (f32 && !grad && nlev > 96 && m.V < 192 * tiles)) return false;
+  if (m.V < sweepw_least_nodes(pair, grad, f32, nlev) * tiles) return false;
+  // (FP32 vector columns of several chunks on tiles of fewer than 192 nodes,
+  // where the column form's two or four levels per lane hold the whole column:
+  // O320 in tiles of 125, 104 levels, 209 against 180 us, 137: 259 against 272,
+  // 200: 398 against 346; one pass: 104 levels 366 against 238, 200: 640 against
+  // 423)
+  if (f32 && !grad && m.V < 192 * tiles &&
+      (pair ? nlev > 96 : (nlev > 96 && nlev <= 128) || (nlev > 192 && nlev <= 256)))
+    return false;
   if (pair) {
     if (!large && values < 1500000) return false;
   } else if (m.V >= 1500000) {
     if (values < (f32 || grad ? 3000000 : 0) + 900 * tiles) return false;
-  } else if (nlev < (f32 && grad ? 6 : 5) ||
-             values < (f32 && grad ? 1800000 : 1300000) + 900 * tiles) {
+  } else if (grad ? nlev < (f32 ? 5 : m.V >= 750000 ? 3 : 4) || values < (f32 ? 1400000 + 800 * tiles
+                                                          : 1300000 + 700 * tiles)
+                  : nlev < (f32 ? 5 : 3) || values < (f32 ? 1300000 + 470 * tiles
+                                                          : 1150000 + 400 * tiles)) {
     return false;
   }
   const SweepwPlan p = dt == ATLAS_F64 ? (grad ? sweepw_plan<double, OP_GRAD, false>(ms, nlev, 0)
@@ -3088,10 +3114,17 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
                                        : (grad ? sweepw_plan<float, OP_GRAD, false>(ms, nlev, 0)
                                                : sweepw_plan<float, OP_DIV, false>(ms, nlev, 0));
   if (p.lds > kMaxLds) return false;
-  // (FP32 columns of several chunks fill the chip no better than one: O200,
-  // 582 parts, 220 levels, divergence 180 against 151 us for the column form)
-  if (!large && (nlev > 48 || 2 * p.lds > kMaxLds) &&
-      m.ntiles * ms.cuts[p.cut].parts * (f32 ? 1 : p.nchunk) < 600)
+  // (several chunks make several pieces of a part, but FP32 columns have the
+  // column form's lane vectors beside them, which hold up to 256 levels: there on
+  // 250000 nodes and more, or above that, and where the last round of pieces is not
+  // too empty: O256 200 levels 202 against 227 us, O220 184 against 170, 280 levels
+  // 241 against 262; O200's 776 pieces are a little more than three rounds: 178
+  // against 154, 280 levels 224 against 217)
+  const int64_t parts = (int64_t)m.ntiles * ms.cuts[p.cut].parts;
+  const int64_t pieces = parts * p.nchunk, cus = device_cu_count();
+  const bool chunks = !f32 || ((m.V >= 250000 || nlev >= 256) &&
+                               9 * pieces >= 7 * cus * ((pieces + cus - 1) / cus));
+  if (!large && (nlev > 48 || 2 * p.lds > kMaxLds) && (chunks ? pieces : parts) < 600)
     return false;
   s->variant = ATLAS_VARIANT_SWEEP;
   s->block = max(512, p.block);
@@ -3147,6 +3180,14 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   const bool sweep_fits = m.d.sweep_ok && m.d.ntiles >= kSweepMinTiles &&
                           m.d.V >= 512 * (int64_t)m.d.ntiles &&
                           max(1, m.d.segmax) * kGeoWords <= 768;
+  auto staged = [](LaunchShape v) {
+    v.variant = ATLAS_VARIANT_SWEEP;
+    v.block = 768;
+    v.nodes_per_block = 0;
+    v.blocks_per_cu = 1;
+    v.level_vec = 0;
+    return v;
+  };
   if (op == ATLAS_OP_LAPLACIAN) {
     // the fused one-pass form, wave-specialised, where it beats the two
     // passes on their own shapes: on large meshes from 4 levels in FP64
@@ -3154,28 +3195,32 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     // 33 in FP32 (24 levels: 1.46 against 1.22 ms, 40: 1.78 against 1.75,
     // 63: 2.19 against 3.15, 137: 4.85 against 5.65; it needs no workspace);
     // on small ones with work enough to hide its longer walk and pieces enough
-    // to fill the chip (FP64: O320, 37 levels, 158 against 291 us; O200 has 194
-    // tiles: 60 levels 119 against 140; O160 130: 80 levels 119 against 113, 100
-    // 157 against 137, 137 levels, which the passes' columns take in three chunks
-    // of lanes, 187 against 245; O120 79: 129 levels 111 against 106, 170 118
-    // against 141; FP32: O320, 80 levels 268 against 363; O256 has
-    // 304: 120 levels 223 against 274; O200, 200 levels, 305 against 280, 300 349
-    // against 643; O160 151 against 122)
+    // to fill the chip (FP64: O320, 37 levels, 149 against 292 us; O120, 62000
+    // nodes: 80 levels 86 against 85, 96: 86 against 97, 137: 114 against 144;
+    // O160 60 levels 102 against 110, 128 161 against 206; O180 37 levels, 5 M
+    // values, 96 against 77, 47: 88 against 118; O200, 167000 nodes, 37 levels 79
+    // against 90, 40: 103 against 95; FP32: O320, 64 levels 158 against 274,
+    // 40: 131 against 127; O220 112 levels, 23 M values, 165 against 175, 137:
+    // 187 against 244; O160 240 levels, 26 M, 205 against 199, 300 235 against
+    // 271)
     const bool f64 = dt == ATLAS_F64;
     const int64_t values = (int64_t)m.d.V * nlev;
     const bool worth =
         m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 33)
-        : f64 ? values >= 5000000 && (m.d.ntiles >= 180 || nlev > (m.d.ntiles >= 100 ? 128 : 160))
-              : values >= (m.d.ntiles >= 300 ? 25000000 : 36000000) && nlev >= 64;
-    // Small tiles form most gradients several times over: from 48 nodes a tile,
-    // in FP64 with values enough for each tile's walk (O320 in tiles of 63: 4
-    // levels 117 against 62 us, 8: 113 against 103, 16: 142 against 190; in tiles
-    // of 125, 4 levels 73 against 61, 8: 71 against 101; in tiles of 16, 37
-    // levels 519 against 337, 260: 4612 against 2027), in FP32 below 96 nodes up
-    // to 96 levels (tiles of 63: 64 levels 249 against 273, 100: 569 against 385).
+        : f64 ? values >= 5000000 && (m.d.V >= 150000 || nlev > 40)
+              : values >= 25000000 && nlev >= 64;
+    // Small tiles form most gradients several times over: from 48 nodes a tile
+    // (30 where the two passes' columns take two of 64 lanes or more parts), in
+    // FP64 with values enough for each tile's walk (O640 in tiles of 63: 4 levels
+    // 417 against 271 us, 8: 416 against 446; of 127, 4 levels 251 against 266;
+    // of 32: 37 levels 1223 against 1417, 64: 2234 against 1748; of 16, O320:
+    // 37 levels 519 against 337, 260: 4612 against 2027), in FP32 below 96 nodes up
+    // to 96 levels (O320 in tiles of 63: 64 levels 249 against 273, 100: 569
+    // against 385).
     const int64_t tiles = m.d.ntiles;
-    const bool wide = m.d.V >= 48 * tiles &&
-                      (f64 ? values >= 700 * tiles : m.d.V >= 96 * tiles || nlev <= 96);
+    const int least = f64 && ((nlev >= 16 && nlev <= 56) || nlev > 256) ? 30 : 48;
+    const bool wide = m.d.V >= least * tiles &&
+                      (f64 ? values >= 505 * tiles : m.d.V >= 96 * tiles || nlev <= 96);
     FusedwPlan fw;
     LaunchShape fs;
     fs.variant = ATLAS_VARIANT_FUSED;
@@ -3196,13 +3241,32 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   // long enough to hide each step's loads repay the walk.  FP32 gradient:
   // 20 to 79 levels (O1280: 16 levels 1560 against 1370 us for the flat form,
   // 20: 1589 against 1785, 37: 1590 against 2177 for the column form, 64: 1834
-  // against 2380, 80: 2682 against 2618); FP64 gradient from 48 (below).
-  if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT && sweep_fits && nlev >= 20 && nlev < 80) {
-    s.variant = ATLAS_VARIANT_SWEEP;
-    s.block = 768;
-    s.nodes_per_block = 0;
-    s.blocks_per_cu = 1;
-    return s;
+  // against 2380, 80: 2706 against 2683); FP64 gradient from 48 (below).
+  if (dt == ATLAS_F32 && op == ATLAS_OP_GRADIENT && sweep_fits && nlev >= 20 && nlev < 80)
+    return staged(s);
+  // The derivatives in longitude and latitude also take it for longer columns,
+  // from levels that grow as the tiles get fewer -- but not from 241 to 256
+  // levels, whose last chunk is short (FP32, O640, 240 levels 1011 against 1273
+  // us, 256: 1868 against 1354; FP64, O320, 879 against 681).  FP32: from 161
+  // levels, up to 256 of which the column form holds in one level per lane
+  // (O500, 160 levels 612 against 553, 185: 622 against 666; O640 892 against
+  // 1090; O320 170 levels 246 against 257, 280: 481 against 515; O256 240 levels
+  // 272 against 227); on more than 1.5 M nodes from 100 (O640, 120 levels 772
+  // against 799; O900 91 levels 1450 against 1337), 4 M from 80 (O1280, 120 levels
+  // 2887 against 3136).  On tiles of fewer than 512 nodes later (O320 in tiles of
+  // 367: FP32, 185 levels 278 against 275, 240: 312 against 336; FP64, 80 levels
+  // 257 against 252, 120: 298 against 344).  FP64: O400, 60 levels 332 against
+  // 350; O320, 97 levels 265 against 295, 120: 280 against 357; O256, 160 levels
+  // 329 against 319, 200: 353 against 378; O220, 210 levels 255 against 294.
+  const bool f32 = dt == ATLAS_F32;
+  if (!packed && op == ATLAS_OP_GRADIENT && m.d.sweep_ok &&
+      max(1, m.d.segmax) * kGeoWords <= 768 && (nlev <= 240 || nlev > 256) &&
+      m.d.V >= (nlev > (f32 ? 200 : 90) ? 320 : 512) * (int64_t)m.d.ntiles) {
+    const int t = m.d.ntiles;
+    if (f32 ? t >= 400 && nlev >= (m.d.V >= 4000000 ? 80 : m.d.V >= 1500000 ? 100 : 161)
+            : t >= 220 && nlev >= (t >= kSweepMinTiles ? 48 : t >= 650 ? 60
+                                   : t >= 400 ? 100 : 180))
+      return staged(s);
   }
   if (nlev < 24) return s;
   if (nlev < 48) {
@@ -3221,10 +3285,7 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
   if (dt == ATLAS_F64 && op == ATLAS_OP_GRADIENT && sweep_fits) {
     // (O1280: 64 levels 2953 against 3205 us for the column form, 137: 5891
     // against 7185)
-    s.variant = ATLAS_VARIANT_SWEEP;
-    s.block = 768;
-    s.nodes_per_block = 0;
-    s.blocks_per_cu = 1;
+    return staged(s);
   }
   return s;
 }
@@ -3521,11 +3582,14 @@ static atlas_status launch_div_curl_typed(const MeshStore &ms, atlas_dtype dt, c
         !sweepw_builtin(ms, ATLAS_OP_DIVERGENCE, dt, nlev, true, &sh))
       sh = default_shape(ms, ATLAS_OP_DIVERGENCE, nlev, dt);
     if (sh.variant == ATLAS_VARIANT_SWEEP && sweepw_applies<T, OP_DIV>(m, nlev, sh)) {
-      // (FP32 columns of several chunks: on large meshes only; O1280, 137
-      // levels 4.93 against 5.31 ms for the column form, O320 380 against
-      // 345 us)
+      // (FP32 columns of several chunks: on large meshes (O1280, 137 levels 4.93
+      // against 5.31 ms for the column form, O320 380 against 345 us), and where
+      // that form leaves half of its lane vectors' last one idle or reads the
+      // column in parts: O320 in tiles of 367 nodes, 137 levels 347 against 333 us,
+      // 185: 357 against 413, 200: 504 against 431, 260: 526 against 667)
       const SweepwPlan p = sweepw_plan<T, OP_DIV, true>(ms, nlev, sh.level_chunk);
-      if (p.lds <= kMaxLds && (p.nchunk == 1 || sizeof(T) == 8 || m.V >= 750000)) {
+      if (p.lds <= kMaxLds && (p.nchunk == 1 || sizeof(T) == 8 || m.V >= 750000 ||
+                               (nlev > 160 && nlev <= 192) || nlev > 256)) {
         sh.block = max(512, p.block);
         return launch_sweepw<T, OP_DIV, true>(ms, in, od, oc, nlev, sh, st);
       }
@@ -3679,10 +3743,13 @@ static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fu
     // such workgroups fit (O1280: FP64, 80 levels in three chunks of 14 on half
     // tiles 4.47 ms, two of 20 5.60; 60 levels 3.02 against 3.19, 120 5.96 against
     // 6.41; 100 levels in three of 17 8.01 against 6.36, in four of 13 5.96; FP32,
-    // 170 levels 5.82 against 7.04, 100 3.91 against 4.20).
+    // 170 levels 5.82 against 7.04, 100 3.91 against 4.20).  Not three for one (75
+    // levels, one of 38 3.68 ms, three of 13 4.43; FP32, 150: 4.88 against 5.84),
+    // and not on tiles of fewer than 512 nodes, whose halves form more gradients
+    // twice (O320 in tiles of 368: FP32, 100 levels, 341 against 359 us).
     bool pair = false;
-    if (sh.level_chunk == 0 && 2 * bytes(vpc) > kMaxLds) {
-      for (int n = nchunk + 1; n <= nchunk + 2 && !pair; ++n) {
+    if (sh.level_chunk == 0 && m.V >= 512 * (int64_t)m.ntiles && 2 * bytes(vpc) > kMaxLds) {
+      for (int n = nchunk + 1; n <= min(nchunk + 2, 2 * nchunk) && !pair; ++n) {
         const int c = (nvec + n - 1) / n;
         if (c >= 13 && c <= 16 && fits(c) && 2 * bytes(c) <= kMaxLds) {
           vpc = c;
@@ -3706,12 +3773,16 @@ static bool fusedw_plan(const MeshStore &ms, int nlev, const LaunchShape &sh, Fu
     // the chunk, as in the sweep -- but not eight lanes with four elements or
     // more: eight positions a wavefront leave a run of 34 to four or five of
     // the wavefronts, each with a long chain (O1280, 30 levels, 1.91 ms, on 16
-    // lanes 1.60; O500, 37 levels, 522 against 468 us).
+    // lanes 1.60; O500, 37 levels, 522 against 468 us; FP32, 80 levels, O640 1062
+    // against 949) -- except 34 to 36 elements in FP32, of which 16 lanes take
+    // three with a quarter of them idle (O640, 72 levels, 655 against 698 us;
+    // FP64, 36 levels, 545 against 527).
     const int nel = p.vpc * 2;
     int cost = INT_MAX;
     for (int l : {8, 16, 32}) {
       const int e = (nel + l - 1) / l;
-      if (e <= (l == 8 ? 3 : kLswMaxNe) && (e + 3) * l < cost) {
+      const bool lanes8 = e <= 3 || (sizeof(T) == 4 && e == 5 && nel <= 36);
+      if ((l > 8 || lanes8) && e <= kLswMaxNe && (e + 3) * l < cost) {
         cost = (e + 3) * l;
         p.lpn = l;
         p.ne = e;

@@ -5,30 +5,27 @@ import pytest
 from host_util import on_host
 
 
-@pytest.mark.parametrize("N", [160, 320])
-def test_gradient_lonlat_below_a_thousand_tiles(N):
+@pytest.mark.parametrize("N,layout,first", [
+    # first levels of the register-staged sweep (FP64, FP32)
+    (160, None, (999, 999)), (240, None, (180, 999)), (320, None, (100, 161)),
+    (400, None, (60, 161)), (500, None, (48, 161)), (320, (16, 24), (91, 201)),
+    (320, (8, 16), (999, 999)),
+])
+def test_gradient_lonlat(N, layout, first):
     """d/dlon and d/dlat read their scales by position, so the packed sweep
-    cannot serve them, and the register-staged one leaves most of the chip
-    idle on a mesh of a few hundred tiles: flat and column forms."""
+    cannot serve them, and the register-staged one needs many tiles or long
+    columns: flat and column forms before.  (FP32 from 20 to 79 levels on large
+    meshes besides; not 241 to 256 levels.)"""
     result = on_host(f"""
-m = P.Mesh({N})
+m = P.Mesh({N}, layout={layout!r})
 result = [(nlev, dt, launches(L.atlas_nabla_gradient_lonlat, m.handle, IN, nlev, dt, OUT, None)[-1][0])
-          for nlev in (1, 4, 12, 23, 24, 37, 64, 137, 200) for dt in (F64, F32)]
+          for nlev in (1, 4, 12, 19, 20, 23, 24, 37, 47, 48, 59, 60, 79, 80, 90, 91, 99, 100, 137,
+                       160, 161, 179, 180, 200, 201, 240, 241, 256, 257, 300) for dt in (F64, F32)]
 """)
     for nlev, dt, kernel in result:
-        assert ("k_flat" if nlev < 24 else "k_col") in kernel, (nlev, dt, kernel)
-
-
-def test_gradient_lonlat_on_many_tiles():
-    """A mesh of a thousand tiles and more: the register-staged sweep from 20
-    levels in FP32 (to 79) and from 48 in FP64."""
-    result = on_host("""
-m = P.Mesh(500)
-result = [(nlev, dt, launches(L.atlas_nabla_gradient_lonlat, m.handle, IN, nlev, dt, OUT, None)[-1][0])
-          for nlev in (1, 4, 12, 19, 20, 23, 24, 47, 48, 79, 80, 137, 200) for dt in (F64, F32)]
-""")
-    for nlev, dt, kernel in result:
-        staged = nlev >= 48 if dt == 1 else 20 <= nlev < 80
+        staged = nlev >= first[1 - dt] and not 240 < nlev <= 256
+        if N == 500:
+            staged |= (dt == 0 and 20 <= nlev < 80) or (dt == 1 and nlev >= 48)
         want = "k_sweepv" if staged else "k_flat" if nlev < 24 else "k_col"
         assert want in kernel, (nlev, dt, kernel)
 
@@ -43,10 +40,11 @@ result = [apply(m, op, nlev, dt)[-1][0] for op, nlev, dt in {calls!r}]
 @pytest.mark.parametrize("N,layout,calls", [
     # (operator, levels, dtype) of calls too short for the sweep, and the
     # shortest that take it
-    (500, None, [(0, 2, 1), (0, 4, 1), (1, 2, 0), (1, 4, 0), (0, 5, 0)]),
-    (320, None, [(0, 4, 1), (0, 5, 0), (1, 4, 0), (1, 1, 1)]),
+    (500, None, [(0, 2, 1), (1, 2, 1), (1, 4, 0), (0, 4, 0)]),
+    (320, None, [(0, 3, 1), (0, 4, 0), (1, 4, 0), (1, 3, 1)]),
     (640, None, [(0, 2, 1), (1, 2, 0)]),
-    (320, (8, 16), [(0, 3, 1), (0, 8, 0), (1, 3, 0), (1, 1, 1)]),
+    (320, (8, 16), [(0, 8, 1), (0, 9, 0), (1, 6, 0), (1, 5, 1)]),
+    (160, None, [(0, 12, 1), (0, 13, 0), (1, 12, 0), (1, 11, 1)]),
     (160, (8, 8), [(0, 3, 1), (0, 10, 0), (1, 20, 0), (1, 1, 1)]),
 ])
 def test_short_columns_keep_the_flat_form(N, layout, calls):
@@ -55,10 +53,13 @@ def test_short_columns_keep_the_flat_form(N, layout, calls):
 
 
 @pytest.mark.parametrize("N,layout,calls", [
-    (500, None, [(0, 5, 1), (1, 5, 1), (0, 6, 0), (1, 5, 0)]),
-    (320, None, [(0, 5, 1), (0, 6, 0), (1, 5, 0)]),
+    (500, None, [(0, 3, 1), (1, 3, 1), (0, 5, 0), (1, 5, 0)]),
+    (320, None, [(0, 4, 1), (0, 5, 0), (1, 5, 0), (1, 4, 1)]),
     (640, None, [(0, 3, 1), (1, 1, 1), (1, 3, 0), (0, 4, 0)]),
-    (320, (8, 16), [(0, 20, 1), (0, 20, 0), (1, 60, 0)]),
+    (320, (8, 16), [(0, 9, 1), (0, 10, 0), (1, 7, 0), (1, 6, 1), (1, 137, 0), (1, 260, 0)]),
+    (160, None, [(0, 13, 1), (0, 14, 0), (1, 13, 0), (1, 12, 1)]),
+    (160, (8, 8), [(0, 60, 1), (1, 260, 1), (0, 170, 0)]),
+    (256, None, [(1, 193, 0), (1, 200, 0)]), (180, None, [(1, 260, 0)]),
 ])
 def test_longer_columns_take_the_sweep(N, layout, calls):
     for call, kernel in zip(calls, _forms(N, layout, calls)):
@@ -66,7 +67,11 @@ def test_longer_columns_take_the_sweep(N, layout, calls):
 
 
 def test_columns_on_small_tiles_keep_the_column_form():
-    for kernel in _forms(160, (8, 8), [(0, 60, 1), (1, 137, 0), (0, 200, 1)]):
+    for kernel in _forms(160, (8, 8), [(0, 37, 1), (1, 137, 0), (1, 60, 1), (0, 60, 0)]):
+        assert "k_col" in kernel, kernel
+    for kernel in _forms(320, (8, 16), [(1, 104, 0), (1, 200, 0)]):
+        assert "k_col" in kernel, kernel
+    for kernel in _forms(200, None, [(1, 220, 0), (1, 260, 0)]):
         assert "k_col" in kernel, kernel
 
 
@@ -107,9 +112,14 @@ result.append(launches(L.atlas_nabla_div_curl, m.handle, IN, 200, F32, OUT, OUT2
     (640, 170, 0, 16, 2, 3440 * 3, 72800),
     # 72 levels would leave chunks of 12
     (640, 72, 1, 16, 5, 3440, 154208),
-    # not eight lanes with four or five elements
+    # one chunk of 38 stays one
+    (640, 75, 1, 16, 5, 3440, 162016),
+    # not eight lanes with four or five elements ...
     (640, 30, 1, 16, 2, 1720, 133920),
+    (640, 36, 1, 16, 3, 1720, 155616),
     (640, 80, 0, 16, 3, 3440, 92320),
+    # ... but for 34 to 36 of FP32
+    (640, 72, 0, 8, 5, 1720, 156704),
 ])
 def test_fused_laplacian_chunks(N, nlev, dt, lanes, elements, pieces, lds):
     (name, blocks, threads, used), = on_host(f"""
@@ -122,10 +132,12 @@ result = apply(m, LAPL, {nlev}, {dt})
 
 
 @pytest.mark.parametrize("N,nlev,dt,fused", [
-    (160, 47, 1, False), (160, 80, 1, False), (160, 128, 1, False), (160, 129, 1, True),
-    (120, 100, 1, False), (120, 160, 1, False), (120, 161, 1, True),
+    (160, 46, 1, False), (160, 47, 1, True), (160, 128, 1, True),
+    (120, 80, 1, False), (120, 81, 1, True),
+    (180, 37, 1, False), (180, 47, 1, True), (200, 30, 1, True), (180, 40, 1, False),
     (200, 60, 1, True), (320, 37, 1, True),
-    (200, 170, 0, False), (200, 300, 0, True), (320, 80, 0, True), (256, 137, 0, True),
+    (200, 149, 0, False), (200, 150, 0, True), (220, 124, 0, False), (220, 137, 0, True),
+    (320, 63, 0, False), (320, 64, 0, True), (320, 80, 0, True), (256, 137, 0, True),
 ])
 def test_fused_laplacian_on_few_tiles(N, nlev, dt, fused):
     names = [k[0] for k in on_host(f"m = P.Mesh({N})\nresult = apply(m, LAPL, {nlev}, {dt})")]
@@ -282,7 +294,7 @@ dc = [launches(L.atlas_nabla_div_curl, m.handle, IN, nlev, dt, OUT, OUT2, None)
       for nlev in (2, 5, 16, 37, 47, 64, 91, 96, 97, 137) for dt in (F64, F32)]
 result = [fused, [[n[0] for n in c] for c in dc]]
 """)
-    assert fused == [False, False, True, False, True, False, True, False]
+    assert fused == [False, False, True, False, True, False, True, True]
     # 2 levels: flat; 37 and 47 (FP32: 47): two column passes; FP32 above: one
     forms = ["".join(sorted({f for f in ("flat", "sweepw", "colv_dc", "colvI") if f in "".join(c)}))
              for c in dc]
@@ -290,11 +302,11 @@ result = [fused, [[n[0] for n in c] for c in dc]]
                      ["sweepw", "colv_dc"] * 5)
 
 
-@pytest.mark.parametrize("nlev,positions", [(2, 256), (3, 256), (4, 256), (5, 204)])
+@pytest.mark.parametrize("nlev,positions", [(2, 256), (3, 256), (4, 256), (5, 204), (20, 51)])
 def test_flat_blocks_of_large_meshes(nlev, positions):
     """A block's values are one pass of its threads, or a part of one."""
     V, launch = on_host(f"""
-m = P.Mesh(500)
+m = P.Mesh(nx=P.regular_gaussian_nx(400))
 result = [int(m.info.nnodes), apply(m, GRAD, {nlev}, F32)[-1]]
 """)
     name, blocks, threads, _ = launch
