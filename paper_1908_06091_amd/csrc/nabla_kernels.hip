@@ -3073,12 +3073,20 @@ static int sweepw_least_nodes(bool pair, bool grad, bool f32, int nlev) {
     if ((nlev >= 16 && nlev < 48) || (!f32 && nlev > 256)) return 30;
     return nlev >= 5 && nlev < 16 ? 48 : 96;
   }
-  if (!grad) return !f32 && nlev > 256 ? 30 : 96;  // (tiles of 61: 217 against 348)
-  // gradients: FP64 from 42 levels (tiles of 61: 60 levels 51 against 59 us, 137:
-  // 103 against 121; of 32 nodes, 91 levels 252 against 290, 137: 471 against
-  // 444), FP32 from 161 to 240 (170 levels 61 against 73, 137: 73 against 61)
+  if (!grad) {
+    // FP64 above 256 levels: parts again (tiles of 61: 217 against 348); FP32 from 13
+    // to 16, which the flat form takes in two passes (O640 in tiles of 63: 283
+    // against 411, 20: 581 against 516)
+    if (!f32 && nlev > 256) return 30;
+    return f32 && nlev > 12 && nlev <= 16 ? 48 : 96;
+  }
+  // gradients: FP64 from 20 levels (O640 in tiles of 63: 20 levels 396 against 495
+  // us, 37: 674 against 688, 60: 674 against 924; of 32 nodes, O320: 91 levels 252
+  // against 290, 137: 471 against 444), FP32 from 161 to 240 (tiles of 61: 170
+  // levels 61 against 73, 137: 73 against 61)
   if (f32) return nlev > 160 && nlev <= 240 ? 48 : 96;
-  return nlev < 42 ? 96 : nlev <= 112 ? 30 : 48;
+  if (nlev >= 42) return nlev <= 112 ? 30 : 48;
+  return nlev >= 20 && nlev <= 24 ? 48 : 96;
 }
 static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int nlev, bool pair,
                            LaunchShape *s) {
@@ -3102,7 +3110,7 @@ static bool sweepw_default(const MeshStore &ms, atlas_op op, atlas_dtype dt, int
   if (pair) {
     if (!large && values < 1500000) return false;
   } else if (m.V >= 1500000) {
-    if (values < (f32 || grad ? 3000000 : 0) + 900 * tiles) return false;
+    if (values < (f32 || grad ? 3000000 : 0) + 600 * tiles) return false;
   } else if (grad ? nlev < (f32 ? 5 : m.V >= 750000 ? 3 : 4) || values < (f32 ? 1400000 + 800 * tiles
                                                           : 1300000 + 700 * tiles)
                   : nlev < (f32 ? 5 : 3) || values < (f32 ? 1300000 + 470 * tiles
