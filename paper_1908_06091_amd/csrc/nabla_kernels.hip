@@ -3591,10 +3591,11 @@ static atlas_status launch_div_curl_typed(const MeshStore &ms, atlas_dtype dt, c
       sh = default_shape(ms, ATLAS_OP_DIVERGENCE, nlev, dt);
     if (sh.variant == ATLAS_VARIANT_SWEEP && sweepw_applies<T, OP_DIV>(m, nlev, sh)) {
       // (FP32 columns of several chunks: on large meshes (O1280, 137 levels 4.93
-      // against 5.31 ms for the column form, O320 380 against 345 us), and where
-      // that form leaves half of its lane vectors' last one idle or reads the
-      // column in parts: O320 in tiles of 367 nodes, 137 levels 347 against 333 us,
-      // 185: 357 against 413, 200: 504 against 431, 260: 526 against 667)
+      // against 5.31 ms for the column form, O320 380 against 345 us); on smaller
+      // ones where that form's three levels per lane are nearly used up or it
+      // reads the column in parts: O320 in tiles of 367 nodes, 137 levels 347
+      // against 333 us, 185: 357 against 413, 200: 504 against 431, 260: 526
+      // against 667)
       const SweepwPlan p = sweepw_plan<T, OP_DIV, true>(ms, nlev, sh.level_chunk);
       if (p.lds <= kMaxLds && (p.nchunk == 1 || sizeof(T) == 8 || m.V >= 750000 ||
                                (nlev > 160 && nlev <= 192) || nlev > 256)) {
