@@ -795,9 +795,10 @@ class Upload {
       (void)hipGetLastError();
       return fail(ATLAS_ENOMEM, "hipMalloc of mesh store failed");
     }
-    const atlas_status st = copy(static_cast<char *>(p));
-    if (st != ATLAS_OK) (void)hipFree(p);
-    else *block = p;
+    auto give_back = [](void *q) { (void)hipFree(q); };
+    std::unique_ptr<void, decltype(give_back)> held(p, give_back);
+    const atlas_status st = copy(static_cast<char *>(p));  // (may run out of host memory)
+    if (st == ATLAS_OK) *block = held.release();
     return st;
   }
   size_t bytes() const { return std::max<size_t>(256, total_); }
