@@ -3206,34 +3206,23 @@ LaunchShape default_shape(const MeshStore &m, atlas_op op, int nlev, atlas_dtype
     // to fill the chip (FP64: O320, 37 levels, 149 against 292 us; O120, 62000
     // nodes: 80 levels 86 against 85, 96: 86 against 97, 137: 114 against 144;
     // O160 60 levels 102 against 110, 128 161 against 206; O180 37 levels, 5 M
-    // values, 96 against 77, 47: 88 against 118; O200, 167000 nodes, 37 levels 79
-    // against 90, 40: 103 against 95; FP32: O320, 64 levels 158 against 274,
-    // 40: 131 against 127; O220 112 levels, 23 M values, 165 against 175, 137:
+    // values, 89 against 77, 47: 88 against 118; FP32: O320, 64 levels 158 against
+    // 274, 40: 131 against 127; O220 112 levels, 23 M values, 165 against 175, 137:
     // 187 against 244; O160 240 levels, 26 M, 205 against 199, 300 235 against
     // 271)
     const bool f64 = dt == ATLAS_F64;
     const int64_t values = (int64_t)m.d.V * nlev;
     const bool worth =
         m.d.ntiles >= kSweepMinTiles ? nlev >= (f64 ? 4 : 33)
-        : f64 ? values >= 5000000 && (m.d.V >= 150000 || nlev > 40)
-              : values >= 25000000 && nlev >= 64;
-    // Small tiles form most gradients several times over: from 48 nodes a tile
-    // (30 where the two passes' columns take two of 64 lanes or more parts), in
-    // FP64 with values enough for each tile's walk (O640 in tiles of 63: 4 levels
-    // 417 against 271 us, 8: 416 against 446; of 127, 4 levels 251 against 266;
-    // of 32: 37 levels 1223 against 1417, 64: 2234 against 1748; of 16, O320:
-    // 37 levels 519 against 337, 260: 4612 against 2027), in FP32 below 96 nodes up
-    // to 96 levels (O320 in tiles of 63: 64 levels 249 against 273, 100: 569
-    // against 385).
-    const int64_t tiles = m.d.ntiles;
-    const int least = f64 && ((nlev >= 16 && nlev <= 56) || nlev > 256) ? 30 : 48;
-    const bool wide = m.d.V >= least * tiles &&
-                      (f64 ? values >= 505 * tiles : m.d.V >= 96 * tiles || nlev <= 96);
+        : f64 ? values >= 5000000 : values >= 25000000 && nlev >= 64;
+    // (Also where tiles are so small that most gradients are formed several times:
+    // O320 in tiles of 16 nodes, FP64, 37 levels 519 against 337 us.  The two
+    // passes need the gradient's memory, which callers of such meshes do without.)
     FusedwPlan fw;
     LaunchShape fs;
     fs.variant = ATLAS_VARIANT_FUSED;
     fs.block = kLswBlock;
-    if (worth && wide && m.d.ntiles >= kSweepFewTiles &&
+    if (worth && m.d.ntiles >= kSweepFewTiles &&
         (f64 ? fusedw_plan<double>(m, nlev, fs, &fw) : fusedw_plan<float>(m, nlev, fs, &fw))) {
       fs.block = max(512, fw.block);
       return fs;
