@@ -366,6 +366,11 @@ static ItemShape tuned_item_shape(atlas_mesh_t mesh, atlas_op op, const void *in
                              {FORM_COLUMN, 8, 1},  {FORM_COLUMN, 32, 1},
                              {FORM_FLAT, fl, 0},   {FORM_FLAT, std::max(1, fl / 4), 0}};
   for (const ItemShape &c : cands) {
+    // One level per lane leaves most lanes of a short column idle: the kernel
+    // timed here hides that with its many wavefronts, the persistent one, which
+    // holds fewer, does not (36 FP32 items of O48 to O167, seven of them gradients
+    // of 10 levels: a replay takes 1015 us with it, 912 without).
+    if (c.form == FORM_COLUMN && c.level_vec == 1 && nlev < 24) continue;
     const atlas_launch l{c.form == FORM_COLUMN ? ATLAS_VARIANT_COLUMN : ATLAS_VARIANT_FLAT, 256,
                          c.npb, 0, 0, c.level_vec};
     const float t = time_shape(mesh, op, in, nlev, dt, out, ws, l, st, e0, e1);

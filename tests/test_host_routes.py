@@ -333,3 +333,19 @@ for N, layout, calls in ((320, (4, 4), [(4, F64), (37, F64), (260, F64), (64, F3
 """)
     for names in result:
         assert len(names) == 1 and "lsweepw" in names[0], names
+
+
+@pytest.mark.parametrize("nlev,tried", [(10, False), (23, False), (24, True), (137, True)])
+def test_batch_tuning_of_short_columns(nlev, tried):
+    """One level per lane is no candidate for a batch's short columns: what it
+    gains alone it loses in the persistent kernel."""
+    names = on_host(f"""
+m = P.Mesh(48)
+item = (P._abi.WorkItem * 1)()
+item[0].mesh, item[0].op, item[0].nlev, item[0].in_, item[0].out = m.handle, GRAD, {nlev}, IN, OUT
+cfg, batch = P._abi.BatchConfig(F32, 0, 1, 0, 0, -1), ctypes.c_void_p()
+result = [n[0] for n in launches(L.atlas_batch_build, item, 1, ctypes.byref(cfg), None,
+                                 ctypes.byref(batch))]
+""")
+    assert any("k_columnIf" in n for n in names) == tried, names
+    assert any("k_colvIf" in n for n in names) and any("k_flatIf" in n for n in names)
