@@ -186,6 +186,9 @@ atlas_status atlas_mesh_desc_free(atlas_mesh_desc *desc);
 /* Validate `desc`, copy it to the current device (synchronous) and derive
  * the per-node scales.  The host arrays may be freed on return.  The mesh
  * belongs to the library until atlas_mesh_free.
+ * Where the device has no room for the wave-specialised forms' plans and
+ * packed records, the mesh goes without them and its calls take the other
+ * forms.
  * Errors: ATLAS_EINVAL (malformed description: counts, index ranges, CSR
  * order, signs, non-positive volumes, non-finite geometry), ATLAS_ENOMEM,
  * ATLAS_EDEVICE. */

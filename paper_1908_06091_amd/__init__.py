@@ -81,11 +81,11 @@ def _dtype_code(t):
 # are not part of its documented interface).
 def _stream(stream):
     if stream is None:
-        torch = _torch()
+        c = _torch()._C
         try:
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            return c._cuda_getCurrentRawStream(c._cuda_getDevice())
         except AttributeError:
-            stream = torch.cuda.current_stream()
+            stream = _torch().cuda.current_stream()
     return stream.cuda_stream
 
 
